@@ -42,8 +42,8 @@ JOB_CPU_SHARE = 16
 # 2.4 GHz; the datasheet figure counts packed FP32, which these kernels do
 # not use
 PEAK_FP32_UNPACKED_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
-KERNEL_SOURCES = ["paper_2406_01713_amd/csrc/wos_device.hpp", "paper_2406_01713_amd/csrc/wos_kernels.hip",
-                  "paper_2406_01713_amd/csrc/wos_params.hpp"]
+KERNEL_SOURCES = ["paper_2406_01713_amd/csrc/" + f for f in
+                  ("wos_device.hpp", "wos_walk.hpp", "wos_persistent.hip", "wos_kernels.hip", "wos_params.hpp")]
 
 
 def log(*a):

@@ -21,7 +21,11 @@ LIB = os.path.join(PKG, "libwos.so")
 BUILD = os.path.join(ROOT, "_build")
 ARCH = os.environ.get("WOS_OFFLOAD_ARCH", "gfx950")
 
-SOURCES = ["wos_kernels.hip", "wos_api.cpp", "wos_microbench.hip"]
+# (source, macro definitions): the walk kernels are compiled once per
+# variant, so their long compilations run side by side
+SOURCES = [("wos_persistent.hip", ["-DWOS_PERSISTENT_SRC=0"]), ("wos_persistent.hip", ["-DWOS_PERSISTENT_SRC=1"]),
+           ("wos_plain.hip", ["-DWOS_PLAIN_T=float"]), ("wos_plain.hip", ["-DWOS_PLAIN_T=double"]),
+           ("wos_kernels.hip", []), ("wos_api.cpp", []), ("wos_microbench.hip", [])]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-x", "hip",
          *os.environ.get("WOS_EXTRA_FLAGS", "").split(),
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -35,10 +39,11 @@ def _hipcc():
     return h
 
 
-def _compile(src):
+def _compile(unit):
+    src, defs = unit
     os.makedirs(BUILD, exist_ok=True)
-    obj = os.path.join(BUILD, os.path.basename(src) + ".o")
-    cmd = [_hipcc(), *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    obj = os.path.join(BUILD, os.path.basename(src) + "".join(defs).replace("=", "_") + ".o")
+    cmd = [_hipcc(), *FLAGS, *defs, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     noise = "not a recognized feature for this target"
     err = "\n".join(l for l in r.stderr.splitlines() if noise not in l)

@@ -781,7 +781,7 @@ __device__ __forceinline__ T distance(cenv<T> p, const T (&x)[D], int& cls, Work
     const T dga = Math<T>::min(dg, Math<T>::min(da, dout));
     const T tg = Math<T>::min(dga, ub);  // the scans' threshold before the box result
     p = fresh(p);
-    T db;
+    T db = Math<T>::inf();
     uint32_t nb, ns;         // member distances per lane (wave-uniform scans)
     uint64_t eb = 0, es = 0;  // member distances of the wave (pair-compacted scans)
     uint64_t cbt = 0;         // cluster bounding boxes tested by the wave
@@ -813,7 +813,7 @@ __device__ __forceinline__ T distance(cenv<T> p, const T (&x)[D], int& cls, Work
         nb = (uint32_t)fresh(p)->n_box;
     }
     p = fresh(p);
-    T ds;
+    T ds = Math<T>::inf();
     if (p->n_cl_sph) {
         ns = 0;
         bool done = false;

@@ -1,193 +1,23 @@
-// wos_kernels.hip -- Walk-on-Spheres kernels for gfx950 (CDNA4, wave64).
+// wos_kernels.hip -- kernels around the walks for gfx950 (CDNA4, wave64), and
+// the dispatch of the persistent walk kernel's variants.
 //
-//   plain_kernel       one walk per lane, one wave per (query, 64-walk chunk);
-//                      the wave runs until its longest walk ends (forward, or
-//                      forward + backward sums when BWD: the backward pass
-//                      regenerates the same walks from their Philox counters)
-//   persistent_kernel  ragged batch of environments in one launch: resident
-//                      waves pull work units (env, query, walk range) from a
-//                      device counter, and a lane whose walk ends starts the
-//                      unit's next walk at once (lane refill), so a wave is not
-//                      held by its longest walk
 //   finalize_*         per-query means, standard errors and backward products
 //                      from per-wave partial sums, in a fixed order
 //   plan_update        one gradient-ascent step of the planning loop
 //
-// All walk arithmetic lives in wos_device.hpp; the estimator is Sec. IV-A of
+// The walk kernels are in wos_plain.hip and wos_persistent.hip, all walk
+// arithmetic in wos_device.hpp; the estimator is Sec. IV-A of
 // the paper (screened WoS, first-sphere gradient), the step rule Sec. VII.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 
-#include "wos_device.hpp"
 #include "wos_launch.hpp"
+#include "wos_walk.hpp"
 
 namespace wos {
 
 namespace {
-
-constexpr int kBlock = 256;  // 4 waves per block for the plain / finalize kernels
-
-__device__ __forceinline__ void apply_key_add(uint32_t& k0, uint32_t& k1, const uint64_t* key_add)
-{
-    if (key_add) {
-        const uint64_t key = (((uint64_t)k1 << 32) | k0) + *to_const(key_add);
-        k0 = (uint32_t)key;
-        k1 = (uint32_t)(key >> 32);
-    }
-}
-
-// Sum the accumulators of a wave and let lane 0 store them.
-template <int N>
-__device__ __forceinline__ void wave_store(double (&a)[N], double* out)
-{
-#pragma unroll
-    for (int i = 0; i < N; ++i) a[i] = wave_sum(a[i]);
-    if ((threadIdx.x & (kWave - 1)) == 0) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) out[i] = a[i];
-    }
-}
-
-// 2^ex: the factor between a finished walk's stored weighted terms and their
-// values (the FP32 walk keeps the weight's exponent apart; FP64 does not).
-template <typename T>
-__device__ __forceinline__ double walk_scale(const WalkEnd<T>& e)
-{
-    if (sizeof(T) == 8) return 1.0;
-    return ::ldexp(1.0, e.ex);
-}
-
-// One-point gradient of a finished walk: gs v0, plus gs0 (z - x_0) when a
-// point source lies in the first ball (gs0 carries no weight, so no scale).
-template <typename T, int D, int DA, bool SRC>
-__device__ __forceinline__ double walk_grad(const WalkEnd<T>& e, const T (&v0)[DA], cenv<T> p, const T* xq, int i,
-                                            double sc)
-{
-    const double g = (double)(e.gs * v0[i]) * sc;
-    if (SRC) return g + (double)(e.gs0 * (p->src_z[i] - xq[i]));
-    return g;
-}
-
-// d u_hat / d sigma of a finished walk: (W g) S, plus the source part.
-template <typename T, bool SRC>
-__device__ __forceinline__ double walk_dsigma(const WalkEnd<T>& e, double sc)
-{
-    if (SRC) return ((double)e.ubd * (double)e.S + (double)e.srcS) * sc;
-    return (double)e.u * (double)e.S * sc;
-}
-
-// Contribution of one finished walk to an accumulator row laid out for DA
-// coordinates (nacc(DA) entries), of which the first D are in use.
-template <typename T, int D, int DA, bool SRC>
-__device__ __forceinline__ void accumulate(double (&a)[nacc(DA)], const WalkEnd<T>& e, const T (&v0)[DA],
-                                           cenv<T> p, const T* xq)
-{
-    const double sc = walk_scale(e);
-    const double u = (double)e.u * sc;
-    a[0] += u;
-    a[1] += u * u;
-#pragma unroll
-    for (int i = 0; i < D; ++i) {
-        const double g = walk_grad<T, D, DA, SRC>(e, v0, p, xq, i, sc);
-        a[2 + i] += g;
-        a[2 + DA + i] += g * g;
-    }
-    a[2 + 2 * DA] += (double)e.steps;
-    a[3 + 2 * DA] += (e.status == kTruncated) ? 1.0 : 0.0;
-    a[4 + 2 * DA] += (e.status == kDegenerate) ? 1.0 : 0.0;
-    a[5 + 2 * DA] += walk_dsigma<T, SRC>(e, sc);
-    a[6 + 2 * DA] += (double)e.goal_w * sc;
-}
-
-// The wave's work tally goes into lane 0's accumulators before the wave sum.
-template <int N>
-__device__ __forceinline__ void add_work(double (&a)[N], int at, const WorkCount& wc)
-{
-    if ((threadIdx.x & (kWave - 1)) == 0) {
-        a[at] += (double)wc.sph;
-        a[at + 1] += (double)wc.box;
-        a[at + 2] += (double)wc.cbox;
-    }
-}
-
-// ------------------------------------------------------------------------
-// Plain kernel.  FP32: at least 4 waves per SIMD (at most 128 registers per
-// lane) where that needs no scratch memory (d <= 6, and d = 7 without a
-// point source), else at least 3 (168 registers); left free, the allocator
-// may take a few more and fall a wave lower.
-// ------------------------------------------------------------------------
-template <typename T, int D, bool SRC>
-constexpr int plain_waves()
-{
-    return sizeof(T) != 4 ? 1 : (D < 7 || (D == 7 && !SRC)) ? 4 : 3;
-}
-
-template <typename T, int D, bool BWD, bool SRC>
-__global__ void __launch_bounds__(kBlock, (plain_waves<T, D, SRC>()))
-plain_kernel(const EnvP<T>* penv, const T* __restrict__ queries, int64_t n_units, int32_t chunks,
-             int64_t n_walks, int64_t w_base, uint32_t q_base, const uint64_t* __restrict__ key_add,
-             double* __restrict__ partials, double* __restrict__ records)
-{
-    __shared__ uint32_t pair_lds[kBlock / kWave][kPairLds];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t unit = (int64_t)blockIdx.x * (kBlock / kWave) + wv;
-    if (unit >= n_units) return;
-    const int64_t q = unit / chunks;
-    const int64_t wi = (unit - q * chunks) * kWave + lane;
-    const cenv<T> p = (cenv<T>)penv;
-    uint32_t k0 = p->key0, k1 = p->key1;
-    apply_key_add(k0, k1, key_add);
-
-    T xq[D];
-    cptr<T> qrow = to_const(queries) + q * D;
-#pragma unroll
-    for (int i = 0; i < D; ++i) xq[i] = qrow[i];
-
-    const bool active = wi < n_walks;
-    Walker<T, D> s;
-    walker_start<T, D, D>(s, xq, (uint32_t)(w_base + wi));
-    WalkEnd<T> e;
-    e.u = e.gs = e.S = e.goal_w = T(0);
-    e.ex = 0;
-    e.steps = 0;
-    e.status = kTruncated;
-    e.cls = kOuter;
-    WorkCount wc(pair_lds[wv]);
-    // every lane steps until the wave's last walk ends (a finished lane runs
-    // along idle), so the obstacle scans and the work tally stay wave-uniform
-    bool done = !active;
-    while (__builtin_amdgcn_ballot_w64(!done) != 0) {
-        WalkEnd<T> ek;
-        const bool fin = walker_step<T, D, BWD, D, SRC>(p, s, q_base + (uint32_t)q, k0, k1, ek, wc, !done);
-        if (fin && !done) {
-            e = ek;
-            done = true;
-        }
-    }
-
-    double a[nacc(D)];
-#pragma unroll
-    for (int i = 0; i < nacc(D); ++i) a[i] = 0.0;
-    if (active) accumulate<T, D, D, SRC>(a, e, s.v0, p, xq);
-    add_work(a, 7 + 2 * D, wc);
-    wave_store<nacc(D)>(a, partials + unit * nacc(D));
-
-    if (records != nullptr && active) {
-        double* r = records + wi * (D + 7);
-        const double sc = walk_scale(e);
-        r[0] = (double)e.u * sc;
-#pragma unroll
-        for (int i = 0; i < D; ++i) r[1 + i] = walk_grad<T, D, D, SRC>(e, s.v0, p, xq, i, sc);
-        r[D + 1] = (double)e.S;
-        r[D + 2] = (double)e.goal_w * sc;
-        r[D + 3] = (double)e.steps;
-        r[D + 4] = (double)e.status;
-        r[D + 5] = (double)e.cls;
-        r[D + 6] = walk_dsigma<T, SRC>(e, sc);
-    }
-}
 
 __device__ __forceinline__ double se_of(double s, double s2, double n)
 {
@@ -286,180 +116,6 @@ reduce_pairs(const double* __restrict__ prod, int64_t n, double* out0, double* o
     if (threadIdx.x == 0) {
         *out0 = s0[0];
         *out1 = s1[0];
-    }
-}
-
-// ------------------------------------------------------------------------
-// Persistent ragged-batch kernel (FP32).
-// ------------------------------------------------------------------------
-typedef __attribute__((address_space(4))) const BatchEnv CBatch;
-
-constexpr int kNAccBatch = nacc(kMaxDim);
-
-// One walk step of an env of dimension d on the shared 8-wide walker state.
-template <bool BWD, bool SRC>
-__device__ __forceinline__ bool step_any_d(int d, cenv<float> p, Walker<float, kMaxDim>& s, uint32_t q,
-                                           uint32_t k0, uint32_t k1, WalkEnd<float>& e, WorkCount& wc,
-                                           bool live)
-{
-    switch (d) {
-    case 2: return walker_step<float, 2, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live);
-    case 3: return walker_step<float, 3, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live);
-    case 4: return walker_step<float, 4, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live);
-    case 5: return walker_step<float, 5, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live);
-    case 6: return walker_step<float, 6, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live);
-    case 7: return walker_step<float, 7, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live);
-    default: return walker_step<float, 8, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live);
-    }
-}
-
-// Gradient sums and sums of squares of a work unit (2 x kMaxDim doubles per
-// lane) live in LDS: they change only when a walk ends, and keeping them out
-// of registers leaves the walk loop without register spills.  Layout per
-// wave: [entry][lane], so a wave's accesses to one entry are contiguous.
-constexpr int kLdsAcc = 2 * kMaxDim;
-
-// One work unit: walks [w_begin, w_end) of one query, with lane refill.  The
-// walker state is 8 wide for every d, so the dimension only selects the step
-// code.  Accumulators other than the gradient ones stay in registers.
-template <bool BWD, bool SRC>
-__device__ __forceinline__ void run_unit(cenv<float> p, CBatch& be, int64_t local, const float* queries,
-                                         uint32_t k0, uint32_t k1, double* lds, uint32_t* pairs, double* out)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const int d = be.d;
-    const int64_t n_walks = be.n_walks;
-    const int64_t ql = local / be.splits;
-    const int64_t sp = local - ql * be.splits;
-    const int64_t w_begin = sp * (int64_t)be.wps;
-    const int64_t w_end = (w_begin + be.wps < n_walks) ? w_begin + be.wps : n_walks;
-    // walks of the unit counted from w_begin in 32 bits (a unit holds at
-    // most wps < 2^31 walks); walk ids are taken modulo 2^32 as before
-    const int32_t n_unit = (int32_t)(w_end - w_begin);
-    const uint32_t id0 = (uint32_t)w_begin;
-
-    float xq[kMaxDim];
-    cptr<float> qrow = to_const(queries) + (be.q_off + ql) * be.q_stride;
-#pragma unroll
-    for (int i = 0; i < kMaxDim; ++i) xq[i] = (i < d) ? qrow[i < d ? i : 0] : 0.0f;
-
-    // registers: [0] u, [1] u^2, then steps, truncated, degenerate, u S,
-    // goal weight, sphere and box distances and cluster boxes (the nacc
-    // layout without the gradient entries; the last three from the wave's
-    // work tally)
-    constexpr int NR = kNAccBatch - kLdsAcc;
-    double a[NR];
-#pragma unroll
-    for (int i = 0; i < NR; ++i) a[i] = 0.0;
-    double* g = lds + lane;
-#pragma unroll
-    for (int i = 0; i < kLdsAcc; ++i) g[i * kWave] = 0.0;
-
-    // lanes [0, be.lanes) carry walks; the rest (with more than one lane per
-    // walker) only take part in the member scans of the pair rounds
-    const int lanes = be.lanes;
-    Walker<float, kMaxDim> s;
-    bool active = lane < lanes && lane < n_unit;
-    walker_start<float, kMaxDim, kMaxDim>(s, xq, id0 + (uint32_t)lane);
-    int32_t base = lanes;
-    const uint32_t qi = (uint32_t)ql;
-    WorkCount wc(pairs);
-
-    while (__builtin_amdgcn_ballot_w64(active) != 0) {
-        WalkEnd<float> e;
-        // idle lanes (the unit has no walks left for them) step along
-        bool fin = step_any_d<BWD, SRC>(d, p, s, qi, k0, k1, e, wc, active);
-        fin = fin && active;
-        {
-            if (fin) {
-                const double sc = walk_scale(e);
-                const double u = (double)e.u * sc;
-                a[0] += u;
-                a[1] += u * u;
-                a[2] += (double)e.steps;
-                a[3] += (e.status == kTruncated) ? 1.0 : 0.0;
-                a[4] += (e.status == kDegenerate) ? 1.0 : 0.0;
-                a[5] += walk_dsigma<float, SRC>(e, sc);
-                a[6] += (double)e.goal_w * sc;
-                // static indices (unrolled, guarded by d) keep the walker in
-                // registers; a runtime loop bound would index it dynamically
-                // and move it to scratch memory
-#pragma unroll
-                for (int i = 0; i < kMaxDim; ++i) {
-                    if (i < d) {
-                        const double gi = walk_grad<float, kMaxDim, kMaxDim, SRC>(e, s.v0, p, xq, i, sc);
-                        g[i * kWave] += gi;
-                        g[(kMaxDim + i) * kWave] += gi * gi;
-                    }
-                }
-            }
-        }
-        // lane refill: finished lanes take the unit's next walks in lane order
-        const uint64_t m = __builtin_amdgcn_ballot_w64(fin);
-        if (m) {
-            if (fin) {
-                const uint32_t rank =
-                    __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                const int32_t wn = base + (int32_t)rank;
-                if (wn < n_unit) {
-                    walker_start<float, kMaxDim, kMaxDim>(s, xq, id0 + (uint32_t)wn);
-                } else {
-                    active = false;
-                }
-            }
-            base += __popcll(m);
-        }
-    }
-    add_work(a, 7, wc);
-    // back to the nacc(kMaxDim) layout for the partial row
-    double row[kNAccBatch];
-    row[0] = a[0];
-    row[1] = a[1];
-#pragma unroll
-    for (int i = 0; i < kLdsAcc; ++i) row[2 + i] = g[i * kWave];
-#pragma unroll
-    for (int i = 2; i < NR; ++i) row[kLdsAcc + i] = a[i];
-    wave_store<kNAccBatch>(row, out);
-}
-
-// Launch shape: WPB waves per block (1, 2 or 4; the LDS slices scale with
-// it) and at least 4 resident waves per SIMD in every shape (the second
-// launch bound: at most 128 registers per lane).  4 waves per SIMD measured
-// faster than 3 (6 %) or 5 (18 %, spills).
-template <bool BWD, bool SRC, int WPB>
-__global__ void __launch_bounds__(WPB * kWave, 4)
-persistent_kernel(const EnvP<float>* envs, const BatchEnv* benv, int n_benv,
-                  const float* __restrict__ queries, int64_t total_units,
-                  uint32_t key0, uint32_t key1, const uint64_t* __restrict__ key_add,
-                  unsigned* counter, double* __restrict__ partials)
-{
-    __shared__ double lds_acc[WPB][kLdsAcc * kWave];
-    __shared__ uint32_t pair_lds[WPB][kPairLds];
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    double* lds = lds_acc[wv];
-    uint32_t* pairs = pair_lds[wv];
-    uint32_t k0 = key0, k1 = key1;
-    apply_key_add(k0, k1, key_add);
-    CBatch* B = (CBatch*)benv;
-    const unsigned one = ((threadIdx.x & (kWave - 1)) == 0) ? 1u : 0u;
-    // A wave takes at most total_units units, so the loop is bounded even if
-    // the counter were wrong.  Every lane issues the atomic (lane 0 adds 1,
-    // the others 0): no lane-dependent branch around it, so the loop stays
-    // wave-uniform; lane 0's old value is the unit index.
-    for (int64_t taken = 0; taken < total_units; ++taken) {
-        const unsigned u = __builtin_amdgcn_readfirstlane(atomicAdd(counter, one));
-        if ((int64_t)u >= total_units) break;
-        // last env whose first unit is <= u (empty envs share the next offset)
-        int lo = 0, hi = n_benv - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (B[mid].unit_off <= (int64_t)u) lo = mid;
-            else hi = mid - 1;
-        }
-        CBatch& be = B[lo];
-        const cenv<float> p = (cenv<float>)(envs + be.slot);
-        run_unit<BWD, SRC>(p, be, (int64_t)u - be.unit_off, queries, k0, k1, lds, pairs,
-                           partials + (int64_t)u * kNAccBatch);
     }
 }
 
@@ -655,52 +311,6 @@ inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1)
 // ------------------------------------------------------------------------
 // Launchers.
 // ------------------------------------------------------------------------
-template <typename T, int D, bool BWD, bool SRC>
-static void plain_go(unsigned grid, const EnvP<T>* p, const T* queries, int64_t units, int32_t chunks,
-                     int64_t n_walks, int64_t w_base, uint32_t q_base, const uint64_t* key_add, double* partials,
-                     double* records, hipStream_t st)
-{
-    hipLaunchKernelGGL((plain_kernel<T, D, BWD, SRC>), dim3(grid), dim3(kBlock), 0, st, p, queries, units, chunks,
-                       n_walks, w_base, q_base, key_add, partials, records);
-}
-
-template <typename T, int D>
-static hipError_t plain_d(bool bwd, bool src, const EnvP<T>* p, const T* queries, int64_t n_q, int64_t n_walks,
-                          int64_t w_base, uint32_t q_base, const uint64_t* key_add, double* partials,
-                          double* records, hipStream_t st)
-{
-    const int32_t chunks = (int32_t)((n_walks + kWave - 1) / kWave);
-    const int64_t units = n_q * chunks;
-    if (units == 0) return hipSuccess;
-    const unsigned grid = blocks_for(units, kBlock / kWave);
-    if (bwd && src)
-        plain_go<T, D, true, true>(grid, p, queries, units, chunks, n_walks, w_base, q_base, key_add, partials, records, st);
-    else if (bwd)
-        plain_go<T, D, true, false>(grid, p, queries, units, chunks, n_walks, w_base, q_base, key_add, partials, records, st);
-    else if (src)
-        plain_go<T, D, false, true>(grid, p, queries, units, chunks, n_walks, w_base, q_base, key_add, partials, records, st);
-    else
-        plain_go<T, D, false, false>(grid, p, queries, units, chunks, n_walks, w_base, q_base, key_add, partials, records, st);
-    return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_plain(int d, bool bwd, bool src, const EnvP<T>* p, const T* queries, int64_t n_q,
-                        int64_t n_walks, int64_t w_base, uint32_t q_base, const uint64_t* key_add,
-                        double* partials, double* records, hipStream_t st)
-{
-    switch (d) {
-    case 2: return plain_d<T, 2>(bwd, src, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
-    case 3: return plain_d<T, 3>(bwd, src, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
-    case 4: return plain_d<T, 4>(bwd, src, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
-    case 5: return plain_d<T, 5>(bwd, src, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
-    case 6: return plain_d<T, 6>(bwd, src, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
-    case 7: return plain_d<T, 7>(bwd, src, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
-    case 8: return plain_d<T, 8>(bwd, src, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
-    default: return hipErrorInvalidValue;
-    }
-}
-
 template <typename T, int D>
 static hipError_t fin_d(bool bwd, const double* partials, int64_t n_q, int32_t chunks, int64_t n_walks,
                         T* out_u, T* out_grad, double* out_stats, const T* ubar, T* out_dx,
@@ -735,10 +345,6 @@ hipError_t launch_finalize_plain(int d, bool bwd, const double* partials, int64_
     }
 }
 
-template hipError_t launch_plain<float>(int, bool, bool, const EnvP<float>*, const float*, int64_t, int64_t,
-                                        int64_t, uint32_t, const uint64_t*, double*, double*, hipStream_t);
-template hipError_t launch_plain<double>(int, bool, bool, const EnvP<double>*, const double*, int64_t, int64_t,
-                                         int64_t, uint32_t, const uint64_t*, double*, double*, hipStream_t);
 template hipError_t launch_finalize_plain<float>(int, bool, const double*, int64_t, int32_t, int64_t, float*,
                                                  float*, double*, const float*, float*, double*, double*,
                                                  hipStream_t);
@@ -752,63 +358,19 @@ hipError_t launch_reduce_pairs(const double* prod, int64_t n, double* out0, doub
     return hipGetLastError();
 }
 
-template <bool BWD, bool SRC>
-static hipError_t persistent_go(int grid, int block, const EnvP<float>* envs, const BatchEnv* benv, int n_benv,
-                                const float* queries, int64_t total_units, uint32_t key0, uint32_t key1,
-                                const uint64_t* key_add, unsigned* counter, double* partials, hipStream_t st)
-{
-#define WOS_PERSISTENT_CASE(W)                                                                                  \
-    case W * kWave:                                                                                             \
-        hipLaunchKernelGGL((persistent_kernel<BWD, SRC, W>), dim3(grid), dim3(block), 0, st, envs, benv, n_benv, \
-                           queries, total_units, key0, key1, key_add, counter, partials);                       \
-        return hipSuccess;
-    switch (block) {
-        WOS_PERSISTENT_CASE(1)
-        WOS_PERSISTENT_CASE(2)
-        WOS_PERSISTENT_CASE(4)
-    default: return hipErrorInvalidValue;
-    }
-#undef WOS_PERSISTENT_CASE
-}
-
 hipError_t launch_persistent(bool bwd, bool src, int grid, int block, const EnvP<float>* envs,
                              const BatchEnv* benv, int n_benv, const float* queries, int64_t total_units,
                              uint32_t key0, uint32_t key1, const uint64_t* key_add, unsigned* counter,
                              double* partials, hipStream_t st)
 {
     if (total_units == 0) return hipSuccess;
-    hipError_t e;
-    if (bwd && src)
-        e = persistent_go<true, true>(grid, block, envs, benv, n_benv, queries, total_units, key0, key1, key_add, counter, partials, st);
-    else if (bwd)
-        e = persistent_go<true, false>(grid, block, envs, benv, n_benv, queries, total_units, key0, key1, key_add, counter, partials, st);
-    else if (src)
-        e = persistent_go<false, true>(grid, block, envs, benv, n_benv, queries, total_units, key0, key1, key_add, counter, partials, st);
-    else
-        e = persistent_go<false, false>(grid, block, envs, benv, n_benv, queries, total_units, key0, key1, key_add, counter, partials, st);
-    return e != hipSuccess ? e : hipGetLastError();
-}
-
-template <bool BWD, bool SRC>
-static int resident_per_cu(int block)
-{
-    int per_cu = 0;
-    hipError_t e = hipErrorInvalidValue;
-    switch (block) {
-    case 1 * kWave: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persistent_kernel<BWD, SRC, 1>, block, 0); break;
-    case 2 * kWave: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persistent_kernel<BWD, SRC, 2>, block, 0); break;
-    case 4 * kWave: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persistent_kernel<BWD, SRC, 4>, block, 0); break;
-    default: break;
-    }
-    return (e == hipSuccess && per_cu > 0) ? per_cu : 1;
+    return src ? launch_persistent_variant<true>(bwd, grid, block, envs, benv, n_benv, queries, total_units, key0, key1, key_add, counter, partials, st)
+               : launch_persistent_variant<false>(bwd, grid, block, envs, benv, n_benv, queries, total_units, key0, key1, key_add, counter, partials, st);
 }
 
 int persistent_resident_blocks(bool bwd, bool src, int block)
 {
-    const int per_cu = (bwd && src) ? resident_per_cu<true, true>(block)
-                       : bwd        ? resident_per_cu<true, false>(block)
-                       : src        ? resident_per_cu<false, true>(block)
-                                    : resident_per_cu<false, false>(block);
+    const int per_cu = src ? persistent_blocks_per_cu<true>(bwd, block) : persistent_blocks_per_cu<false>(bwd, block);
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess) return per_cu;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 1;

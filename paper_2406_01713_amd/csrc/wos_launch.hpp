@@ -37,6 +37,15 @@ hipError_t launch_persistent(bool bwd, bool src, int grid, int block, const EnvP
                              const uint64_t* key_add, unsigned* counter, double* partials,
                              hipStream_t st);
 
+// The two variants of the above, without and with point-source terms.
+template <bool SRC>
+hipError_t launch_persistent_variant(bool bwd, int grid, int block, const EnvP<float>* envs, const BatchEnv* benv,
+                                     int n_benv, const float* queries, int64_t total_units, uint32_t key0,
+                                     uint32_t key1, const uint64_t* key_add, unsigned* counter, double* partials,
+                                     hipStream_t st);
+template <bool SRC>
+int persistent_blocks_per_cu(bool bwd, int block);
+
 // Resident waves of the persistent kernel for a block size (occupancy x CUs).
 int persistent_resident_blocks(bool bwd, bool src, int block);
 
