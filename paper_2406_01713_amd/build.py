@@ -25,7 +25,7 @@ ARCH = os.environ.get("WOS_OFFLOAD_ARCH", "gfx950")
 # variant, so their long compilations run side by side
 SOURCES = [("wos_persistent.hip", ["-DWOS_PERSISTENT_SRC=0"]), ("wos_persistent.hip", ["-DWOS_PERSISTENT_SRC=1"]),
            ("wos_plain.hip", ["-DWOS_PLAIN_T=float"]), ("wos_plain.hip", ["-DWOS_PLAIN_T=double"]),
-           ("wos_kernels.hip", []), ("wos_api.cpp", []), ("wos_microbench.hip", [])]
+           ("wos_kernels.hip", []), ("wos_grid.hip", []), ("wos_api.cpp", []), ("wos_microbench.hip", [])]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-x", "hip",
          *os.environ.get("WOS_EXTRA_FLAGS", "").split(),
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

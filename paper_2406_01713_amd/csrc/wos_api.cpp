@@ -99,6 +99,12 @@ struct wos_domain {
     size_t off_sph_bnd = 0, off_box_cl = 0, off_box_bnd = 0;
     size_t off_sph_mf = 0, off_box_mf = 0;  // matrix-core features (FP32 buffer only)
     size_t off_sph_cb = 0, off_box_cb = 0;  // cluster bounding boxes (FP32 buffer only)
+    // cell lists (see kGridMin), shared by both precisions; null: none
+    GridBuild grid;
+    GridCell* sph_cells = nullptr;
+    GridCell* box_cells = nullptr;
+    uint32_t* sph_list = nullptr;
+    uint32_t* box_list = nullptr;
 };
 
 namespace {
@@ -120,9 +126,11 @@ int series_coeffs(double b, double y_max, double tol, double* c)
     return -1;
 }
 
+// counted: the caller reports how many obstacle distances the walks evaluate;
+// environments below kClusterMin obstacles then scan all of them.
 template <typename T>
 int make_env(const wos_domain* D, double sigma, double eps, uint64_t seed, uint32_t env_id,
-             const wos_options& o, EnvP<T>& p)
+             const wos_options& o, EnvP<T>& p, bool counted = false)
 {
     std::memset(&p, 0, sizeof(p));
     if (!(sigma >= 0.0) || !std::isfinite(sigma)) return fail(WOS_EINVAL, "sigma must be finite and >= 0 (got %g)", sigma);
@@ -183,6 +191,21 @@ int make_env(const wos_domain* D, double sigma, double eps, uint64_t seed, uint3
     p.box_test = (o.flags & WOS_BOX_TEST) ? 1 : (o.flags & WOS_NO_BOX_TEST) ? 0 : D->geom_d >= kBoxTestMinDim;
     // a pair-queue entry holds the cluster index in 26 bits
     if (p.use_mfma == 2 && (D->n_cl_sph >= (1 << 26) || D->n_cl_box >= (1 << 26))) p.use_mfma = 1;
+    // cell lists: not where a flag asks for a particular scan of every step
+    if (!(o.flags & (WOS_FULL_SCAN | WOS_SCALAR_CULL | WOS_WAVE_SCAN)) && D->grid.cells) {
+        if (!counted || D->n_sph >= kClusterMin) p.sph_cells = D->sph_cells;
+        if (!counted || D->n_box >= kClusterMin) p.box_cells = D->box_cells;
+        p.sph_list = D->sph_list;
+        p.box_list = D->box_list;
+        p.grid_last = D->grid.cells - 1;
+        p.grid_inv = (T)(1.0 / (double)D->grid.h);
+        for (int i = 0; i < kMaxDim; ++i) {
+            p.grid_n[i] = D->grid.n[i];
+            p.grid_off[i] = i < D->geom_d ? (T)(-(double)D->grid.lo[i] / (double)D->grid.h) : T(0);
+            p.grid_max[i] = (T)(D->grid.n[i] - 1);
+        }
+        for (int l = 0; l < 3; ++l) p.grid_lev[l] = (T)D->grid.lev[l];
+    }
     p.d = D->d;
     p.geom_d = D->geom_d;
     p.pad_g = 0;
@@ -524,6 +547,53 @@ void build_mfma_features(int d, int64_t n_cl, const float* bnd, float* out)
             for (int s = 0; s < 3; ++s) o[s] = (float)f[4 * s + k];
             o[3] = 0.0f;
         }
+}
+
+// Cell table of a domain: cubic cells over the outer boundary's box, about
+// kGridCellsPer per obstacle and at most about kGridCellsMax.
+void plan_grid(const wos_domain* D, GridBuild& g)
+{
+    const int k = D->geom_d;
+    const double target = std::min<double>(kGridCellsMax, (double)kGridCellsPer * (double)(D->n_sph + D->n_box));
+    double lo[kMaxDim], ext[kMaxDim], vol = 1.0, diag = 0.0;
+    for (int i = 0; i < k; ++i) {
+        lo[i] = D->outer_kind == WOS_OUTER_BOX ? D->lo[i] : D->oc[i] - D->orad;
+        const double hi = D->outer_kind == WOS_OUTER_BOX ? D->hi[i] : D->oc[i] + D->orad;
+        ext[i] = hi - lo[i];
+        vol *= ext[i];
+        diag += ext[i] * ext[i];
+    }
+    const double h0 = std::pow(vol / target, 1.0 / k);
+    double h = 0.0, cells = 1.0;
+    for (int i = 0; i < kMaxDim; ++i) g.n[i] = 1;
+    for (int i = 0; i < k; ++i) {
+        g.n[i] = (uint32_t)std::min<double>(kGridMaxAxis, std::max(1.0, std::ceil(ext[i] / h0 - 0.25)));
+        h = std::max(h, ext[i] / g.n[i]);
+        cells *= g.n[i];
+    }
+    // anisotropic boxes: fewer cells where the common edge needs fewer
+    for (int i = 0; i < k; ++i) g.n[i] = (uint32_t)std::min<double>(g.n[i], std::max(1.0, std::ceil(ext[i] / h)));
+    cells = 1.0;
+    for (int i = 0; i < k; ++i) cells *= g.n[i];
+    // the index is formed in 24-bit products, and FP32 has to hold it all
+    if (!(cells <= 4.0 * kGridCellsMax) || !(h > 0.0) || !(h < 1e18) || !(h > 1e-18)) return;
+    g.k = k;
+    g.cells = (uint32_t)cells;
+    g.h = (float)(h * (1.0 + 0x1p-20));
+    for (int i = 0; i < kMaxDim; ++i) g.lo[i] = g.pad[i] = g.olo[i] = g.ohi[i] = g.oc[i] = 0.0f;
+    for (int i = 0; i < k; ++i) {
+        g.lo[i] = (float)lo[i];
+        // 2^-10 of an edge covers the cell coordinate's rounding (at most 512
+        // cells per axis); 16 units of rounding of the coordinates the rest
+        g.pad[i] = (float)(0x1p-10 * h + 0x1p-20 * (std::fabs(lo[i]) + ext[i]));
+        g.olo[i] = (float)D->lo[i];
+        g.ohi[i] = (float)D->hi[i];
+        g.oc[i] = (float)D->oc[i];
+    }
+    g.orad = (float)D->orad;
+    g.outer_kind = D->outer_kind;
+    g.margin = (float)(0x1p-16 * (D->coord_scale + std::sqrt(diag)));
+    for (int l = 0; l < 3; ++l) g.lev[l] = (float)(kGridLev[l] * h);
 }
 
 int check_device(const wos_domain* D)
@@ -959,7 +1029,7 @@ int run_batch(const wos_domain* const* envs, int n_envs, const float* queries, c
     BatchEnv* hb = reinterpret_cast<BatchEnv*>(host_tab + env_bytes);
     bool src = false;
     for (int e = 0; e < n_envs; ++e) {
-        if ((rc = make_env<float>(envs[e], sigma[e], eps[e], seed, (uint32_t)e, o, hp[e]))) return rc;
+        if ((rc = make_env<float>(envs[e], sigma[e], eps[e], seed, (uint32_t)e, o, hp[e], out_stats != nullptr))) return rc;
         src = src || envs[e]->has_src;
         if (bwd && envs[e]->has_src && !(sigma[e] > 0.0))
             return fail(WOS_ENOTSUP, "env %d: the sigma derivative of a point source is provided for sigma > 0 only", e);
@@ -1353,6 +1423,14 @@ int wos_create_domain(int d, const wos_spheres* spheres, const wos_boxes* boxes,
         if (e == hipSuccess) e = hipMemcpy(D->cl_f, cf.data(), cf_elems * sizeof(float), hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(D->cl_d, cd.data(), cl_elems * sizeof(double), hipMemcpyHostToDevice);
     }
+    // cell lists
+    if (ns >= kGridMin || nb >= kGridMin) plan_grid(D, D->grid);
+    if (D->grid.cells) {
+        if (e == hipSuccess && ns >= kGridMin)
+            e = build_grid(D->grid, d, false, D->sph_f, ns, &D->sph_cells, &D->sph_list);
+        if (e == hipSuccess && nb >= kGridMin)
+            e = build_grid(D->grid, d, true, D->box_f, nb, &D->box_cells, &D->box_list);
+    }
     if (e != hipSuccess) {
         wos_destroy_domain(D);
         return fail(e == hipErrorOutOfMemory ? WOS_ENOMEM : WOS_EHIP, "domain upload: %s", hipGetErrorString(e));
@@ -1372,6 +1450,10 @@ void wos_destroy_domain(wos_domain* D)
     (void)hipFree(D->cl_d);
     (void)hipFree(D->arm_f);
     (void)hipFree(D->arm_d);
+    (void)hipFree(D->sph_cells);
+    (void)hipFree(D->box_cells);
+    (void)hipFree(D->sph_list);
+    (void)hipFree(D->box_list);
     delete D;
 }
 

@@ -62,6 +62,8 @@ struct Math<float> {
     static __device__ __forceinline__ float min(float a, float b) { return __builtin_fminf(a, b); }
     static __device__ __forceinline__ float max(float a, float b) { return __builtin_fmaxf(a, b); }
     static __device__ __forceinline__ float abs(float a) { return __builtin_fabsf(a); }
+    // x clamped to [0, hi]; NaN gives an end
+    static __device__ __forceinline__ float clamp0(float x, float hi) { return __builtin_amdgcn_fmed3f(x, 0.0f, hi); }
     static __device__ __forceinline__ float exp(float x) { return __expf(x); }
     static __device__ __forceinline__ float log(float x) { return __logf(x); }
     static __device__ __forceinline__ float pow(float x, float y) { return __expf(y * __logf(x)); }
@@ -104,6 +106,7 @@ struct Math<double> {
     static __device__ __forceinline__ double min(double a, double b) { return __builtin_fmin(a, b); }
     static __device__ __forceinline__ double max(double a, double b) { return __builtin_fmax(a, b); }
     static __device__ __forceinline__ double abs(double a) { return __builtin_fabs(a); }
+    static __device__ __forceinline__ double clamp0(double x, double hi) { return max(min(x, hi), 0.0); }
     static __device__ __forceinline__ double exp(double x) { return ::exp(x); }
     static __device__ __forceinline__ double log(double x) { return ::log(x); }
     static __device__ __forceinline__ double pow(double x, double y) { return ::pow(x, y); }
@@ -618,6 +621,117 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
     return (uint32_t)x;
 }
 
+// Orders a wave's LDS accesses of one lane against the others' in the
+// compiler's eyes (a wave's LDS instructions execute in order, so no
+// instruction is needed): without it a lane's load after its own store may be
+// replaced by the stored value although another lane has written there since.
+__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local"); }
+
+// Inclusive prefix maximum over the 64 lanes (0 where a lane has no source).
+__device__ __forceinline__ uint32_t wave_incl_max(uint32_t v)
+{
+    int x = (int)v;
+    auto up = [&](int y) { x = y > x ? y : x; };
+    up(__builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));  // row_shr:1
+    up(__builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));  // row_shr:2
+    up(__builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));  // row_shr:4
+    up(__builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));  // row_shr:8
+    up(__builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));  // row_bcast:15
+    up(__builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));  // row_bcast:31
+    return (uint32_t)x;
+}
+
+// ------------------------------------------------------------------------
+// Cell lists (see kGridMin): the cell of x, and the minimum over a list.
+// ------------------------------------------------------------------------
+// Cell index of x.  The coordinate is clamped per axis (NaN gives an end of
+// the range), so the index is always inside the table; the lists allow for
+// the rounding of the coordinate.
+template <typename T, int D>
+__device__ __forceinline__ uint32_t grid_cell(cenv<T> p, const T (&x)[D])
+{
+    uint32_t idx = 0;
+    const T inv = p->grid_inv;
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+        const T t = Math<T>::clamp0(Math<T>::fma(x[i], inv, p->grid_off[i]), p->grid_max[i]);
+        idx = __umul24(idx, p->grid_n[i]) + (uint32_t)t;
+    }
+    return idx < p->grid_last ? idx : p->grid_last;
+}
+
+// Entries of a cell to read for threshold t (kGridFull: scan the clusters).
+template <typename T>
+__device__ __forceinline__ uint32_t grid_count(cenv<T> p, uint32_t counts, T t)
+{
+    const uint32_t sh = t <= p->grid_lev[0] ? 0u : t <= p->grid_lev[1] ? 8u : t <= p->grid_lev[2] ? 16u : 24u;
+    return (counts >> sh) & 0xFFu;
+}
+
+// Lists of at most kCellDirect entries are walked by their own lanes; longer
+// ones are spread over the wave.
+constexpr uint32_t kCellDirect = 2;
+
+// Minimum over list entries [off, off + n) of every lane's own list (n = 0:
+// none).  All lanes of the wave take part.  evals counts the distances.
+//
+// Short lists: lane by lane, one entry per iteration.  Otherwise (FP32) the
+// wave takes the concatenation of all lists 64 entries at a time, one per
+// lane: each list's lane marks the list's first slot in LDS, a prefix
+// maximum carries the owner to the following slots, and the position, list
+// offset and minimum are the owner's, by lane shuffles and an LDS atomic min.
+template <typename T, int D, bool BOX>
+__device__ __forceinline__ T cell_min(cptr<uint32_t> list, cptr<T> rows, uint32_t off, uint32_t n, const T (&x)[D],
+                                      uint64_t& evals, uint32_t* lds)
+{
+    constexpr int S = BOX ? box_stride(D) : sph_stride(D);
+    T best = Math<T>::inf();
+    uint64_t m = __builtin_amdgcn_ballot_w64(n > 0);
+    if (m == 0) return best;
+    if (sizeof(T) != 4 || __builtin_amdgcn_ballot_w64(n > kCellDirect) == 0) {
+        for (uint32_t i = 0; m != 0; m = __builtin_amdgcn_ballot_w64(n > ++i)) {
+            evals += (uint64_t)__popcll(m);
+            if (i < n) {
+                cptr<T> r = rows + (int64_t)list[off + i] * S;
+                best = Math<T>::min(best, BOX ? box_dist<T, D>(x, r) : sphere_dist<T, D>(x, r));
+            }
+        }
+        return best;
+    }
+    if constexpr (sizeof(T) == 4) {
+        const int lane = threadIdx.x & (kWave - 1);
+        uint32_t* slot = lds;
+        uint32_t* mins = lds + kWave;
+        mins[lane] = ord_of(best);
+        const uint32_t incl = wave_incl_scan(n);
+        const int total = __builtin_amdgcn_readlane((int)incl, kWave - 1);
+        const int pre = (int)(incl - n);
+        const uint32_t base = off - (uint32_t)pre;
+        evals += (uint64_t)total;
+        for (int b = 0; b < total; b += kWave) {  // wave-uniform
+            slot[lane] = 0u;
+            wave_lds_fence();
+            const int s = pre - b;  // this lane's list starts at slot s of the round
+            if (n > 0 && s < kWave && s + (int)n > 0) slot[s > 0 ? s : 0] = (uint32_t)lane + 1u;
+            wave_lds_fence();
+            const uint32_t own = wave_incl_max(slot[lane]);  // >= 1: some list covers slot 0
+            const int w = (int)(own > 0 ? own - 1u : 0u);
+            const bool act = b + lane < total;
+            const uint32_t e = (uint32_t)__shfl((int)base, w, kWave) + (uint32_t)(b + lane);
+            T xw[D];
+#pragma unroll
+            for (int i = 0; i < D; ++i) xw[i] = __shfl(x[i], w, kWave);
+            if (act) {
+                cptr<T> r = rows + (int64_t)list[e] * S;
+                atomicMin(&mins[w], ord_of(BOX ? box_dist<T, D>(xw, r) : sphere_dist<T, D>(xw, r)));
+            }
+        }
+        wave_lds_fence();
+        best = float_of_ord(mins[lane]);
+    }
+    return best;
+}
+
 // Min over the members of the clusters each lane may need (thr as for
 // cluster_min), with the cluster test on the matrix cores, a bounding-box
 // test of the pairs it keeps (BOXT), and the members of the pairs that pass
@@ -744,20 +858,75 @@ __device__ __forceinline__ float cluster_min_pairs(cptr<float> rows, const float
     }
     evals += ((uint64_t)pairs + (uint64_t)mqn) * kCluster;
     boxes += tested;
+    wave_lds_fence();
     return float_of_ord(best[lane]);
 }
 
-// R = distance to the boundary; cls = first component attaining it in the
-// order goal, spheres, boxes, outer.  The goal and outer distances come first
-// and bound the box scan, whose result then bounds the sphere scan; ub, any
-// value at or above the R a scan of every obstacle computes (the walker's
-// bound from its previous step, +inf when it has none), bounds both scans as
-// well.  Culled clusters leave R and cls as a scan of every obstacle gives
-// them.
-template <typename T, int D>
-__device__ __forceinline__ T distance(cenv<T> p, const T (&x)[D], int& cls, WorkCount& wc, bool live,
-                                      T ub = Math<T>::inf())
+// Minimum over one kind's obstacles by the cluster scan (or, below
+// kClusterMin of them and under WOS_FULL_SCAN, over all of them) for the
+// lanes of live.  n: distances per live lane (wave-uniform scans); evals,
+// cbt: distances and cluster boxes of the wave (pair scan).
+template <typename T, int D, bool BOX>
+__device__ __forceinline__ T scan_min(cenv<T> p, const T (&xg)[D], T thr, bool live, uint32_t& n, uint64_t& evals,
+                                      uint64_t& cbt, uint32_t* pairs)
 {
+    p = fresh(p);
+    const int n_cl = BOX ? p->n_cl_box : p->n_cl_sph;
+    if (!n_cl) {
+        if (BOX) {
+            n = (uint32_t)p->n_box;
+            return boxes_min<T, D>(to_const(p->box), fresh(p)->n_box, xg);
+        }
+        n = (uint32_t)p->n_sph;
+        return spheres_min<T, D>(to_const(p->sph), fresh(p)->n_sph, xg);
+    }
+    n = 0;
+    cptr<T> rows = to_const(BOX ? p->box_cl : p->sph_cl);
+    if constexpr (sizeof(T) == 4) {
+        const float* mf = BOX ? p->box_mf : p->sph_mf;
+        if (p->use_mfma == 2) {
+            const float* cb = BOX ? p->box_cb : p->sph_cb;
+            return p->box_test ? cluster_min_pairs<D, BOX, true>(rows, mf, cb, n_cl, xg, thr, live, evals, cbt, pairs)
+                               : cluster_min_pairs<D, BOX, false>(rows, mf, cb, n_cl, xg, thr, live, evals, cbt, pairs);
+        }
+        if (p->use_mfma) return cluster_min_mfma<D, BOX>(rows, mf, n_cl, xg, thr, live, n);
+    }
+    return cluster_min<T, D, BOX>(rows, to_const(BOX ? p->box_bnd : p->sph_bnd), n_cl, xg, thr, live, n);
+}
+
+// R = distance to the boundary; cls = first component attaining it in the
+// order goal, spheres, boxes, outer, for the lanes of live.  The goal and outer
+// distances come first and bound the box scan, whose result then bounds the
+// sphere scan; ub, any value at or above the R a scan of every obstacle
+// computes (the walker's bound from its previous step, +inf when it has
+// none), bounds both scans as well.  Obstacles that a cell list or the
+// culling leaves out never attain R, so R and cls are as a scan of every
+// obstacle gives them.
+//
+// lists (wave-uniform): read the cell lists where the environment has them
+// (lanes of look; their points must lie inside the outer boundary up to
+// rounding); lanes whose list is too long, and every live lane without
+// lists, take the scan.  between() runs after the headers' loads are issued
+// and before they are used: work that does not depend on the distance hides
+// their latency there.
+template <typename T, int D, typename F>
+__device__ __forceinline__ T distance(cenv<T> p, const T (&x)[D], int& cls, WorkCount& wc, bool live, bool lists,
+                                      bool look, T ub, F&& between)
+{
+    // extruded geometry: obstacles and the outer boundary see the leading
+    // geom_d coordinates only (their stored centres are zero beyond them)
+    T xg[D];
+#pragma unroll
+    for (int i = 0; i < D; ++i) xg[i] = (i < p->geom_d) ? x[i] : T(0);
+    const bool gs = lists && p->sph_cells != nullptr, gb = lists && p->box_cells != nullptr;  // wave-uniform
+    GridCell hs = {0, 0}, hb = {0, 0};
+    if (gs || gb) {
+        const uint32_t cell = grid_cell<T, D>(fresh(p), xg);
+        if (gs) hs = fresh(p)->sph_cells[cell];
+        if (gb) hb = fresh(p)->box_cells[cell];
+    }
+    between();
+    p = fresh(p);
     T dg = Math<T>::inf();
     if (p->has_goal) {
         T t = x[0] - p->goal_c[0];
@@ -769,81 +938,43 @@ __device__ __forceinline__ T distance(cenv<T> p, const T (&x)[D], int& cls, Work
         }
         dg = Math<T>::sqrt(acc) - p->goal_r;
     }
-    // extruded geometry: obstacles and the outer boundary see the leading
-    // geom_d coordinates only (their stored centres are zero beyond them)
-    T xg[D];
-#pragma unroll
-    for (int i = 0; i < D; ++i) xg[i] = (i < p->geom_d) ? x[i] : T(0);
     const T dout = outer_dist<T, D>(fresh(p), xg);
     p = fresh(p);
     // the arm bound (joint coordinates, never extruded) tightens the scans
     const T da = p->n_arm ? arm_dist<T, D>(p, x) : Math<T>::inf();
     const T dga = Math<T>::min(dg, Math<T>::min(da, dout));
     const T tg = Math<T>::min(dga, ub);  // the scans' threshold before the box result
-    p = fresh(p);
-    T db = Math<T>::inf();
-    uint32_t nb, ns;         // member distances per lane (wave-uniform scans)
-    uint64_t eb = 0, es = 0;  // member distances of the wave (pair-compacted scans)
+    uint32_t nb = 0, ns = 0;  // member distances per lane (wave-uniform scans)
+    uint64_t eb = 0, es = 0;  // distances of the wave (cell lists and pair-compacted scans)
     uint64_t cbt = 0;         // cluster bounding boxes tested by the wave
-    if (p->n_cl_box) {
-        nb = 0;
-        bool done = false;
-        if constexpr (sizeof(T) == 4) {
-            if (p->use_mfma == 2) {
-                if (p->box_test)
-                    db = cluster_min_pairs<D, true, true>(to_const(fresh(p)->box_cl), fresh(p)->box_mf,
-                                                          fresh(p)->box_cb, fresh(p)->n_cl_box, xg, tg, live, eb,
-                                                          cbt, wc.pairs);
-                else
-                    db = cluster_min_pairs<D, true, false>(to_const(fresh(p)->box_cl), fresh(p)->box_mf,
-                                                           fresh(p)->box_cb, fresh(p)->n_cl_box, xg, tg, live, eb,
-                                                           cbt, wc.pairs);
-                done = true;
-            } else if (p->use_mfma) {
-                db = cluster_min_mfma<D, true>(to_const(p->box_cl), fresh(p)->box_mf, fresh(p)->n_cl_box, xg,
-                                               tg, live, nb);
-                done = true;
-            }
-        }
-        if (!done)
-            db = cluster_min<T, D, true>(to_const(fresh(p)->box_cl), to_const(fresh(p)->box_bnd), fresh(p)->n_cl_box, xg,
-                                         tg, live, nb);
-    } else {
-        db = boxes_min<T, D>(to_const(p->box), fresh(p)->n_box, xg);
-        nb = (uint32_t)fresh(p)->n_box;
+    T db = Math<T>::inf(), ds = Math<T>::inf();
+    bool scan = live;
+    if (gb) {
+        uint32_t n = look ? grid_count<T>(fresh(p), hb.counts, tg) : 0u;
+        scan = n == kGridFull;
+        n = scan ? 0u : n;
+        db = cell_min<T, D, true>(to_const(fresh(p)->box_list), to_const(fresh(p)->box), hb.off, n, xg, eb, wc.pairs);
     }
-    p = fresh(p);
-    T ds = Math<T>::inf();
-    if (p->n_cl_sph) {
-        ns = 0;
-        bool done = false;
-        if constexpr (sizeof(T) == 4) {
-            if (p->use_mfma == 2) {
-                if (p->box_test)
-                    ds = cluster_min_pairs<D, false, true>(to_const(fresh(p)->sph_cl), fresh(p)->sph_mf,
-                                                           fresh(p)->sph_cb, fresh(p)->n_cl_sph, xg,
-                                                           Math<T>::min(tg, db), live, es, cbt, wc.pairs);
-                else
-                    ds = cluster_min_pairs<D, false, false>(to_const(fresh(p)->sph_cl), fresh(p)->sph_mf,
-                                                            fresh(p)->sph_cb, fresh(p)->n_cl_sph, xg,
-                                                            Math<T>::min(tg, db), live, es, cbt, wc.pairs);
-                done = true;
-            } else if (p->use_mfma) {
-                ds = cluster_min_mfma<D, false>(to_const(p->sph_cl), fresh(p)->sph_mf, fresh(p)->n_cl_sph, xg,
-                                                Math<T>::min(tg, db), live, ns);
-                done = true;
-            }
-        }
-        if (!done)
-            ds = cluster_min<T, D, false>(to_const(fresh(p)->sph_cl), to_const(fresh(p)->sph_bnd), fresh(p)->n_cl_sph,
-                                          xg, Math<T>::min(tg, db), live, ns);
-    } else {
-        ds = spheres_min<T, D>(to_const(p->sph), fresh(p)->n_sph, xg);
-        ns = (uint32_t)fresh(p)->n_sph;
+    if (!gb || __builtin_amdgcn_ballot_w64(scan) != 0) {
+        const T b = scan_min<T, D, true>(p, xg, tg, scan, nb, eb, cbt, wc.pairs);
+        db = Math<T>::min(db, (scan || !gb) ? b : Math<T>::inf());
+        wc.box += (uint64_t)__popcll(__ballot(scan)) * nb;
     }
-    const uint64_t lanes = (uint64_t)__popcll(__ballot(live));
-    wc.sph += lanes * ns + es;
-    wc.box += lanes * nb + eb;
+    scan = live;
+    const T ts = Math<T>::min(tg, db);
+    if (gs) {
+        uint32_t n = look ? grid_count<T>(fresh(p), hs.counts, ts) : 0u;
+        scan = n == kGridFull;
+        n = scan ? 0u : n;
+        ds = cell_min<T, D, false>(to_const(fresh(p)->sph_list), to_const(fresh(p)->sph), hs.off, n, xg, es, wc.pairs);
+    }
+    if (!gs || __builtin_amdgcn_ballot_w64(scan) != 0) {
+        const T s = scan_min<T, D, false>(p, xg, ts, scan, ns, es, cbt, wc.pairs);
+        ds = Math<T>::min(ds, (scan || !gs) ? s : Math<T>::inf());
+        wc.sph += (uint64_t)__popcll(__ballot(scan)) * ns;
+    }
+    wc.sph += es;
+    wc.box += eb;
     wc.cbox += cbt;
     const T ao = Math<T>::min(da, dout);
     const T bo = Math<T>::min(db, ao);
@@ -1103,7 +1234,6 @@ struct Walker {
     T v0[D];   // first direction
     T W;       // prod_{i < k} C(R_i): weight of u_hat(x_0)
     T W1;      // prod_{1 <= i < k} C(R_i): weight of u_hat(x_1)
-    T gfac;    // (d / R_0) C1(R_0)
     T S;       // sum_{i < k} d ln C(R_i) / d sigma
     T src;     // point source: sum_{i < k} W_i amp G_B(x_i): source part of u_hat(x_0)
     T src1;    // the same with weights W1_i, i >= 1: of u_hat(x_1)
@@ -1114,6 +1244,32 @@ struct Walker {
     int32_t ex;  // W, W1, src, src1 and srcS hold their values times 2^-ex (FP32 only)
     T rb;        // bound on this step's R from the previous one (+inf on a walk's first step)
 };
+
+// What every walk of a work unit shares, because all start at the unit's query
+// point: R and its component there, and the gradient factor (d / R_0) C1(R_0).
+// The unit's first step (first set, every lane at the query point) takes the
+// distance by the cluster scan, which also serves points outside the cell
+// table, and fills the rest in.
+template <typename T>
+struct UnitStart {
+    T R = T(0);
+    T gfac = T(0);
+    int cls = kOuter;
+    bool first = true;
+};
+
+// Lane 0's value in a scalar register.
+__device__ __forceinline__ float uniform_of(float v)
+{
+    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v)));
+}
+__device__ __forceinline__ double uniform_of(double v)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
 
 template <typename T>
 struct WalkEnd {
@@ -1138,7 +1294,6 @@ __device__ __forceinline__ void walker_start(Walker<T, DA>& s, const T (&xq)[DA]
     for (int i = 0; i < DA; ++i) s.v0[i] = T(0);
     s.W = T(1);
     s.W1 = T(1);
-    s.gfac = T(0);
     s.S = T(0);
     s.src = T(0);
     s.src1 = T(0);
@@ -1184,26 +1339,40 @@ template <bool SRC, bool BWD, int DA>
 __device__ __forceinline__ void renormalize(Walker<double, DA>&) {}
 
 // Returns true when the walk ended (e is then filled in).  (key0, key1) is
-// the Philox key of the launch, q the query's index in its environment.  The
-// walker may store DA >= D coordinates; only the first D are used.
+// the Philox key of the launch, q the query's index in its environment, st
+// the unit's start (lane 0 must be live on the unit's first step).  The walker
+// may store DA >= D coordinates; only the first D are used.
 template <typename T, int D, bool BWD, int DA = D, bool SRC = false>
 __device__ __forceinline__ bool walker_step(cenv<T> p0, Walker<T, DA>& s, uint32_t q, uint32_t key0,
-                                            uint32_t key1, WalkEnd<T>& e, WorkCount& wc, bool live)
+                                            uint32_t key1, WalkEnd<T>& e, WorkCount& wc, bool live, UnitStart<T>& st)
 {
     static_assert(DA >= D, "walker storage narrower than the dimension");
     const T(&x)[D] = reinterpret_cast<const T(&)[D]>(s.x);
     int cls;
     // the step-to-step bound, in the dimensions where it culls (kStepBoundMaxDim)
     constexpr bool kBound = D <= kStepBoundMaxDim;
-    const T R = distance<T, D>(fresh(p0), x, cls, wc, live, kBound ? s.rb : Math<T>::inf());
+    const uint32_t k = s.k;
+    // the step's direction does not depend on its distance
+    T v[D];
+    T R = distance<T, D>(fresh(p0), x, cls, wc, live, !st.first, live && k > 0, kBound ? s.rb : Math<T>::inf(),
+                         [&] { direction<T, D>(k, s.w, q, fresh(p0)->env_id, key0, key1, v); });
     cenv<T> p = fresh(p0);
+    if (st.first) {  // wave-uniform
+        st.R = uniform_of(R);
+        st.cls = __builtin_amdgcn_readfirstlane(cls);
+        st.gfac = T(D) * Math<T>::rcp(st.R * horner<T>(p->cC1, p->nt_C1, p->qsigma * (st.R * st.R)));
+        st.first = false;
+    } else {
+        R = k > 0 ? R : st.R;
+        cls = k > 0 ? cls : st.cls;
+    }
+    p = fresh(p0);
     // R(x) is a minimum of distances, each 1-Lipschitz, and the walker moves
     // R: the next R is at most 2 R, and with the margins (rb_abs covers the
     // rounding of the positions and of every component's computed distance,
     // +inf where coordinates are unbounded) at most this computed bound, so
     // it is a threshold the scans may cull against without changing R or cls
     if (kBound) s.rb = Math<T>::fma(R, T(2.001953125), p->rb_abs);  // 2 (1 + 2^-10)
-    const uint32_t k = s.k;
     if (R < p->eps) {
         const T g = boundary_value<T, D>(p, x, cls);
         const bool first = (k == 0);
@@ -1212,13 +1381,13 @@ __device__ __forceinline__ bool walker_step(cenv<T> p0, Walker<T, DA>& s, uint32
         e.status = first ? kDegenerate : kAbsorbed;
         e.ex = s.ex;
         e.u = s.W * g;
-        e.gs = first ? T(0) : s.gfac * s.W1 * g;
+        e.gs = first ? T(0) : st.gfac * s.W1 * g;
         e.S = s.S;
         e.goal_w = (cls == kGoal) ? s.W : T(0);
         if (SRC) {
             e.ubd = e.u;
             e.u += s.src;
-            e.gs = first ? T(0) : s.gfac * (s.W1 * g + s.src1);
+            e.gs = first ? T(0) : st.gfac * (s.W1 * g + s.src1);
             e.gs0 = s.gs0;
             e.srcS = s.srcS;
         }
@@ -1245,13 +1414,13 @@ __device__ __forceinline__ bool walker_step(cenv<T> p0, Walker<T, DA>& s, uint32
         }
         if (dz2 < R * R) {
             const T r = Math<T>::sqrt(dz2);
-            const SourceTerm<T> st = ball_green<T, D, BWD>(p, r, R);
+            const SourceTerm<T> sg = ball_green<T, D, BWD>(p, r, R);
             p = fresh(p0);
-            const T Ga = p->src_amp * st.G;
-            if (BWD) s.srcS = Math<T>::fma(s.W, Math<T>::fma(s.S, Ga, p->src_amp * st.dG), s.srcS);
+            const T Ga = p->src_amp * sg.G;
+            if (BWD) s.srcS = Math<T>::fma(s.W, Math<T>::fma(s.S, Ga, p->src_amp * sg.dG), s.srcS);
             s.src = Math<T>::fma(s.W, Ga, s.src);
             if (k > 0) s.src1 = Math<T>::fma(s.W1, Ga, s.src1);
-            else if (r > T(0)) s.gs0 = p->c_imp * p->src_amp * st.gm / r;
+            else if (r > T(0)) s.gs0 = p->c_imp * p->src_amp * sg.gm / r;
         }
         p = fresh(p0);
     }
@@ -1265,12 +1434,7 @@ __device__ __forceinline__ bool walker_step(cenv<T> p0, Walker<T, DA>& s, uint32
     if (BWD) {
         const T p1 = horner<T>(p->cC1, p->nt_C1, y);
         s.S = Math<T>::fma(T(-0.5 / D) * R2 * p1, C, s.S);
-        if (k == 0) s.gfac = T(D) * Math<T>::rcp(R * p1);
-    } else if (k == 0) {
-        s.gfac = T(D) * Math<T>::rcp(R * horner<T>(p->cC1, p->nt_C1, y));
     }
-    T v[D];
-    direction<T, D>(k, s.w, q, fresh(p0)->env_id, key0, key1, v);
     if (k == 0) {
 #pragma unroll
         for (int i = 0; i < D; ++i) s.v0[i] = v[i];

@@ -237,7 +237,7 @@ plan_update(const EnvP<float>* penv, float* __restrict__ x, int64_t n, const flo
     for (int i = 0; i < D; ++i) xs[i] = (n > 0) ? x[si * D + i] : 0.0f;
     int cls;
     WorkCount wc(pair_lds[__builtin_amdgcn_readfirstlane(threadIdx.x / kWave)]);
-    const float R = distance<float, D>(p, xs, cls, wc, valid);
+    const float R = distance<float, D>(p, xs, cls, wc, valid, false, false, Math<float>::inf(), [] {});
     if (valid) {
         float dz2 = 0.0f;
         if (p->has_src) {

@@ -70,6 +70,26 @@ template <typename T>
 hipError_t launch_varadhan(const T* u, const T* grad, int64_t n, int d, int stride, double sigma, T* w,
                            T* grad_w, hipStream_t st);
 
+// Cell lists of one obstacle kind (see kGridMin): the geometry of the table
+// and what bounds the walker's threshold in it.
+struct GridBuild {
+    int k = 0;                           // coordinates the obstacles depend on
+    uint32_t n[kMaxDim], cells = 0;      // cells per axis (1 past k), their product
+    float lo[kMaxDim], h = 0;            // first corner, edge
+    float pad[kMaxDim];                  // enlargement of a cell (rounding of its coordinate)
+    float margin = 0;                    // enlargement of every distance comparison
+    float lev[3];                        // threshold ranges
+    int outer_kind = 0;
+    float olo[kMaxDim], ohi[kMaxDim], oc[kMaxDim], orad = 0;
+};
+
+// Builds the lists of m obstacles (device FP32 rows of dimension d) into
+// arrays it allocates; *cells stays null, with hipSuccess, where the lists
+// would take more than kGridEntriesMax entries.  Synchronises the device.
+constexpr uint32_t kGridEntriesMax = 1u << 25;
+hipError_t build_grid(const GridBuild& g, int d, bool box, const float* rows, int64_t m, GridCell** cells,
+                      uint32_t** list);
+
 // Fill kernels (used instead of hipMemsetAsync so the calls are capturable).
 hipError_t launch_fill_u32(unsigned* p, int64_t n, unsigned v, hipStream_t st);
 hipError_t launch_fill_f64(double* p, int64_t n, double v, hipStream_t st);

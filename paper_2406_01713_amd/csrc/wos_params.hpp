@@ -81,6 +81,33 @@ constexpr int kClusterBox = 2 * kMaxDim;
 constexpr int kMfmaTile = 16;
 constexpr int kMfmaFeat = 12;
 
+// Cell lists.  The outer boundary's box (its first geom_d coordinates) is cut
+// into cubic cells, and every cell lists the obstacles that can be nearest to
+// some point of it: those whose distance from the cell is at most both the
+// largest distance to the outer boundary and the smallest over the obstacles
+// of the largest distance to one obstacle, taken over the cell.  A walk step
+// looks up its cell and evaluates only that list.  An entry's level says how
+// small the walker's threshold may be before the entry cannot matter: a list
+// holds its entries of distance (from the cell) at most kGridLev[0] edges
+// first, then those up to kGridLev[1], kGridLev[2] and the rest, and the
+// cell's header {offset, four count bytes} gives how many to read for a
+// threshold in each of the four ranges; byte kGridFull sends the walker to
+// the cluster scan instead (more entries than a byte counts).
+// Sizes: a walk simulation of the ragged batch evaluates 0.05-0.2 obstacles
+// per walk-step in d = 6, 7 at 2.6e5 cells (against 10 members of kept
+// clusters), 1.2-1.8 in the densest 4- and 5-D scenes; twice the edge at least
+// doubles that, half of it no longer fits an XCD's 4 MB L2 with its headers.
+constexpr int kGridMin = 16;            // fewer obstacles: every one is scanned
+constexpr int kGridCellsMax = 1 << 18;  // target cells (per axis counts are rounded up)
+constexpr int kGridCellsPer = 1024;     // target cells per obstacle, below kGridCellsMax
+constexpr int kGridMaxAxis = 512;
+constexpr uint32_t kGridFull = 255;
+constexpr double kGridLev[3] = {0.08, 0.25, 0.6};
+struct GridCell {
+    uint32_t off;     // first entry in the list
+    uint32_t counts;  // entries to read per threshold range, one byte each
+};
+
 // Per-environment parameters of one walk launch.  Read by every lane with
 // wave-uniform addresses, so the compiler keeps them in scalar registers.
 template <typename T>
@@ -101,6 +128,14 @@ struct EnvP {
                                  // wave-uniform member scan, 2 matrix cores with pair compaction;
                                  // box_test (with 2): pairs pass the bounding-box test first
     int32_t d, has_goal;
+    const GridCell* sph_cells;  // cell lists (caller-order row indices); null: none
+    const GridCell* box_cells;
+    const uint32_t* sph_list;
+    const uint32_t* box_list;
+    uint32_t grid_n[kMaxDim];   // cells per axis (1 past geom_d)
+    uint32_t grid_last, pad_grid;  // cells - 1
+    T grid_inv, grid_off[kMaxDim], grid_max[kMaxDim];  // cell coordinate x inv + off, clamped to [0, max]
+    T grid_lev[3];              // threshold ranges of the count bytes
     int32_t geom_d, pad_g;     // obstacles and the outer boundary depend on x[0..geom_d) only
     const T* arm_pts;          // planar arm: n_arm x 2 task-plane obstacle points
     int32_t n_arm, pad_arm;    // 0: no arm

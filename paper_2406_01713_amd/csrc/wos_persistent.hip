@@ -21,16 +21,16 @@ typedef __attribute__((address_space(4))) const BatchEnv CBatch;
 template <bool BWD, bool SRC>
 __device__ __forceinline__ bool step_any_d(int d, cenv<float> p, Walker<float, kMaxDim>& s, uint32_t q,
                                            uint32_t k0, uint32_t k1, WalkEnd<float>& e, WorkCount& wc,
-                                           bool live)
+                                           bool live, UnitStart<float>& st)
 {
     switch (d) {
-    case 2: return walker_step<float, 2, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live);
-    case 3: return walker_step<float, 3, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live);
-    case 4: return walker_step<float, 4, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live);
-    case 5: return walker_step<float, 5, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live);
-    case 6: return walker_step<float, 6, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live);
-    case 7: return walker_step<float, 7, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live);
-    default: return walker_step<float, 8, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live);
+    case 2: return walker_step<float, 2, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
+    case 3: return walker_step<float, 3, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
+    case 4: return walker_step<float, 4, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
+    case 5: return walker_step<float, 5, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
+    case 6: return walker_step<float, 6, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
+    case 7: return walker_step<float, 7, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
+    default: return walker_step<float, 8, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
     }
 }
 
@@ -85,11 +85,12 @@ __device__ __forceinline__ void run_unit(cenv<float> p, CBatch& be, int64_t loca
     int32_t base = lanes;
     const uint32_t qi = (uint32_t)ql;
     WorkCount wc(pairs);
+    UnitStart<float> st;
 
     while (__builtin_amdgcn_ballot_w64(active) != 0) {
         WalkEnd<float> e;
         // idle lanes (the unit has no walks left for them) step along
-        bool fin = step_any_d<BWD, SRC>(d, p, s, qi, k0, k1, e, wc, active);
+        bool fin = step_any_d<BWD, SRC>(d, p, s, qi, k0, k1, e, wc, active, st);
         fin = fin && active;
         {
             if (fin) {

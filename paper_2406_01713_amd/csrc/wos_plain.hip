@@ -56,12 +56,13 @@ plain_kernel(const EnvP<T>* penv, const T* __restrict__ queries, int64_t n_units
     e.status = kTruncated;
     e.cls = kOuter;
     WorkCount wc(pair_lds[wv]);
+    UnitStart<T> st;
     // every lane steps until the wave's last walk ends (a finished lane runs
     // along idle), so the obstacle scans and the work tally stay wave-uniform
     bool done = !active;
     while (__builtin_amdgcn_ballot_w64(!done) != 0) {
         WalkEnd<T> ek;
-        const bool fin = walker_step<T, D, BWD, D, SRC>(p, s, q_base + (uint32_t)q, k0, k1, ek, wc, !done);
+        const bool fin = walker_step<T, D, BWD, D, SRC>(p, s, q_base + (uint32_t)q, k0, k1, ek, wc, !done, st);
         if (fin && !done) {
             e = ek;
             done = true;
