@@ -184,7 +184,10 @@ typedef struct {
  * then boxes, then the arm, then the outer boundary.  With 64 or more spheres
  * (boxes) the domain also keeps them grouped in clusters of 8 with bounding
  * spheres; the walk kernels skip a cluster that provably holds no nearer
- * obstacle, which changes the work done, never a distance or a walk.
+ * obstacle, which changes the work done, never a distance or a walk.  From 16
+ * obstacles of a kind on, a table of cells over the outer boundary's box lists
+ * the obstacles that can be nearest in each cell (built on the device during
+ * this call, 1 to 10 MB); walk steps read their cell's list.
  * source may be NULL (no volume source, the boundary-data problem).
  * Errors: WOS_EDIM, WOS_EINVAL (NULL out/outer/bdata, non-finite values,
  * negative radii, empty box, bad source, geom_d outside [0, d], boxes or an
@@ -271,10 +274,13 @@ int wos_backward(const wos_domain* dom, const void* queries, int64_t n_queries, 
  *              se_grad, then
  *              [12] sphere distances evaluated per walk (mean),
  *              [13] box distances evaluated per walk (mean),
- *              [14] cluster bounds evaluated per walk (mean),
- *              [15] cluster bounding boxes tested per walk (mean); these
- *              count the work the obstacle scan did after culling (per walk
- *              they wrap modulo 2^32)
+ *              [14] clusters x walk-steps per walk (mean): the bounds a
+ *              cluster scan of every step takes,
+ *              [15] cluster bounding boxes tested per walk (mean); 12, 13
+ *              and 15 count the work the obstacle scan did after culling
+ *              (per walk they wrap modulo 2^32).  A call that asks for them
+ *              scans every obstacle of environments with fewer than 64 at
+ *              each step; without out_stats those read their cell lists too
  *   grad_u     device float, sum Q, or NULL for forward only
  *   out_dx     device float, (sum Q) x 8 (required with grad_u)
  *   out_dsigma device double, n_envs (required with grad_u)

@@ -23,7 +23,8 @@ ARCH = os.environ.get("WOS_OFFLOAD_ARCH", "gfx950")
 
 # (source, macro definitions): the walk kernels are compiled once per
 # variant, so their long compilations run side by side
-SOURCES = [("wos_persistent.hip", ["-DWOS_PERSISTENT_SRC=0"]), ("wos_persistent.hip", ["-DWOS_PERSISTENT_SRC=1"]),
+SOURCES = [*(("wos_persistent.hip", [f"-DWOS_PERSISTENT_SRC={s}", f"-DWOS_PERSISTENT_LISTS={l}"])
+             for s in (0, 1) for l in (0, 1)),
            ("wos_plain.hip", ["-DWOS_PLAIN_T=float"]), ("wos_plain.hip", ["-DWOS_PLAIN_T=double"]),
            ("wos_kernels.hip", []), ("wos_grid.hip", []), ("wos_api.cpp", []), ("wos_microbench.hip", [])]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-x", "hip",

@@ -833,7 +833,7 @@ struct BatchLayout {
 // n_envs rows of the unit table.  force: launch-shape fields > 0 override
 // the tuned ones.
 void plan_batch(const wos_domain* const* envs, const int64_t* q_off, int n_envs, const int64_t* n_walks,
-                int q_stride, const Tune* force, bool full_scan, bool src, int* order, BatchEnv* benv,
+                int q_stride, const Tune* force, bool full_scan, bool src, bool lists, int* order, BatchEnv* benv,
                 BatchLayout& L)
 {
     int64_t sumQW = 0, maxM = 0, heavyQ = 0, maxW = 1;
@@ -863,7 +863,7 @@ void plan_batch(const wos_domain* const* envs, const int64_t* q_off, int n_envs,
     // scans of those walks (the pair rounds spread over all 64 lanes)
     const int64_t lanes = kWave / t.lanes_per_walker;
     const int block = t.waves_per_block * kWave;
-    const int resident_blocks = persistent_resident_blocks(true, src, block);
+    const int resident_blocks = persistent_resident_blocks(true, src, lists, block);
     L.block = block;
     L.grid = std::max(1, resident_blocks * t.grid_mult);
     const int64_t waves = (int64_t)L.grid * (block / kWave);
@@ -1027,16 +1027,17 @@ int run_batch(const wos_domain* const* envs, int n_envs, const float* queries, c
     }
     EnvP<float>* hp = reinterpret_cast<EnvP<float>*>(host_tab);
     BatchEnv* hb = reinterpret_cast<BatchEnv*>(host_tab + env_bytes);
-    bool src = false;
+    bool src = false, lists = true;
     for (int e = 0; e < n_envs; ++e) {
         if ((rc = make_env<float>(envs[e], sigma[e], eps[e], seed, (uint32_t)e, o, hp[e], out_stats != nullptr))) return rc;
         src = src || envs[e]->has_src;
+        lists = lists && lists_ok(hp[e]);
         if (bwd && envs[e]->has_src && !(sigma[e] > 0.0))
             return fail(WOS_ENOTSUP, "env %d: the sigma derivative of a point source is provided for sigma > 0 only", e);
     }
 
     BatchLayout L;
-    plan_batch(envs, q_offsets, n_envs, n_walks, kBatchStride, force, (o.flags & WOS_FULL_SCAN) != 0, src, order, hb,
+    plan_batch(envs, q_offsets, n_envs, n_walks, kBatchStride, force, (o.flags & WOS_FULL_SCAN) != 0, src, lists, order, hb,
                L);
     // the kernel hands out units with a 32-bit device counter
     if (L.total_units >= ((int64_t)1 << 32) - 1)
@@ -1071,7 +1072,7 @@ int run_batch(const wos_domain* const* envs, int n_envs, const float* queries, c
     const BatchEnv* d_benv = (const BatchEnv*)(d_tab + env_bytes);
     // the counter starts at 0 (a fill kernel: no memset node if the caller captures)
     WOS_HIP(launch_fill_u32(counter, 1, 0u, st), "fill");
-    WOS_HIP(launch_persistent(bwd, src, L.grid, L.block, d_env, d_benv, n_envs, queries, L.total_units,
+    WOS_HIP(launch_persistent(bwd, src, lists, L.grid, L.block, d_env, d_benv, n_envs, queries, L.total_units,
                               (uint32_t)seed, (uint32_t)(seed >> 32), nullptr, counter, partials, st),
             "persistent walk kernel");
     WOS_HIP(launch_finalize_batch(bwd, d_benv, n_envs, partials, grad_u, out_u, out_grad, kBatchStride,
@@ -1608,7 +1609,7 @@ static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, in
         }
         EnvP<double>* pd;
         if ((rc = S.get(&pd, 1)) || (rc = upload(pd, &p, sizeof(p), st))) return rc;
-        WOS_HIP(launch_plain<double>(d, bwd, D->has_src, pd, (const double*)queries, Q, n_walks, 0, 0, nullptr, partials,
+        WOS_HIP(launch_plain<double>(d, bwd, D->has_src, lists_ok(p), pd, (const double*)queries, Q, n_walks, 0, 0, nullptr, partials,
                                      nullptr, st),
                 "plain walk kernel");
         WOS_HIP(launch_finalize_plain<double>(d, bwd, partials, Q, chunks, n_walks, uo, (double*)out_grad, out_stats,
@@ -1632,7 +1633,7 @@ static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, in
         }
         EnvP<float>* pd;
         if ((rc = S.get(&pd, 1)) || (rc = upload(pd, &p, sizeof(p), st))) return rc;
-        WOS_HIP(launch_plain<float>(d, bwd, D->has_src, pd, (const float*)queries, Q, n_walks, 0, 0, nullptr, partials,
+        WOS_HIP(launch_plain<float>(d, bwd, D->has_src, lists_ok(p), pd, (const float*)queries, Q, n_walks, 0, 0, nullptr, partials,
                                     nullptr, st),
                 "plain walk kernel");
         if (o.flags & WOS_OUT_FP64)  // forward only: the FP64 sums written without rounding to FP32
@@ -1711,7 +1712,7 @@ int wos_debug_walks(const wos_domain* D, const double* query, uint32_t q_index, 
             if (!rc && e == hipSuccess) e = hipMalloc(&pd, sizeof(p));
             if (!rc && e == hipSuccess) e = hipMemcpy(pd, &p, sizeof(p), hipMemcpyHostToDevice);
             if (!rc && e == hipSuccess)
-                e = launch_plain<double>(d, true, D->has_src, (const EnvP<double>*)pd, (const double*)dq, 1, n, w0, q_index, nullptr,
+                e = launch_plain<double>(d, true, D->has_src, lists_ok(p), (const EnvP<double>*)pd, (const double*)dq, 1, n, w0, q_index, nullptr,
                                          part, rec, nullptr);
             if (e == hipSuccess) e = hipDeviceSynchronize();
             (void)hipFree(pd);
@@ -1725,7 +1726,7 @@ int wos_debug_walks(const wos_domain* D, const double* query, uint32_t q_index, 
             if (!rc && e == hipSuccess) e = hipMalloc(&pd, sizeof(p));
             if (!rc && e == hipSuccess) e = hipMemcpy(pd, &p, sizeof(p), hipMemcpyHostToDevice);
             if (!rc && e == hipSuccess)
-                e = launch_plain<float>(d, true, D->has_src, (const EnvP<float>*)pd, (const float*)dq, 1, n, w0, q_index, nullptr,
+                e = launch_plain<float>(d, true, D->has_src, lists_ok(p), (const EnvP<float>*)pd, (const float*)dq, 1, n, w0, q_index, nullptr,
                                         part, rec, nullptr);
             if (e == hipSuccess) e = hipDeviceSynchronize();
             (void)hipFree(pd);
@@ -1823,7 +1824,7 @@ int wos_plan_create(const wos_domain* D, float* x, int64_t n_starts, int64_t n_w
     BatchLayout L;
     BatchEnv benv1;
     int order1;
-    plan_batch(envs, qoff, 1, nw, D->d, nullptr, (o.flags & WOS_FULL_SCAN) != 0, D->has_src, &order1, &benv1, L);
+    plan_batch(envs, qoff, 1, nw, D->d, nullptr, (o.flags & WOS_FULL_SCAN) != 0, D->has_src, lists_ok(P->henv), &order1, &benv1, L);
     if (L.total_units >= ((int64_t)1 << 32) - 1) {
         plan_free(P);
         return fail(WOS_EINVAL, "the plan splits into %lld work units; at most 2^32 - 2", (long long)L.total_units);
@@ -1860,7 +1861,7 @@ int wos_plan_create(const wos_domain* D, float* x, int64_t n_starts, int64_t n_w
     // capture [fused forward + backward walks, finalize, update]
     e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        hipError_t e1 = launch_persistent(true, D->has_src, L.grid, L.block, P->env, P->benv, 1, x, L.total_units,
+        hipError_t e1 = launch_persistent(true, D->has_src, lists_ok(P->henv), L.grid, L.block, P->env, P->benv, 1, x, L.total_units,
                                           P->henv.key0, P->henv.key1, P->step, P->counter, P->partials, st);
         hipError_t e2 = launch_finalize_batch(true, P->benv, 1, P->partials, P->ubar, P->u, P->grad,
                                               kBatchStride, nullptr, P->dx, P->dsig, P->dg, P->dir, P->counter, st);

@@ -660,12 +660,14 @@ __device__ __forceinline__ uint32_t grid_cell(cenv<T> p, const T (&x)[D])
     return idx < p->grid_last ? idx : p->grid_last;
 }
 
-// Entries of a cell to read for threshold t (kGridFull: scan the clusters).
+// Entries of a cell to read for threshold t.
 template <typename T>
 __device__ __forceinline__ uint32_t grid_count(cenv<T> p, uint32_t counts, T t)
 {
     const uint32_t sh = t <= p->grid_lev[0] ? 0u : t <= p->grid_lev[1] ? 8u : t <= p->grid_lev[2] ? 16u : 24u;
-    return (counts >> sh) & 0xFFu;
+    const uint32_t c = (counts >> sh) & 0xFFu;
+    if (__builtin_amdgcn_ballot_w64(c >= kGridCoarse) == 0) return c;  // wave-uniform
+    return grid_decode(c);
 }
 
 // Lists of at most kCellDirect entries are walked by their own lanes; longer
@@ -862,10 +864,10 @@ __device__ __forceinline__ float cluster_min_pairs(cptr<float> rows, const float
     return float_of_ord(best[lane]);
 }
 
-// Minimum over one kind's obstacles by the cluster scan (or, below
-// kClusterMin of them and under WOS_FULL_SCAN, over all of them) for the
-// lanes of live.  n: distances per live lane (wave-uniform scans); evals,
-// cbt: distances and cluster boxes of the wave (pair scan).
+// Minimum over one kind's obstacles by the cluster scan, or, below
+// kClusterMin of them and under WOS_FULL_SCAN, over all of them.  n: distances
+// per live lane (wave-uniform scans); evals, cbt: distances and cluster boxes
+// of the wave (pair scan).
 template <typename T, int D, bool BOX>
 __device__ __forceinline__ T scan_min(cenv<T> p, const T (&xg)[D], T thr, bool live, uint32_t& n, uint64_t& evals,
                                       uint64_t& cbt, uint32_t* pairs)
@@ -894,93 +896,100 @@ __device__ __forceinline__ T scan_min(cenv<T> p, const T (&xg)[D], T thr, bool l
     return cluster_min<T, D, BOX>(rows, to_const(BOX ? p->box_bnd : p->sph_bnd), n_cl, xg, thr, live, n);
 }
 
-// R = distance to the boundary; cls = first component attaining it in the
-// order goal, spheres, boxes, outer, for the lanes of live.  The goal and outer
-// distances come first and bound the box scan, whose result then bounds the
-// sphere scan; ub, any value at or above the R a scan of every obstacle
-// computes (the walker's bound from its previous step, +inf when it has
-// none), bounds both scans as well.  Obstacles that a cell list or the
-// culling leaves out never attain R, so R and cls are as a scan of every
+// Distances to the components other than spheres and boxes.
+template <typename T, int D>
+__device__ __forceinline__ T goal_dist(cenv<T> p, const T (&x)[D])
+{
+    if (!p->has_goal) return Math<T>::inf();
+    T t = x[0] - p->goal_c[0];
+    T acc = t * t;
+#pragma unroll
+    for (int i = 1; i < D; ++i) {
+        t = x[i] - p->goal_c[i];
+        acc = Math<T>::fma(t, t, acc);
+    }
+    return Math<T>::sqrt(acc) - p->goal_r;
+}
+
+// R and its component (the first attaining it in the order goal, spheres,
+// boxes, arm, outer) from the components' distances.
+template <typename T>
+__device__ __forceinline__ T nearest_of(T dg, T ds, T db, T da, T dout, int& cls)
+{
+    const T ao = Math<T>::min(da, dout);
+    const T bo = Math<T>::min(db, ao);
+    const T rest = Math<T>::min(ds, bo);
+    cls = (dg <= rest) ? kGoal : (ds <= bo) ? kSphere : (db <= ao) ? kBox : (da <= dout) ? kArm : kOuter;
+    return Math<T>::min(dg, rest);
+}
+
+// R = distance to the boundary, cls its component, for the lanes of live.  The
+// goal and outer distances come first and bound the box scan, whose result
+// then bounds the sphere scan; ub, any value at or above the R a scan of every
+// obstacle computes (the walker's bound from its previous step, +inf when it
+// has none), bounds both scans as well.  Obstacles that the culling or a cell
+// list leaves out never attain R, so R and cls are as a scan of every
 // obstacle gives them.
 //
-// lists (wave-uniform): read the cell lists where the environment has them
-// (lanes of look; their points must lie inside the outer boundary up to
-// rounding); lanes whose list is too long, and every live lane without
-// lists, take the scan.  between() runs after the headers' loads are issued
-// and before they are used: work that does not depend on the distance hides
-// their latency there.
-template <typename T, int D, typename F>
-__device__ __forceinline__ T distance(cenv<T> p, const T (&x)[D], int& cls, WorkCount& wc, bool live, bool lists,
-                                      bool look, T ub, F&& between)
+// LISTS: environments whose obstacles are in cell lists (lanes of look read
+// them; their points must lie inside the outer boundary up to rounding) or
+// few enough to scan all; otherwise the cluster scan.  between() runs after
+// the list headers' loads are issued and before they are used: work that does
+// not depend on the distance hides their latency there.
+template <typename T, int D, bool LISTS, typename F>
+__device__ __forceinline__ T distance(cenv<T> p, const T (&x)[D], int& cls, WorkCount& wc, bool live, bool look,
+                                      T ub, F&& between)
 {
     // extruded geometry: obstacles and the outer boundary see the leading
     // geom_d coordinates only (their stored centres are zero beyond them)
     T xg[D];
 #pragma unroll
     for (int i = 0; i < D; ++i) xg[i] = (i < p->geom_d) ? x[i] : T(0);
-    const bool gs = lists && p->sph_cells != nullptr, gb = lists && p->box_cells != nullptr;  // wave-uniform
     GridCell hs = {0, 0}, hb = {0, 0};
-    if (gs || gb) {
+    const GridCell* cs = LISTS ? p->sph_cells : nullptr;  // wave-uniform
+    const GridCell* cb = LISTS ? p->box_cells : nullptr;
+    if (LISTS && (cs || cb)) {
         const uint32_t cell = grid_cell<T, D>(fresh(p), xg);
-        if (gs) hs = fresh(p)->sph_cells[cell];
-        if (gb) hb = fresh(p)->box_cells[cell];
+        if (cs) hs = cs[cell];
+        if (cb) hb = cb[cell];
     }
     between();
     p = fresh(p);
-    T dg = Math<T>::inf();
-    if (p->has_goal) {
-        T t = x[0] - p->goal_c[0];
-        T acc = t * t;
-#pragma unroll
-        for (int i = 1; i < D; ++i) {
-            t = x[i] - p->goal_c[i];
-            acc = Math<T>::fma(t, t, acc);
-        }
-        dg = Math<T>::sqrt(acc) - p->goal_r;
-    }
-    const T dout = outer_dist<T, D>(fresh(p), xg);
+    const T dg = goal_dist<T, D>(p, x);
+    const T dout = outer_dist<T, D>(p, xg);
     p = fresh(p);
     // the arm bound (joint coordinates, never extruded) tightens the scans
     const T da = p->n_arm ? arm_dist<T, D>(p, x) : Math<T>::inf();
-    const T dga = Math<T>::min(dg, Math<T>::min(da, dout));
-    const T tg = Math<T>::min(dga, ub);  // the scans' threshold before the box result
-    uint32_t nb = 0, ns = 0;  // member distances per lane (wave-uniform scans)
-    uint64_t eb = 0, es = 0;  // distances of the wave (cell lists and pair-compacted scans)
-    uint64_t cbt = 0;         // cluster bounding boxes tested by the wave
+    const T tg = Math<T>::min(Math<T>::min(dg, Math<T>::min(da, dout)), ub);  // threshold before the box result
     T db = Math<T>::inf(), ds = Math<T>::inf();
-    bool scan = live;
-    if (gb) {
-        uint32_t n = look ? grid_count<T>(fresh(p), hb.counts, tg) : 0u;
-        scan = n == kGridFull;
-        n = scan ? 0u : n;
-        db = cell_min<T, D, true>(to_const(fresh(p)->box_list), to_const(fresh(p)->box), hb.off, n, xg, eb, wc.pairs);
+    uint32_t nb = 0, ns = 0;  // distances per live lane (wave-uniform scans)
+    if (LISTS) {
+        if (cb) {
+            const uint32_t n = look ? grid_count<T>(fresh(p), hb.counts, tg) : 0u;
+            db = cell_min<T, D, true>(to_const(fresh(p)->box_list), to_const(fresh(p)->box), hb.off, n, xg, wc.box,
+                                      wc.pairs);
+        } else if (p->n_box) {
+            nb = (uint32_t)p->n_box;
+            db = boxes_min<T, D>(to_const(p->box), (int)nb, xg);
+        }
+        if (cs) {
+            const uint32_t n = look ? grid_count<T>(fresh(p), hs.counts, Math<T>::min(tg, db)) : 0u;
+            ds = cell_min<T, D, false>(to_const(fresh(p)->sph_list), to_const(fresh(p)->sph), hs.off, n, xg, wc.sph,
+                                       wc.pairs);
+        } else if (p->n_sph) {
+            ns = (uint32_t)p->n_sph;
+            ds = spheres_min<T, D>(to_const(p->sph), (int)ns, xg);
+        }
+    } else {
+        db = scan_min<T, D, true>(p, xg, tg, live, nb, wc.box, wc.cbox, wc.pairs);
+        ds = scan_min<T, D, false>(p, xg, Math<T>::min(tg, db), live, ns, wc.sph, wc.cbox, wc.pairs);
     }
-    if (!gb || __builtin_amdgcn_ballot_w64(scan) != 0) {
-        const T b = scan_min<T, D, true>(p, xg, tg, scan, nb, eb, cbt, wc.pairs);
-        db = Math<T>::min(db, (scan || !gb) ? b : Math<T>::inf());
-        wc.box += (uint64_t)__popcll(__ballot(scan)) * nb;
+    if (!LISTS || (ns | nb) != 0) {
+        const uint64_t lanes = (uint64_t)__popcll(__builtin_amdgcn_ballot_w64(live));
+        wc.sph += lanes * ns;
+        wc.box += lanes * nb;
     }
-    scan = live;
-    const T ts = Math<T>::min(tg, db);
-    if (gs) {
-        uint32_t n = look ? grid_count<T>(fresh(p), hs.counts, ts) : 0u;
-        scan = n == kGridFull;
-        n = scan ? 0u : n;
-        ds = cell_min<T, D, false>(to_const(fresh(p)->sph_list), to_const(fresh(p)->sph), hs.off, n, xg, es, wc.pairs);
-    }
-    if (!gs || __builtin_amdgcn_ballot_w64(scan) != 0) {
-        const T s = scan_min<T, D, false>(p, xg, ts, scan, ns, es, cbt, wc.pairs);
-        ds = Math<T>::min(ds, (scan || !gs) ? s : Math<T>::inf());
-        wc.sph += (uint64_t)__popcll(__ballot(scan)) * ns;
-    }
-    wc.sph += es;
-    wc.box += eb;
-    wc.cbox += cbt;
-    const T ao = Math<T>::min(da, dout);
-    const T bo = Math<T>::min(db, ao);
-    const T rest = Math<T>::min(ds, bo);
-    cls = (dg <= rest) ? kGoal : (ds <= bo) ? kSphere : (db <= ao) ? kBox : (da <= dout) ? kArm : kOuter;
-    return Math<T>::min(dg, rest);
+    return nearest_of<T>(dg, ds, db, da, dout, cls);
 }
 
 // Closest boundary point xbar on the absorbing component (Fig. 2), in the
@@ -1224,6 +1233,112 @@ __device__ __noinline__ SourceTerm<T> ball_green(cenv<T> p, T r, T R)
 }
 
 // ------------------------------------------------------------------------
+// Start of a work unit: all its walks start at the same query point, so the
+// distance there, its component and the gradient factor (d / R_0) C1(R_0) are
+// taken once, the obstacles (or clusters of them) spread over the lanes.
+// Query points may lie anywhere, also outside the cell table.
+// ------------------------------------------------------------------------
+template <typename T>
+struct UnitStart {
+    T R, gfac;
+    int cls;
+};
+
+// Lane 0's value in a scalar register.
+__device__ __forceinline__ float uniform_of(float v)
+{
+    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v)));
+}
+__device__ __forceinline__ double uniform_of(double v)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Minimum over one kind's obstacles at a point all lanes share: lane l takes
+// obstacles l, l + 64, ..., or clusters, each passing its bounding sphere's
+// test against thr (as cluster_min) and, with the bounding-box test (FP32, as
+// box_round), its box's before its members are evaluated.
+template <typename T, int D, bool BOX>
+__device__ __forceinline__ T start_min(cenv<T> p, const T (&xg)[D], T thr, uint64_t& evals, uint64_t& cbt)
+{
+    constexpr int S = BOX ? box_stride(D) : sph_stride(D);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int n_cl = BOX ? p->n_cl_box : p->n_cl_sph;
+    T best = Math<T>::inf();
+    if (!n_cl) {
+        const int n = BOX ? p->n_box : p->n_sph;
+        cptr<T> rows = to_const(BOX ? p->box : p->sph);
+        for (int j = lane; j < n; j += kWave)
+            best = Math<T>::min(best, BOX ? box_dist<T, D>(xg, rows + (int64_t)j * S) : sphere_dist<T, D>(xg, rows + (int64_t)j * S));
+        evals += (uint64_t)n;
+    } else {
+        constexpr int SB = sph_stride(D);
+        cptr<T> bnd = to_const(BOX ? p->box_bnd : p->sph_bnd);
+        cptr<T> rows = to_const(BOX ? p->box_cl : p->sph_cl);
+        cptr<float> boxes = to_const(BOX ? p->box_cb : p->sph_cb);
+        const bool box_test = sizeof(T) == 4 && p->box_test;
+        for (int c0 = 0; c0 < n_cl; c0 += kWave) {  // wave-uniform
+            const int c = c0 + lane < n_cl ? c0 + lane : n_cl - 1;
+            const T lb = cluster_bound<T, D>(xg, bnd + (int64_t)c * SB);
+            bool need = c0 + lane < n_cl && !(lb > thr || lb > best);
+            if (box_test) {
+                cbt += (uint64_t)__popcll(__builtin_amdgcn_ballot_w64(need));
+                cptr<float> r = boxes + (int64_t)c * kClusterBox;
+                T acc = T(0);
+#pragma unroll
+                for (int i = 0; i < D; ++i) {
+                    const T t = Math<T>::max(Math<T>::max((T)r[i] - xg[i], xg[i] - (T)r[kMaxDim + i]), T(0));
+                    acc = Math<T>::fma(t, t, acc);
+                }
+                need = need && !(Math<T>::sqrt(acc) * Cull<T>::shrink > Math<T>::max(thr, T(0)));
+            }
+            evals += (uint64_t)__popcll(__builtin_amdgcn_ballot_w64(need)) * kCluster;
+            if (need) {
+                cptr<T> m = rows + (int64_t)c * (kCluster * S);
+#pragma unroll 1
+                for (int j = 0; j < kCluster; ++j)
+                    best = Math<T>::min(best, BOX ? box_dist<T, D>(xg, m + j * S) : sphere_dist<T, D>(xg, m + j * S));
+            }
+        }
+    }
+#pragma unroll
+    for (int off = kWave / 2; off >= 1; off >>= 1) best = Math<T>::min(best, __shfl_xor(best, off, kWave));
+    return best;
+}
+
+template <typename T, int D, int DA>
+__device__ __forceinline__ UnitStart<T> unit_start(cenv<T> p, const T (&xq)[DA], WorkCount& wc)
+{
+    T x[D], xg[D];
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+        x[i] = xq[i];
+        xg[i] = (i < p->geom_d) ? x[i] : T(0);
+    }
+    const T dg = goal_dist<T, D>(p, x);
+    const T dout = outer_dist<T, D>(p, xg);
+    const T da = p->n_arm ? arm_dist<T, D>(p, x) : Math<T>::inf();
+    const T tg = Math<T>::min(dg, Math<T>::min(da, dout));
+    uint64_t es = 0, eb = 0, cbt = 0;
+    const T db = start_min<T, D, true>(p, xg, tg, eb, cbt);
+    const T ds = start_min<T, D, false>(p, xg, Math<T>::min(tg, db), es, cbt);
+    // counted where the steps' own work is that of the lists (scans of every
+    // obstacle count one evaluation per obstacle and step, the first included)
+    if (p->box_cells) wc.box += eb;
+    if (p->sph_cells) wc.sph += es;
+    if (p->box_cells || p->sph_cells) wc.cbox += cbt;
+    UnitStart<T> st;
+    int cls;
+    st.R = uniform_of(nearest_of<T>(dg, ds, db, da, dout, cls));
+    st.cls = __builtin_amdgcn_readfirstlane(cls);
+    st.gfac = uniform_of(T(D) * Math<T>::rcp(st.R * horner<T>(p->cC1, p->nt_C1, p->qsigma * (st.R * st.R))));
+    return st;
+}
+
+// ------------------------------------------------------------------------
 // One walk (Sec. IV-A).  State lives in registers; an iteration makes one
 // distance evaluation and either absorbs (eps-shell, Fig. 2) or applies the
 // step's weight and jumps to a uniform point on the sphere of radius R.
@@ -1244,32 +1359,6 @@ struct Walker {
     int32_t ex;  // W, W1, src, src1 and srcS hold their values times 2^-ex (FP32 only)
     T rb;        // bound on this step's R from the previous one (+inf on a walk's first step)
 };
-
-// What every walk of a work unit shares, because all start at the unit's query
-// point: R and its component there, and the gradient factor (d / R_0) C1(R_0).
-// The unit's first step (first set, every lane at the query point) takes the
-// distance by the cluster scan, which also serves points outside the cell
-// table, and fills the rest in.
-template <typename T>
-struct UnitStart {
-    T R = T(0);
-    T gfac = T(0);
-    int cls = kOuter;
-    bool first = true;
-};
-
-// Lane 0's value in a scalar register.
-__device__ __forceinline__ float uniform_of(float v)
-{
-    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v)));
-}
-__device__ __forceinline__ double uniform_of(double v)
-{
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
 
 template <typename T>
 struct WalkEnd {
@@ -1340,11 +1429,12 @@ __device__ __forceinline__ void renormalize(Walker<double, DA>&) {}
 
 // Returns true when the walk ended (e is then filled in).  (key0, key1) is
 // the Philox key of the launch, q the query's index in its environment, st
-// the unit's start (lane 0 must be live on the unit's first step).  The walker
-// may store DA >= D coordinates; only the first D are used.
-template <typename T, int D, bool BWD, int DA = D, bool SRC = false>
+// the unit's start.  LISTS: see distance().  The walker may store DA >= D
+// coordinates; only the first D are used.
+template <typename T, int D, bool BWD, bool LISTS, int DA = D, bool SRC = false>
 __device__ __forceinline__ bool walker_step(cenv<T> p0, Walker<T, DA>& s, uint32_t q, uint32_t key0,
-                                            uint32_t key1, WalkEnd<T>& e, WorkCount& wc, bool live, UnitStart<T>& st)
+                                            uint32_t key1, WalkEnd<T>& e, WorkCount& wc, bool live,
+                                            const UnitStart<T>& st)
 {
     static_assert(DA >= D, "walker storage narrower than the dimension");
     const T(&x)[D] = reinterpret_cast<const T(&)[D]>(s.x);
@@ -1354,19 +1444,11 @@ __device__ __forceinline__ bool walker_step(cenv<T> p0, Walker<T, DA>& s, uint32
     const uint32_t k = s.k;
     // the step's direction does not depend on its distance
     T v[D];
-    T R = distance<T, D>(fresh(p0), x, cls, wc, live, !st.first, live && k > 0, kBound ? s.rb : Math<T>::inf(),
-                         [&] { direction<T, D>(k, s.w, q, fresh(p0)->env_id, key0, key1, v); });
+    T R = distance<T, D, LISTS>(fresh(p0), x, cls, wc, live, live && k > 0, kBound ? s.rb : Math<T>::inf(),
+                                [&] { direction<T, D>(k, s.w, q, fresh(p0)->env_id, key0, key1, v); });
+    R = k > 0 ? R : st.R;
+    cls = k > 0 ? cls : st.cls;
     cenv<T> p = fresh(p0);
-    if (st.first) {  // wave-uniform
-        st.R = uniform_of(R);
-        st.cls = __builtin_amdgcn_readfirstlane(cls);
-        st.gfac = T(D) * Math<T>::rcp(st.R * horner<T>(p->cC1, p->nt_C1, p->qsigma * (st.R * st.R)));
-        st.first = false;
-    } else {
-        R = k > 0 ? R : st.R;
-        cls = k > 0 ? cls : st.cls;
-    }
-    p = fresh(p0);
     // R(x) is a minimum of distances, each 1-Lipschitz, and the walker moves
     // R: the next R is at most 2 R, and with the margins (rb_abs covers the
     // rounding of the positions and of every component's computed distance,

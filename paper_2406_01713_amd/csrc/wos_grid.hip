@@ -103,7 +103,7 @@ __device__ __forceinline__ int level_of(const GridBuild& g, float nd, float lim)
 template <int K, bool BOX>
 __global__ void __launch_bounds__(kBlock)
 grid_count_kernel(GridBuild g, int d, const float* rows_, int m, float* __restrict__ lims,
-                  GridCell* __restrict__ cells, unsigned* __restrict__ total)
+                  GridCell* __restrict__ cells, unsigned* __restrict__ total, unsigned* __restrict__ overfull)
 {
     const uint32_t c = blockIdx.x * kBlock + threadIdx.x;
     const bool valid = c < g.cells;
@@ -122,9 +122,11 @@ grid_count_kernel(GridBuild g, int d, const float* rows_, int m, float* __restri
     uint32_t stored = 0, counts = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const bool fits = n[i] < kGridFull;
-        counts |= (fits ? n[i] : kGridFull) << (8 * i);
-        stored = fits ? n[i] : stored;
+        // a range's entries follow the (rounded-up) ranges before it
+        const uint32_t code = grid_encode(stored + n[i] - (i > 0 ? n[i > 0 ? i - 1 : 0] : 0u));
+        if (code > 255u) *overfull = 1u;
+        counts |= (code < 255u ? code : 255u) << (8 * i);
+        stored = grid_decode(code < 255u ? code : 255u);
     }
     stored = valid ? stored : 0u;
     const uint32_t incl = wave_incl_scan(stored);
@@ -151,10 +153,8 @@ grid_fill_kernel(GridBuild g, int d, const float* rows_, int m, const float* __r
     uint32_t pos[4], end[4], at = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const uint32_t n = (h.counts >> (8 * i)) & 0xFFu;
         pos[i] = at;
-        end[i] = n == kGridFull ? at : n;  // a range past the byte's counts is not stored
-        at = end[i];
+        at = end[i] = grid_decode((h.counts >> (8 * i)) & 0xFFu);
     }
     if (at == 0) return;
     cptr<float> rows = to_const(rows_);
@@ -167,29 +167,34 @@ grid_fill_kernel(GridBuild g, int d, const float* rows_, int m, const float* __r
         for (int i = 0; i < 4; ++i)
             if (l == i && pos[i] < end[i]) list[h.off + pos[i]++] = (uint32_t)j;
     }
+    // rounded-up counts: repeat the cell's first entry
+    const uint32_t first = list[h.off];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        for (; pos[i] < end[i]; ++pos[i]) list[h.off + pos[i]] = first;
 }
 
 template <int K, bool BOX>
 hipError_t build_k(const GridBuild& g, int d, const float* rows, int m, GridCell** cells, uint32_t** list)
 {
     const unsigned grid = (g.cells + kBlock - 1) / kBlock;
-    // [headers | limits | total]
     unsigned char* buf = nullptr;
     float* lims = nullptr;
     uint32_t* entries = nullptr;
-    unsigned total = 0;
+    unsigned told[2] = {0, 0};  // entries, whether some cell holds too many
     hipError_t e = hipMalloc(&buf, (size_t)g.cells * sizeof(GridCell));
-    if (e == hipSuccess) e = hipMalloc(&lims, ((size_t)g.cells + 1) * sizeof(float));
+    if (e == hipSuccess) e = hipMalloc(&lims, ((size_t)g.cells + 2) * sizeof(float));
     GridCell* hd = reinterpret_cast<GridCell*>(buf);
-    unsigned* d_total = reinterpret_cast<unsigned*>(lims) + g.cells;
-    if (e == hipSuccess) e = launch_fill_u32(d_total, 1, 0u, nullptr);
+    unsigned* d_told = reinterpret_cast<unsigned*>(lims) + g.cells;
+    if (e == hipSuccess) e = launch_fill_u32(d_told, 2, 0u, nullptr);
     if (e == hipSuccess) {
         hipLaunchKernelGGL((grid_count_kernel<K, BOX>), dim3(grid), dim3(kBlock), 0, nullptr, g, d, rows, m, lims, hd,
-                           d_total);
+                           d_told, d_told + 1);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = hipMemcpy(&total, d_total, sizeof(total), hipMemcpyDeviceToHost);
-    const bool fits = total <= kGridEntriesMax;
+    if (e == hipSuccess) e = hipMemcpy(told, d_told, sizeof(told), hipMemcpyDeviceToHost);
+    const unsigned total = told[0];
+    const bool fits = total <= kGridEntriesMax && told[1] == 0;
     if (e == hipSuccess && fits) e = hipMalloc(&entries, std::max<size_t>(total, 1) * sizeof(uint32_t));
     if (e == hipSuccess && fits) {
         hipLaunchKernelGGL((grid_fill_kernel<K, BOX>), dim3(grid), dim3(kBlock), 0, nullptr, g, d, rows, m, lims, hd,

@@ -237,7 +237,7 @@ plan_update(const EnvP<float>* penv, float* __restrict__ x, int64_t n, const flo
     for (int i = 0; i < D; ++i) xs[i] = (n > 0) ? x[si * D + i] : 0.0f;
     int cls;
     WorkCount wc(pair_lds[__builtin_amdgcn_readfirstlane(threadIdx.x / kWave)]);
-    const float R = distance<float, D>(p, xs, cls, wc, valid, false, false, Math<float>::inf(), [] {});
+    const float R = distance<float, D, false>(p, xs, cls, wc, valid, false, Math<float>::inf(), [] {});
     if (valid) {
         float dz2 = 0.0f;
         if (p->has_src) {
@@ -358,19 +358,22 @@ hipError_t launch_reduce_pairs(const double* prod, int64_t n, double* out0, doub
     return hipGetLastError();
 }
 
-hipError_t launch_persistent(bool bwd, bool src, int grid, int block, const EnvP<float>* envs,
+hipError_t launch_persistent(bool bwd, bool src, bool lists, int grid, int block, const EnvP<float>* envs,
                              const BatchEnv* benv, int n_benv, const float* queries, int64_t total_units,
                              uint32_t key0, uint32_t key1, const uint64_t* key_add, unsigned* counter,
                              double* partials, hipStream_t st)
 {
     if (total_units == 0) return hipSuccess;
-    return src ? launch_persistent_variant<true>(bwd, grid, block, envs, benv, n_benv, queries, total_units, key0, key1, key_add, counter, partials, st)
-               : launch_persistent_variant<false>(bwd, grid, block, envs, benv, n_benv, queries, total_units, key0, key1, key_add, counter, partials, st);
+    auto* go = src ? (lists ? launch_persistent_variant<true, true> : launch_persistent_variant<true, false>)
+                   : (lists ? launch_persistent_variant<false, true> : launch_persistent_variant<false, false>);
+    return go(bwd, grid, block, envs, benv, n_benv, queries, total_units, key0, key1, key_add, counter, partials, st);
 }
 
-int persistent_resident_blocks(bool bwd, bool src, int block)
+int persistent_resident_blocks(bool bwd, bool src, bool lists, int block)
 {
-    const int per_cu = src ? persistent_blocks_per_cu<true>(bwd, block) : persistent_blocks_per_cu<false>(bwd, block);
+    auto* per = src ? (lists ? persistent_blocks_per_cu<true, true> : persistent_blocks_per_cu<true, false>)
+                    : (lists ? persistent_blocks_per_cu<false, true> : persistent_blocks_per_cu<false, false>);
+    const int per_cu = per(bwd, block);
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess) return per_cu;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 1;

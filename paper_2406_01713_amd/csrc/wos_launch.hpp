@@ -7,11 +7,20 @@
 
 namespace wos {
 
+// Whether the steps can do without the cluster scan: every kind's obstacles
+// are in cell lists or few enough to be scanned.
+template <typename T>
+bool lists_ok(const EnvP<T>& p)
+{
+    return (p.sph_cells || !p.n_cl_sph) && (p.box_cells || !p.n_cl_box);
+}
+
 // Plain walk kernel: one walk per lane, one wave per (query, 64-walk chunk),
 // no refill.  Writes one partial-sum row per wave.  p is a device pointer;
-// src selects the variant with point-source terms.
+// src selects the variant with point-source terms, lists the one whose steps
+// read cell lists or scan every obstacle (EnvP must be fit for it: lists_ok).
 template <typename T>
-hipError_t launch_plain(int d, bool bwd, bool src, const EnvP<T>* p, const T* queries, int64_t n_q,
+hipError_t launch_plain(int d, bool bwd, bool src, bool lists, const EnvP<T>* p, const T* queries, int64_t n_q,
                         int64_t n_walks, int64_t w_base, uint32_t q_base,
                         const uint64_t* key_add, double* partials, double* records,
                         hipStream_t st);
@@ -31,23 +40,23 @@ hipError_t launch_reduce_pairs(const double* prod, int64_t n, double* out0, doub
 // Persistent ragged-batch kernel (FP32): grid of resident waves pulling work
 // units from *counter; refills lanes with the next walk of the unit.  src
 // selects the variant with point-source terms (any env of the batch).
-hipError_t launch_persistent(bool bwd, bool src, int grid, int block, const EnvP<float>* envs,
+hipError_t launch_persistent(bool bwd, bool src, bool lists, int grid, int block, const EnvP<float>* envs,
                              const BatchEnv* benv, int n_benv, const float* queries,
                              int64_t total_units, uint32_t key0, uint32_t key1,
                              const uint64_t* key_add, unsigned* counter, double* partials,
                              hipStream_t st);
 
-// The two variants of the above, without and with point-source terms.
-template <bool SRC>
+// The variants of the above.
+template <bool SRC, bool LISTS>
 hipError_t launch_persistent_variant(bool bwd, int grid, int block, const EnvP<float>* envs, const BatchEnv* benv,
                                      int n_benv, const float* queries, int64_t total_units, uint32_t key0,
                                      uint32_t key1, const uint64_t* key_add, unsigned* counter, double* partials,
                                      hipStream_t st);
-template <bool SRC>
+template <bool SRC, bool LISTS>
 int persistent_blocks_per_cu(bool bwd, int block);
 
 // Resident waves of the persistent kernel for a block size (occupancy x CUs).
-int persistent_resident_blocks(bool bwd, bool src, int block);
+int persistent_resident_blocks(bool bwd, bool src, bool lists, int block);
 
 // Outputs of a batched launch; one block per env; also resets *counter.
 // out_dir (optional, rows like out_grad) receives grad / |grad| formed from
@@ -85,7 +94,8 @@ struct GridBuild {
 
 // Builds the lists of m obstacles (device FP32 rows of dimension d) into
 // arrays it allocates; *cells stays null, with hipSuccess, where the lists
-// would take more than kGridEntriesMax entries.  Synchronises the device.
+// would take more than kGridEntriesMax entries or one of them more than a
+// count byte says.  Synchronises the device.
 constexpr uint32_t kGridEntriesMax = 1u << 25;
 hipError_t build_grid(const GridBuild& g, int d, bool box, const float* rows, int64_t m, GridCell** cells,
                       uint32_t** list);

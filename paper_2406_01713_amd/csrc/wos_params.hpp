@@ -91,8 +91,8 @@ constexpr int kMfmaFeat = 12;
 // holds its entries of distance (from the cell) at most kGridLev[0] edges
 // first, then those up to kGridLev[1], kGridLev[2] and the rest, and the
 // cell's header {offset, four count bytes} gives how many to read for a
-// threshold in each of the four ranges; byte kGridFull sends the walker to
-// the cluster scan instead (more entries than a byte counts).
+// threshold in each of the four ranges.  Bytes from kGridCoarse on count in
+// steps of 16 (the list repeats an entry to fill the last step).
 // Sizes: a walk simulation of the ragged batch evaluates 0.05-0.2 obstacles
 // per walk-step in d = 6, 7 at 2.6e5 cells (against 10 members of kept
 // clusters), 1.2-1.8 in the densest 4- and 5-D scenes; twice the edge at least
@@ -101,7 +101,15 @@ constexpr int kGridMin = 16;            // fewer obstacles: every one is scanned
 constexpr int kGridCellsMax = 1 << 18;  // target cells (per axis counts are rounded up)
 constexpr int kGridCellsPer = 1024;     // target cells per obstacle, below kGridCellsMax
 constexpr int kGridMaxAxis = 512;
-constexpr uint32_t kGridFull = 255;
+constexpr uint32_t kGridCoarse = 128;
+__host__ __device__ constexpr uint32_t grid_decode(uint32_t c)
+{
+    return c < kGridCoarse ? c : kGridCoarse + (c - kGridCoarse) * 16;
+}
+__host__ __device__ constexpr uint32_t grid_encode(uint32_t n)  // > 255: too many
+{
+    return n < kGridCoarse ? n : kGridCoarse + (n - kGridCoarse + 15) / 16;
+}
 constexpr double kGridLev[3] = {0.08, 0.25, 0.6};
 struct GridCell {
     uint32_t off;     // first entry in the list

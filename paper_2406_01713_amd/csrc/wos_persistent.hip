@@ -2,7 +2,8 @@
 // launch: resident waves pull work units (env, query, walk range) from a
 // device counter, and a lane whose walk ends starts the unit's next walk at
 // once (lane refill), so a wave is not held by its longest walk.  Compiled
-// once without and once with point-source terms (WOS_PERSISTENT_SRC = 0, 1).
+// without and with point-source terms (WOS_PERSISTENT_SRC = 0, 1), and with
+// steps that scan clusters or read cell lists (WOS_PERSISTENT_LISTS = 0, 1).
 #include <hip/hip_runtime.h>
 
 #include "wos_launch.hpp"
@@ -18,19 +19,32 @@ namespace {
 typedef __attribute__((address_space(4))) const BatchEnv CBatch;
 
 // One walk step of an env of dimension d on the shared 8-wide walker state.
-template <bool BWD, bool SRC>
+template <bool BWD, bool SRC, bool LISTS>
 __device__ __forceinline__ bool step_any_d(int d, cenv<float> p, Walker<float, kMaxDim>& s, uint32_t q,
                                            uint32_t k0, uint32_t k1, WalkEnd<float>& e, WorkCount& wc,
-                                           bool live, UnitStart<float>& st)
+                                           bool live, const UnitStart<float>& st)
 {
     switch (d) {
-    case 2: return walker_step<float, 2, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
-    case 3: return walker_step<float, 3, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
-    case 4: return walker_step<float, 4, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
-    case 5: return walker_step<float, 5, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
-    case 6: return walker_step<float, 6, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
-    case 7: return walker_step<float, 7, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
-    default: return walker_step<float, 8, BWD, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
+    case 2: return walker_step<float, 2, BWD, LISTS, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
+    case 3: return walker_step<float, 3, BWD, LISTS, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
+    case 4: return walker_step<float, 4, BWD, LISTS, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
+    case 5: return walker_step<float, 5, BWD, LISTS, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
+    case 6: return walker_step<float, 6, BWD, LISTS, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
+    case 7: return walker_step<float, 7, BWD, LISTS, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
+    default: return walker_step<float, 8, BWD, LISTS, kMaxDim, SRC>(p, s, q, k0, k1, e, wc, live, st);
+    }
+}
+
+__device__ __forceinline__ UnitStart<float> start_any_d(int d, cenv<float> p, const float (&xq)[kMaxDim], WorkCount& wc)
+{
+    switch (d) {
+    case 2: return unit_start<float, 2, kMaxDim>(p, xq, wc);
+    case 3: return unit_start<float, 3, kMaxDim>(p, xq, wc);
+    case 4: return unit_start<float, 4, kMaxDim>(p, xq, wc);
+    case 5: return unit_start<float, 5, kMaxDim>(p, xq, wc);
+    case 6: return unit_start<float, 6, kMaxDim>(p, xq, wc);
+    case 7: return unit_start<float, 7, kMaxDim>(p, xq, wc);
+    default: return unit_start<float, 8, kMaxDim>(p, xq, wc);
     }
 }
 
@@ -43,7 +57,7 @@ constexpr int kLdsAcc = 2 * kMaxDim;
 // One work unit: walks [w_begin, w_end) of one query, with lane refill.  The
 // walker state is 8 wide for every d, so the dimension only selects the step
 // code.  Accumulators other than the gradient ones stay in registers.
-template <bool BWD, bool SRC>
+template <bool BWD, bool SRC, bool LISTS>
 __device__ __forceinline__ void run_unit(cenv<float> p, CBatch& be, int64_t local, const float* queries,
                                          uint32_t k0, uint32_t k1, double* lds, uint32_t* pairs, double* out)
 {
@@ -85,12 +99,12 @@ __device__ __forceinline__ void run_unit(cenv<float> p, CBatch& be, int64_t loca
     int32_t base = lanes;
     const uint32_t qi = (uint32_t)ql;
     WorkCount wc(pairs);
-    UnitStart<float> st;
+    const UnitStart<float> st = start_any_d(d, p, xq, wc);
 
     while (__builtin_amdgcn_ballot_w64(active) != 0) {
         WalkEnd<float> e;
         // idle lanes (the unit has no walks left for them) step along
-        bool fin = step_any_d<BWD, SRC>(d, p, s, qi, k0, k1, e, wc, active, st);
+        bool fin = step_any_d<BWD, SRC, LISTS>(d, p, s, qi, k0, k1, e, wc, active, st);
         fin = fin && active;
         {
             if (fin) {
@@ -151,7 +165,7 @@ constexpr size_t kWaveLds = kLdsAcc * kWave * sizeof(double) + kPairLds * sizeof
 // slice per wave) and at least 4 resident waves per SIMD in every shape (the
 // second launch bound: at most 128 registers per lane).  4 waves per SIMD
 // measured faster than 3 (6 %) or 5 (18 %, spills).
-template <bool BWD, bool SRC>
+template <bool BWD, bool SRC, bool LISTS>
 __global__ void __launch_bounds__(4 * kWave, 4)
 persistent_kernel(const EnvP<float>* envs, const BatchEnv* benv, int n_benv,
                   const float* __restrict__ queries, int64_t total_units,
@@ -182,48 +196,48 @@ persistent_kernel(const EnvP<float>* envs, const BatchEnv* benv, int n_benv,
         }
         CBatch& be = B[lo];
         const cenv<float> p = (cenv<float>)(envs + be.slot);
-        run_unit<BWD, SRC>(p, be, (int64_t)u - be.unit_off, queries, k0, k1, lds, pairs,
+        run_unit<BWD, SRC, LISTS>(p, be, (int64_t)u - be.unit_off, queries, k0, k1, lds, pairs,
                            partials + (int64_t)u * kNAccBatch);
     }
 }
 
 }  // namespace
 
-template <bool BWD, bool SRC>
+template <bool BWD, bool SRC, bool LISTS>
 static hipError_t persistent_go(int grid, int block, const EnvP<float>* envs, const BatchEnv* benv, int n_benv,
                                 const float* queries, int64_t total_units, uint32_t key0, uint32_t key1,
                                 const uint64_t* key_add, unsigned* counter, double* partials, hipStream_t st)
 {
-    hipLaunchKernelGGL((persistent_kernel<BWD, SRC>), dim3(grid), dim3(block), (block / kWave) * kWaveLds, st, envs,
+    hipLaunchKernelGGL((persistent_kernel<BWD, SRC, LISTS>), dim3(grid), dim3(block), (block / kWave) * kWaveLds, st, envs,
                        benv, n_benv, queries, total_units, key0, key1, key_add, counter, partials);
     return hipGetLastError();
 }
 
-template <bool SRC>
+template <bool SRC, bool LISTS>
 hipError_t launch_persistent_variant(bool bwd, int grid, int block, const EnvP<float>* envs, const BatchEnv* benv,
                                      int n_benv, const float* queries, int64_t total_units, uint32_t key0,
                                      uint32_t key1, const uint64_t* key_add, unsigned* counter, double* partials,
                                      hipStream_t st)
 {
     if (block != kWave && block != 2 * kWave && block != 4 * kWave) return hipErrorInvalidValue;
-    return bwd ? persistent_go<true, SRC>(grid, block, envs, benv, n_benv, queries, total_units, key0, key1, key_add, counter, partials, st)
-               : persistent_go<false, SRC>(grid, block, envs, benv, n_benv, queries, total_units, key0, key1, key_add, counter, partials, st);
+    return bwd ? persistent_go<true, SRC, LISTS>(grid, block, envs, benv, n_benv, queries, total_units, key0, key1, key_add, counter, partials, st)
+               : persistent_go<false, SRC, LISTS>(grid, block, envs, benv, n_benv, queries, total_units, key0, key1, key_add, counter, partials, st);
 }
 
-template <bool SRC>
+template <bool SRC, bool LISTS>
 int persistent_blocks_per_cu(bool bwd, int block)
 {
     int per_cu = 0;
     const size_t lds = (block / kWave) * kWaveLds;
     const hipError_t e =
-        bwd ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persistent_kernel<true, SRC>, block, lds)
-            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persistent_kernel<false, SRC>, block, lds);
+        bwd ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persistent_kernel<true, SRC, LISTS>, block, lds)
+            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persistent_kernel<false, SRC, LISTS>, block, lds);
     return (e == hipSuccess && per_cu > 0) ? per_cu : 1;
 }
 
-template hipError_t launch_persistent_variant<(WOS_PERSISTENT_SRC != 0)>(
+template hipError_t launch_persistent_variant<(WOS_PERSISTENT_SRC != 0), (WOS_PERSISTENT_LISTS != 0)>(
     bool, int, int, const EnvP<float>*, const BatchEnv*, int, const float*, int64_t, uint32_t, uint32_t,
     const uint64_t*, unsigned*, double*, hipStream_t);
-template int persistent_blocks_per_cu<(WOS_PERSISTENT_SRC != 0)>(bool, int);
+template int persistent_blocks_per_cu<(WOS_PERSISTENT_SRC != 0), (WOS_PERSISTENT_LISTS != 0)>(bool, int);
 
 }  // namespace wos

@@ -24,7 +24,7 @@ constexpr int plain_waves()
     return sizeof(T) != 4 ? 1 : (D < 7 || (D == 7 && !SRC)) ? 4 : 3;
 }
 
-template <typename T, int D, bool BWD, bool SRC>
+template <typename T, int D, bool BWD, bool SRC, bool LISTS>
 __global__ void __launch_bounds__(kBlock, (plain_waves<T, D, SRC>()))
 plain_kernel(const EnvP<T>* penv, const T* __restrict__ queries, int64_t n_units, int32_t chunks,
              int64_t n_walks, int64_t w_base, uint32_t q_base, const uint64_t* __restrict__ key_add,
@@ -56,13 +56,13 @@ plain_kernel(const EnvP<T>* penv, const T* __restrict__ queries, int64_t n_units
     e.status = kTruncated;
     e.cls = kOuter;
     WorkCount wc(pair_lds[wv]);
-    UnitStart<T> st;
+    const UnitStart<T> st = unit_start<T, D, D>(p, xq, wc);
     // every lane steps until the wave's last walk ends (a finished lane runs
     // along idle), so the obstacle scans and the work tally stay wave-uniform
     bool done = !active;
     while (__builtin_amdgcn_ballot_w64(!done) != 0) {
         WalkEnd<T> ek;
-        const bool fin = walker_step<T, D, BWD, D, SRC>(p, s, q_base + (uint32_t)q, k0, k1, ek, wc, !done, st);
+        const bool fin = walker_step<T, D, BWD, LISTS, D, SRC>(p, s, q_base + (uint32_t)q, k0, k1, ek, wc, !done, st);
         if (fin && !done) {
             e = ek;
             done = true;
@@ -96,52 +96,51 @@ inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1)
 }  // namespace
 
 template <typename T, int D, bool BWD, bool SRC>
-static void plain_go(unsigned grid, const EnvP<T>* p, const T* queries, int64_t units, int32_t chunks,
+static void plain_go(bool lists, unsigned grid, const EnvP<T>* p, const T* queries, int64_t units, int32_t chunks,
                      int64_t n_walks, int64_t w_base, uint32_t q_base, const uint64_t* key_add, double* partials,
                      double* records, hipStream_t st)
 {
-    hipLaunchKernelGGL((plain_kernel<T, D, BWD, SRC>), dim3(grid), dim3(kBlock), 0, st, p, queries, units, chunks,
-                       n_walks, w_base, q_base, key_add, partials, records);
+    if (lists)
+        hipLaunchKernelGGL((plain_kernel<T, D, BWD, SRC, true>), dim3(grid), dim3(kBlock), 0, st, p, queries, units,
+                           chunks, n_walks, w_base, q_base, key_add, partials, records);
+    else
+        hipLaunchKernelGGL((plain_kernel<T, D, BWD, SRC, false>), dim3(grid), dim3(kBlock), 0, st, p, queries, units,
+                           chunks, n_walks, w_base, q_base, key_add, partials, records);
 }
 
 template <typename T, int D>
-static hipError_t plain_d(bool bwd, bool src, const EnvP<T>* p, const T* queries, int64_t n_q, int64_t n_walks,
-                          int64_t w_base, uint32_t q_base, const uint64_t* key_add, double* partials,
+static hipError_t plain_d(bool bwd, bool src, bool lists, const EnvP<T>* p, const T* queries, int64_t n_q,
+                          int64_t n_walks, int64_t w_base, uint32_t q_base, const uint64_t* key_add, double* partials,
                           double* records, hipStream_t st)
 {
     const int32_t chunks = (int32_t)((n_walks + kWave - 1) / kWave);
     const int64_t units = n_q * chunks;
     if (units == 0) return hipSuccess;
     const unsigned grid = blocks_for(units, kBlock / kWave);
-    if (bwd && src)
-        plain_go<T, D, true, true>(grid, p, queries, units, chunks, n_walks, w_base, q_base, key_add, partials, records, st);
-    else if (bwd)
-        plain_go<T, D, true, false>(grid, p, queries, units, chunks, n_walks, w_base, q_base, key_add, partials, records, st);
-    else if (src)
-        plain_go<T, D, false, true>(grid, p, queries, units, chunks, n_walks, w_base, q_base, key_add, partials, records, st);
-    else
-        plain_go<T, D, false, false>(grid, p, queries, units, chunks, n_walks, w_base, q_base, key_add, partials, records, st);
+    auto* go = bwd ? (src ? plain_go<T, D, true, true> : plain_go<T, D, true, false>)
+                   : (src ? plain_go<T, D, false, true> : plain_go<T, D, false, false>);
+    go(lists, grid, p, queries, units, chunks, n_walks, w_base, q_base, key_add, partials, records, st);
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_plain(int d, bool bwd, bool src, const EnvP<T>* p, const T* queries, int64_t n_q,
+hipError_t launch_plain(int d, bool bwd, bool src, bool lists, const EnvP<T>* p, const T* queries, int64_t n_q,
                         int64_t n_walks, int64_t w_base, uint32_t q_base, const uint64_t* key_add,
                         double* partials, double* records, hipStream_t st)
 {
     switch (d) {
-    case 2: return plain_d<T, 2>(bwd, src, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
-    case 3: return plain_d<T, 3>(bwd, src, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
-    case 4: return plain_d<T, 4>(bwd, src, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
-    case 5: return plain_d<T, 5>(bwd, src, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
-    case 6: return plain_d<T, 6>(bwd, src, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
-    case 7: return plain_d<T, 7>(bwd, src, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
-    case 8: return plain_d<T, 8>(bwd, src, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
+    case 2: return plain_d<T, 2>(bwd, src, lists, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
+    case 3: return plain_d<T, 3>(bwd, src, lists, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
+    case 4: return plain_d<T, 4>(bwd, src, lists, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
+    case 5: return plain_d<T, 5>(bwd, src, lists, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
+    case 6: return plain_d<T, 6>(bwd, src, lists, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
+    case 7: return plain_d<T, 7>(bwd, src, lists, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
+    case 8: return plain_d<T, 8>(bwd, src, lists, p, queries, n_q, n_walks, w_base, q_base, key_add, partials, records, st);
     default: return hipErrorInvalidValue;
     }
 }
 
-template hipError_t launch_plain<WOS_PLAIN_T>(int, bool, bool, const EnvP<WOS_PLAIN_T>*, const WOS_PLAIN_T*, int64_t,
+template hipError_t launch_plain<WOS_PLAIN_T>(int, bool, bool, bool, const EnvP<WOS_PLAIN_T>*, const WOS_PLAIN_T*, int64_t,
                                               int64_t, int64_t, uint32_t, const uint64_t*, double*, double*,
                                               hipStream_t);
 

@@ -1,0 +1,114 @@
+"""Cell lists of the obstacle scan: walks that look obstacles up in the lists of
+their cell are bitwise those of a scan of every obstacle, in scenes where the
+cell table, its clamping, its count ranges or its fallbacks come into play.
+Equality is exact: a list may only leave out obstacles that are not nearest."""
+import numpy as np
+import pytest
+
+from paper_2406_01713_amd import scenes as S
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch  # noqa: F401  (the HIP runtime the library binds to)
+    from paper_2406_01713_amd import binding
+    return binding
+
+
+def _base(d, rng, outer, m_sph, m_box, rad):
+    s = S._empty(d)
+    if outer["kind"] == "box":
+        lo, hi = np.asarray(outer["lo"], float), np.asarray(outer["hi"], float)
+    else:
+        lo, hi = outer["c"] - outer["r"], outer["c"] + outer["r"]
+    s.update(d=d, sph_c=rng.uniform(lo, hi, size=(m_sph, d)), sph_r=rng.uniform(*rad, size=m_sph), goal_c=None,
+             goal_r=None, outer=outer, bdata=S._bdata(0, d, g_goal=0.0, g_obs=1.0, g_outer=0.25), sigma=0.5,
+             eps=1e-3 * float(np.min(hi - lo)), n_walks=200, seed=11)
+    if m_box:
+        s["box_c"] = rng.uniform(lo, hi, size=(m_box, d))
+        s["box_h"] = rng.uniform(0.0, rad[1], size=(m_box, d))
+    # inside points, one on the boundary's corner region and one outside (degenerate)
+    q = 0.5 * (lo + hi) + 0.25 * rng.uniform(lo - hi, hi - lo, size=(6, d))  # inside the ball too
+    q[4] = hi - 1e-6 * (hi - lo)
+    q[5] = hi + 0.1 * (hi - lo)
+    s["queries"] = q
+    return s
+
+
+def _box(lo, hi):
+    return {"kind": "box", "lo": np.asarray(lo, float), "hi": np.asarray(hi, float)}
+
+
+def _scene(name):
+    rng = np.random.default_rng(sum(map(ord, name)))
+    if name == "flat":  # very unequal edges, far from the origin
+        return _base(3, rng, _box([900.0, -2.0, 0.0], [1000.0, 2.0, 0.5]), 300, 0, (0.02, 0.3))
+    if name == "ball":  # cells outside the outer ball
+        return _base(4, rng, {"kind": "ball", "c": np.array([1.0, -1.0, 0.0, 2.0]), "r": 2.0}, 120, 0, (0.05, 0.2))
+    if name == "mixed":  # both kinds in lists
+        return _base(5, rng, _box([-1] * 5, [1] * 5), 90, 150, (0.02, 0.15))
+    if name == "few":  # lists below the cluster size, boxes scanned
+        return _base(2, rng, _box([-1, -1], [1, 1]), 17, 9, (0.02, 0.2))
+    if name == "d8":
+        return _base(8, rng, _box([-2] * 8, [2] * 8), 400, 70, (0.2, 0.9))
+    if name in ("ring600", "ring5000"):  # equally near obstacles: coarse counts, and too many for a list
+        s = _base(2, rng, _box([-2, -2], [2, 2]), int(name[4:]), 0, (0.0, 0.0))
+        t = np.linspace(0, 2 * np.pi, len(s["sph_r"]), endpoint=False)
+        s["sph_c"] = 0.5 * np.stack([np.cos(t), np.sin(t)], 1)
+        s["queries"][0] = 0.0
+        return s
+    if name == "extruded":
+        s = _base(4, rng, _box([-2] * 4, [2] * 4), 150, 0, (0.02, 0.2))
+        s["geom_d"] = 2
+        s["sph_c"][:, 2:] = 0.0
+        return s
+    raise ValueError(name)
+
+
+def _estimate(B, s, fp64, **kw):
+    import torch
+    dt = torch.float64 if fp64 else torch.float32
+    x = torch.tensor(s["queries"], dtype=dt, device="cuda")
+    Q, d = x.shape
+    u, g = torch.empty(Q, dtype=dt, device="cuda"), torch.empty(Q, d, dtype=dt, device="cuda")
+    st = torch.empty(Q, d + 4, dtype=torch.float64, device="cuda")
+    dom = B.Domain(s)
+    B.wos_estimate(dom, x, s["n_walks"], s["sigma"], s["eps"], s["seed"], u, g, st, opt=B.options(fp64, **kw))
+    rec = B.wos_debug_walks(dom, s["queries"][0], 0, 0, 128, s["sigma"], s["eps"], s["seed"], opt=B.options(fp64, **kw))
+    return [t.cpu().numpy() for t in (u, g, st)] + [rec]
+
+
+NAMES = ["flat", "ball", "mixed", "few", "d8", "ring600", "ring5000", "extruded"]
+
+
+@pytest.mark.parametrize("name", NAMES)
+@pytest.mark.parametrize("fp64", [False, True])
+def test_lists_give_the_full_scans_walks(B, name, fp64):
+    s = _scene(name)
+    a, b = _estimate(B, s, fp64), _estimate(B, s, fp64, full_scan=True)
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y, equal_nan=True)
+    assert np.any(a[0] > 0.25)  # some walks end on obstacles
+
+
+def test_lists_give_the_full_scans_batch(B):
+    """The same in the persistent kernel, without the work statistics (with
+    them, environments below 64 obstacles scan all of them)."""
+    import torch
+    envs = [_scene(n) for n in NAMES if n != "ring5000"]
+    for batch in (envs, envs + [_scene("ring5000")]):  # the second also holds an environment without lists
+        off = np.cumsum([0] + [len(e["queries"]) for e in batch])
+        q = np.zeros((off[-1], 8), np.float32)
+        for e, o in zip(batch, off):
+            q[o:o + len(e["queries"]), :e["d"]] = e["queries"]
+        x = torch.tensor(q, device="cuda")
+        doms = [B.Domain(e) for e in batch]
+        got = []
+        for kw in ({}, dict(full_scan=True)):
+            u, g = torch.empty(len(q), device="cuda"), torch.empty(len(q), 8, device="cuda")
+            B.wos_estimate_batch(doms, x, off, [e["sigma"] for e in batch], [e["eps"] for e in batch], 200, 11, u, g,
+                                 opt=B.options(**kw))
+            got.append((u.cpu().numpy(), g.cpu().numpy()))
+        assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
