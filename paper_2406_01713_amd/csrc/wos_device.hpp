@@ -992,10 +992,42 @@ __device__ __forceinline__ T distance(cenv<T> p, const T (&x)[D], int& cls, Work
     return nearest_of<T>(dg, ds, db, da, dout, cls);
 }
 
+// First obstacle (in caller order) of one kind nearest to x, recovered by
+// rescanning with the same distance code: the list of x's cell where the walk
+// reads lists, which holds every nearest obstacle, else all of them.  (With
+// 1500 spheres and plane-wave data a rescan of all took most of a 5-D launch:
+// about 28000 vector instructions per absorbed walk, against 62 steps of 600.)
+template <typename T, int D, bool BOX, bool LISTS>
+__device__ __forceinline__ int nearest_index(cenv<T> p, const T (&x)[D])
+{
+    constexpr int S = BOX ? box_stride(D) : sph_stride(D);
+    cptr<T> tab = to_const(BOX ? p->box : p->sph);
+    int jm = 0;
+    T best = Math<T>::inf();
+    const GridCell* cells = LISTS ? (BOX ? p->box_cells : p->sph_cells) : nullptr;
+    if (LISTS && cells) {
+        const GridCell h = cells[grid_cell<T, D>(p, x)];
+        const uint32_t n = grid_decode(h.counts >> 24);
+        cptr<uint32_t> list = to_const(BOX ? p->box_list : p->sph_list) + h.off;
+        for (uint32_t i = 0; i < n; ++i) {
+            const int j = (int)list[i];
+            cptr<T> r = tab + (int64_t)j * S;
+            const T dj = BOX ? box_dist<T, D>(x, r) : sphere_dist<T, D>(x, r);
+            if (dj < best || (dj == best && j < jm)) { best = dj; jm = j; }
+        }
+        return jm;
+    }
+    const int n = BOX ? p->n_box : p->n_sph;
+    for (int j = 0; j < n; ++j) {
+        const T dj = BOX ? box_dist<T, D>(x, tab + j * S) : sphere_dist<T, D>(x, tab + j * S);
+        if (dj < best) { best = dj; jm = j; }
+    }
+    return jm;
+}
+
 // Closest boundary point xbar on the absorbing component (Fig. 2), in the
-// coordinates the component depends on.  Sphere and box indices are
-// recovered by rescanning with the same distance code.
-template <typename T, int D>
+// coordinates the component depends on.
+template <typename T, int D, bool LISTS>
 __device__ __forceinline__ void closest_point_in(cenv<T> p, const T (&x)[D], int cls, T (&xb)[D])
 {
 #pragma unroll
@@ -1019,12 +1051,7 @@ __device__ __forceinline__ void closest_point_in(cenv<T> p, const T (&x)[D], int
     if (cls == kBox) {
         constexpr int S = box_stride(D);
         cptr<T> tab = to_const(p->box);
-        int jm = 0;
-        T best = Math<T>::inf();
-        for (int j = 0; j < p->n_box; ++j) {
-            const T dj = box_dist<T, D>(x, tab + j * S);
-            if (dj < best) { best = dj; jm = j; }
-        }
+        const int jm = nearest_index<T, D, true, LISTS>(p, x);
         cptr<T> row = tab + jm * S;
         bool inside = true;
 #pragma unroll
@@ -1050,12 +1077,7 @@ __device__ __forceinline__ void closest_point_in(cenv<T> p, const T (&x)[D], int
     if (cls == kSphere) {
         constexpr int S = sph_stride(D);
         cptr<T> tab = to_const(p->sph);
-        int jm = 0;
-        T best = Math<T>::inf();
-        for (int j = 0; j < p->n_sph; ++j) {
-            const T dj = sphere_dist<T, D>(x, tab + j * S);
-            if (dj < best) { best = dj; jm = j; }
-        }
+        const int jm = nearest_index<T, D, false, LISTS>(p, x);
 #pragma unroll
         for (int i = 0; i < D; ++i) c[i] = tab[jm * S + i];
         r = tab[jm * S + D];
@@ -1085,7 +1107,7 @@ __device__ __forceinline__ void closest_point_in(cenv<T> p, const T (&x)[D], int
 // Closest boundary point of an extruded component (obstacle or outer
 // boundary with geom_d < d): the projection acts on the leading geom_d
 // coordinates and keeps the others.
-template <typename T, int D>
+template <typename T, int D, bool LISTS>
 __device__ __forceinline__ void closest_point(cenv<T> p, const T (&x)[D], int cls, T (&xb)[D])
 {
     if (cls == kArm) {  // the arm bound names no boundary point (class data only)
@@ -1097,19 +1119,19 @@ __device__ __forceinline__ void closest_point(cenv<T> p, const T (&x)[D], int cl
     T xg[D];
 #pragma unroll
     for (int i = 0; i < D; ++i) xg[i] = (i < k) ? x[i] : T(0);
-    closest_point_in<T, D>(p, xg, cls, xb);
+    closest_point_in<T, D, LISTS>(p, xg, cls, xb);
 #pragma unroll
     for (int i = 0; i < D; ++i)
         if (i >= k) xb[i] = x[i];
 }
 
 // Boundary data g at the closest point of the absorbing component.
-template <typename T, int D>
+template <typename T, int D, bool LISTS>
 __device__ __forceinline__ T boundary_value(cenv<T> p, const T (&x)[D], int cls)
 {
     if (p->mode == 0) return cls == kGoal ? p->g_goal : (cls == kOuter ? p->g_outer : p->g_obs);
     T xb[D];
-    closest_point<T, D>(p, x, cls, xb);
+    closest_point<T, D, LISTS>(p, x, cls, xb);
     T s = 0;
 #pragma unroll
     for (int i = 0; i < D; ++i) s = Math<T>::fma(p->ak[i], xb[i], s);
@@ -1241,6 +1263,7 @@ __device__ __noinline__ SourceTerm<T> ball_green(cenv<T> p, T r, T R)
 template <typename T>
 struct UnitStart {
     T R, gfac;
+    T g;  // boundary value there, for a point within eps of the boundary
     int cls;
 };
 
@@ -1335,6 +1358,8 @@ __device__ __forceinline__ UnitStart<T> unit_start(cenv<T> p, const T (&xq)[DA],
     st.R = uniform_of(nearest_of<T>(dg, ds, db, da, dout, cls));
     st.cls = __builtin_amdgcn_readfirstlane(cls);
     st.gfac = uniform_of(T(D) * Math<T>::rcp(st.R * horner<T>(p->cC1, p->nt_C1, p->qsigma * (st.R * st.R))));
+    st.g = T(0);
+    if (st.R < p->eps) st.g = uniform_of(boundary_value<T, D, false>(p, x, st.cls));
     return st;
 }
 
@@ -1456,8 +1481,9 @@ __device__ __forceinline__ bool walker_step(cenv<T> p0, Walker<T, DA>& s, uint32
     // it is a threshold the scans may cull against without changing R or cls
     if (kBound) s.rb = Math<T>::fma(R, T(2.001953125), p->rb_abs);  // 2 (1 + 2^-10)
     if (R < p->eps) {
-        const T g = boundary_value<T, D>(p, x, cls);
         const bool first = (k == 0);
+        T g = st.g;
+        if (!first) g = boundary_value<T, D, LISTS>(p, x, cls);
         e.steps = k + 1;
         e.cls = cls;
         e.status = first ? kDegenerate : kAbsorbed;

@@ -93,6 +93,21 @@ def test_lists_give_the_full_scans_walks(B, name, fp64):
     assert np.any(a[0] > 0.25)  # some walks end on obstacles
 
 
+@pytest.mark.parametrize("name", ["mixed", "ring600", "d8"])
+@pytest.mark.parametrize("fp64", [False, True])
+def test_lists_name_the_full_scans_obstacle(B, name, fp64):
+    """Plane-wave data are read at the closest point of the absorbing obstacle:
+    the one found in the cell's list is the full scan's (also on ties, and for
+    the query inside an obstacle or outside the box)."""
+    s = _scene(name)
+    s["sigma"] = 0.5
+    s = S.with_bdata(s, 2, ak=S.plane_wave_k(s["d"], 0.5))
+    s["queries"][3] = s["sph_c"][0] + (0.0 if name == "ring600" else 1e-3)
+    a, b = _estimate(B, s, fp64), _estimate(B, s, fp64, full_scan=True)
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y, equal_nan=True)
+
+
 def test_lists_give_the_full_scans_batch(B):
     """The same in the persistent kernel, without the work statistics (with
     them, environments below 64 obstacles scan all of them)."""
