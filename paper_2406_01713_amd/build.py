@@ -25,7 +25,8 @@ ARCH = os.environ.get("WOS_OFFLOAD_ARCH", "gfx950")
 # variant, so their long compilations run side by side
 SOURCES = [*(("wos_persistent.hip", [f"-DWOS_PERSISTENT_SRC={s}", f"-DWOS_PERSISTENT_LISTS={l}"])
              for s in (0, 1) for l in (0, 1)),
-           ("wos_plain.hip", ["-DWOS_PLAIN_T=float"]), ("wos_plain.hip", ["-DWOS_PLAIN_T=double"]),
+           *(("wos_plain.hip", [f"-DWOS_PLAIN_T={t}", f"-DWOS_PLAIN_LOW={h}"])
+             for t in ("float", "double") for h in (0, 1)),
            ("wos_kernels.hip", []), ("wos_grid.hip", []), ("wos_api.cpp", []), ("wos_microbench.hip", [])]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-x", "hip",
          *os.environ.get("WOS_EXTRA_FLAGS", "").split(),

@@ -822,6 +822,7 @@ void mix_key(char (&k)[48], const wos_domain* const* envs, const int64_t* q_off,
 
 struct BatchLayout {
     int64_t total_units = 0;
+    int max_d = 2;
     int grid = 0;
     int block = 256;
 };
@@ -843,6 +844,7 @@ void plan_batch(const wos_domain* const* envs, const int64_t* q_off, int n_envs,
         const int64_t q = q_off[e + 1] - q_off[e];
         sumQW += q * n_walks[e];
         maxW = std::max(maxW, n_walks[e]);
+        L.max_d = std::max(L.max_d, envs[e]->d);
         const double c = unit_cost(envs[e], n_walks[e]) * (double)q;
         if (c > heavy) {
             heavy = c;
@@ -863,7 +865,7 @@ void plan_batch(const wos_domain* const* envs, const int64_t* q_off, int n_envs,
     // scans of those walks (the pair rounds spread over all 64 lanes)
     const int64_t lanes = kWave / t.lanes_per_walker;
     const int block = t.waves_per_block * kWave;
-    const int resident_blocks = persistent_resident_blocks(true, src, lists, block);
+    const int resident_blocks = persistent_resident_blocks(true, src, lists, L.max_d, block);
     L.block = block;
     L.grid = std::max(1, resident_blocks * t.grid_mult);
     const int64_t waves = (int64_t)L.grid * (block / kWave);
@@ -1072,7 +1074,7 @@ int run_batch(const wos_domain* const* envs, int n_envs, const float* queries, c
     const BatchEnv* d_benv = (const BatchEnv*)(d_tab + env_bytes);
     // the counter starts at 0 (a fill kernel: no memset node if the caller captures)
     WOS_HIP(launch_fill_u32(counter, 1, 0u, st), "fill");
-    WOS_HIP(launch_persistent(bwd, src, lists, L.grid, L.block, d_env, d_benv, n_envs, queries, L.total_units,
+    WOS_HIP(launch_persistent(bwd, src, lists, L.grid, L.block, d_env, d_benv, n_envs, L.max_d, queries, L.total_units,
                               (uint32_t)seed, (uint32_t)(seed >> 32), nullptr, counter, partials, st),
             "persistent walk kernel");
     WOS_HIP(launch_finalize_batch(bwd, d_benv, n_envs, partials, grad_u, out_u, out_grad, kBatchStride,
@@ -1562,6 +1564,19 @@ int wos_debug_cluster_boxes(int d, const wos_spheres* spheres, const wos_boxes* 
     return WOS_OK;
 }
 
+// Walks per wave of the plain kernel.  Up to one walk per lane of the 4096
+// resident waves (4 per SIMD), one per lane: every walk runs at once.  Above,
+// one range per resident wave (lanes refill) until a range holds 256 walks,
+// then ranges of 256 until each wave takes four, then a quarter of a wave's
+// share.
+static int32_t plain_range(int64_t Q, int64_t n_walks)
+{
+    const double per = (double)std::max<int64_t>(Q, 1) * (double)n_walks / 4096.0;
+    const double want = std::max(0.25 * per, std::min(256.0, per));
+    const int64_t r = ((int64_t)std::min(std::ceil(want), 1e9) + kWave - 1) / kWave * kWave;
+    return (int32_t)std::max<int64_t>(kWave, std::min<int64_t>(r, (n_walks + kWave - 1) / kWave * kWave));
+}
+
 static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, int64_t n_walks, double sigma,
                          double eps, uint64_t seed, void* out_u, void* out_grad, double* out_stats,
                          const void* grad_u, void* out_dx, double* out_dsigma, double* out_dg, double* out_dq,
@@ -1585,7 +1600,8 @@ static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, in
     if (bwd && D->has_src && !(sigma > 0.0))
         return fail(WOS_ENOTSUP, "the sigma derivative of a point source is provided for sigma > 0 only");
     const int d = D->d;
-    const int32_t chunks = (int32_t)((n_walks + kWave - 1) / kWave);
+    const int32_t wpu = plain_range(Q, n_walks);
+    const int32_t chunks = (int32_t)((n_walks + wpu - 1) / wpu);
     Scratch S(st);
     double* partials = nullptr;
     double* prod = nullptr;
@@ -1609,8 +1625,7 @@ static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, in
         }
         EnvP<double>* pd;
         if ((rc = S.get(&pd, 1)) || (rc = upload(pd, &p, sizeof(p), st))) return rc;
-        WOS_HIP(launch_plain<double>(d, bwd, D->has_src, lists_ok(p), pd, (const double*)queries, Q, n_walks, 0, 0, nullptr, partials,
-                                     nullptr, st),
+        WOS_HIP(launch_plain<double>(d, bwd, D->has_src, lists_ok(p), pd, (const double*)queries, Q, n_walks, wpu, 0, 0, partials, nullptr, st),
                 "plain walk kernel");
         WOS_HIP(launch_finalize_plain<double>(d, bwd, partials, Q, chunks, n_walks, uo, (double*)out_grad, out_stats,
                                               (const double*)grad_u, (double*)out_dx, out_dq, prod, st),
@@ -1633,8 +1648,7 @@ static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, in
         }
         EnvP<float>* pd;
         if ((rc = S.get(&pd, 1)) || (rc = upload(pd, &p, sizeof(p), st))) return rc;
-        WOS_HIP(launch_plain<float>(d, bwd, D->has_src, lists_ok(p), pd, (const float*)queries, Q, n_walks, 0, 0, nullptr, partials,
-                                    nullptr, st),
+        WOS_HIP(launch_plain<float>(d, bwd, D->has_src, lists_ok(p), pd, (const float*)queries, Q, n_walks, wpu, 0, 0, partials, nullptr, st),
                 "plain walk kernel");
         if (o.flags & WOS_OUT_FP64)  // forward only: the FP64 sums written without rounding to FP32
             WOS_HIP(launch_finalize_plain<double>(d, false, partials, Q, chunks, n_walks, (double*)out_u,
@@ -1712,8 +1726,7 @@ int wos_debug_walks(const wos_domain* D, const double* query, uint32_t q_index, 
             if (!rc && e == hipSuccess) e = hipMalloc(&pd, sizeof(p));
             if (!rc && e == hipSuccess) e = hipMemcpy(pd, &p, sizeof(p), hipMemcpyHostToDevice);
             if (!rc && e == hipSuccess)
-                e = launch_plain<double>(d, true, D->has_src, lists_ok(p), (const EnvP<double>*)pd, (const double*)dq, 1, n, w0, q_index, nullptr,
-                                         part, rec, nullptr);
+                e = launch_plain<double>(d, true, D->has_src, lists_ok(p), (const EnvP<double>*)pd, (const double*)dq, 1, n, kWave, w0, q_index, part, rec, nullptr);
             if (e == hipSuccess) e = hipDeviceSynchronize();
             (void)hipFree(pd);
         } else {
@@ -1726,8 +1739,7 @@ int wos_debug_walks(const wos_domain* D, const double* query, uint32_t q_index, 
             if (!rc && e == hipSuccess) e = hipMalloc(&pd, sizeof(p));
             if (!rc && e == hipSuccess) e = hipMemcpy(pd, &p, sizeof(p), hipMemcpyHostToDevice);
             if (!rc && e == hipSuccess)
-                e = launch_plain<float>(d, true, D->has_src, lists_ok(p), (const EnvP<float>*)pd, (const float*)dq, 1, n, w0, q_index, nullptr,
-                                        part, rec, nullptr);
+                e = launch_plain<float>(d, true, D->has_src, lists_ok(p), (const EnvP<float>*)pd, (const float*)dq, 1, n, kWave, w0, q_index, part, rec, nullptr);
             if (e == hipSuccess) e = hipDeviceSynchronize();
             (void)hipFree(pd);
         }
@@ -1861,7 +1873,7 @@ int wos_plan_create(const wos_domain* D, float* x, int64_t n_starts, int64_t n_w
     // capture [fused forward + backward walks, finalize, update]
     e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        hipError_t e1 = launch_persistent(true, D->has_src, lists_ok(P->henv), L.grid, L.block, P->env, P->benv, 1, x, L.total_units,
+        hipError_t e1 = launch_persistent(true, D->has_src, lists_ok(P->henv), L.grid, L.block, P->env, P->benv, 1, L.max_d, x, L.total_units,
                                           P->henv.key0, P->henv.key1, P->step, P->counter, P->partials, st);
         hipError_t e2 = launch_finalize_batch(true, P->benv, 1, P->partials, P->ubar, P->u, P->grad,
                                               kBatchStride, nullptr, P->dx, P->dsig, P->dg, P->dir, P->counter, st);

@@ -911,34 +911,37 @@ __device__ __forceinline__ T goal_dist(cenv<T> p, const T (&x)[D])
     return Math<T>::sqrt(acc) - p->goal_r;
 }
 
-// R and its component (the first attaining it in the order goal, spheres,
-// boxes, arm, outer) from the components' distances.
+// Distances to the components of the boundary; +inf where there is none or
+// where the scan left the component out.
 template <typename T>
-__device__ __forceinline__ T nearest_of(T dg, T ds, T db, T da, T dout, int& cls)
-{
-    const T ao = Math<T>::min(da, dout);
-    const T bo = Math<T>::min(db, ao);
-    const T rest = Math<T>::min(ds, bo);
-    cls = (dg <= rest) ? kGoal : (ds <= bo) ? kSphere : (db <= ao) ? kBox : (da <= dout) ? kArm : kOuter;
-    return Math<T>::min(dg, rest);
-}
+struct Near {
+    T dg, ds, db, da, dout;  // goal, spheres, boxes, arm, outer boundary
+    __device__ __forceinline__ T R() const
+    {
+        return Math<T>::min(dg, Math<T>::min(ds, Math<T>::min(db, Math<T>::min(da, dout))));
+    }
+    // the first component attaining R in the order above
+    __device__ __forceinline__ int cls() const
+    {
+        const T ao = Math<T>::min(da, dout);
+        const T bo = Math<T>::min(db, ao);
+        return (dg <= Math<T>::min(ds, bo)) ? kGoal : (ds <= bo) ? kSphere : (db <= ao) ? kBox
+               : (da <= dout) ? kArm : kOuter;
+    }
+};
 
-// R = distance to the boundary, cls its component, for the lanes of live.  The
-// goal and outer distances come first and bound the box scan, whose result
+// Distances to the boundary's components for the lanes of live.  The goal and outer distances come first and bound the box scan, whose result
 // then bounds the sphere scan; ub, any value at or above the R a scan of every
 // obstacle computes (the walker's bound from its previous step, +inf when it
 // has none), bounds both scans as well.  Obstacles that the culling or a cell
 // list leaves out never attain R, so R and cls are as a scan of every
 // obstacle gives them.
 //
-// LISTS: environments whose obstacles are in cell lists (lanes of look read
-// them; their points must lie inside the outer boundary up to rounding) or
-// few enough to scan all; otherwise the cluster scan.  between() runs after
-// the list headers' loads are issued and before they are used: work that does
-// not depend on the distance hides their latency there.
-template <typename T, int D, bool LISTS, typename F>
-__device__ __forceinline__ T distance(cenv<T> p, const T (&x)[D], int& cls, WorkCount& wc, bool live, bool look,
-                                      T ub, F&& between)
+// LISTS: environments whose obstacles are in cell lists (points must lie
+// inside the outer boundary up to rounding) or few enough to scan all;
+// otherwise the cluster scan.
+template <typename T, int D, bool LISTS>
+__device__ __forceinline__ Near<T> distance(cenv<T> p, const T (&x)[D], WorkCount& wc, bool live, T ub)
 {
     // extruded geometry: obstacles and the outer boundary see the leading
     // geom_d coordinates only (their stored centres are zero beyond them)
@@ -953,7 +956,6 @@ __device__ __forceinline__ T distance(cenv<T> p, const T (&x)[D], int& cls, Work
         if (cs) hs = cs[cell];
         if (cb) hb = cb[cell];
     }
-    between();
     p = fresh(p);
     const T dg = goal_dist<T, D>(p, x);
     const T dout = outer_dist<T, D>(p, xg);
@@ -965,7 +967,7 @@ __device__ __forceinline__ T distance(cenv<T> p, const T (&x)[D], int& cls, Work
     uint32_t nb = 0, ns = 0;  // distances per live lane (wave-uniform scans)
     if (LISTS) {
         if (cb) {
-            const uint32_t n = look ? grid_count<T>(fresh(p), hb.counts, tg) : 0u;
+            const uint32_t n = live ? grid_count<T>(fresh(p), hb.counts, tg) : 0u;
             db = cell_min<T, D, true>(to_const(fresh(p)->box_list), to_const(fresh(p)->box), hb.off, n, xg, wc.box,
                                       wc.pairs);
         } else if (p->n_box) {
@@ -973,7 +975,7 @@ __device__ __forceinline__ T distance(cenv<T> p, const T (&x)[D], int& cls, Work
             db = boxes_min<T, D>(to_const(p->box), (int)nb, xg);
         }
         if (cs) {
-            const uint32_t n = look ? grid_count<T>(fresh(p), hs.counts, Math<T>::min(tg, db)) : 0u;
+            const uint32_t n = live ? grid_count<T>(fresh(p), hs.counts, Math<T>::min(tg, db)) : 0u;
             ds = cell_min<T, D, false>(to_const(fresh(p)->sph_list), to_const(fresh(p)->sph), hs.off, n, xg, wc.sph,
                                        wc.pairs);
         } else if (p->n_sph) {
@@ -989,7 +991,7 @@ __device__ __forceinline__ T distance(cenv<T> p, const T (&x)[D], int& cls, Work
         wc.sph += lanes * ns;
         wc.box += lanes * nb;
     }
-    return nearest_of<T>(dg, ds, db, da, dout, cls);
+    return Near<T>{dg, ds, db, da, dout};
 }
 
 // First obstacle (in caller order) of one kind nearest to x, recovered by
@@ -1171,38 +1173,84 @@ __device__ __forceinline__ T horner(const C& c, int nt, T y)
 // at sigma = 0 both take their Laplace forms.
 // ------------------------------------------------------------------------
 
-// K_nu(z) and K_{nu+1}(z), z > 0, together: the trapezoidal rule on the
-// integral of exp(-z cosh t) cosh(nu t) over t >= 0, with step
-// min(1/4, 1/(2 sqrt(z))) (the integrand's width near 0 shrinks like
-// 1/sqrt(z)), summed until the terms are past their peak and below the
-// precision's rounding.  cosh(nu t) exp(-z cosh t) is formed as
+// K_nu and K_{nu+1}, nu = d/2 - 1, at two arguments z > 0 (+inf otherwise).
+//
+// Odd d: half-integer orders, elementary: K_{1/2}(z) = sqrt(pi / (2 z)) e^-z,
+// K_{-1/2} = K_{1/2}, and upward by K_{m+1} = K_{m-1} + (2 m / z) K_m (all
+// terms positive, so stable).
+//
+// Even d: the trapezoidal rule on the integral of exp(-z cosh t) cosh(nu t)
+// over t >= 0, with step min(1/4, 1/(2 sqrt(z))) (the integrand's width near 0
+// shrinks like 1/sqrt(z)), summed until the terms are past their peak and below
+// the precision's rounding.  cosh(nu t) exp(-z cosh t) is formed as
 // (exp(a + nu t) + exp(a - nu t)) / 2, a = -z cosh t, with the exponent capped
-// so that a source closer than about 1e-9 cannot overflow FP32.
-template <typename T>
-__device__ __forceinline__ void bessel_k_pair(T nu, T z, T& k0, T& k1)
+// so that a source closer than about 1e-9 cannot overflow FP32.  The rule is
+// a serial chain of about 35 nodes whose latency is most of a source step, so
+// both arguments and two nodes of each go through it side by side.
+template <typename T, int D>
+__device__ __forceinline__ void bessel_k_pairs(T za, T zb, T (&ka)[2], T (&kb)[2])
 {
-    if (!(z > T(0))) {
-        k0 = k1 = Math<T>::inf();
-        return;
+    const bool oka = za > T(0), okb = zb > T(0);
+    if (D % 2 == 1) {
+        auto half = [](T z, T (&k)[2]) {
+            z = Math<T>::max(z, sizeof(T) == 4 ? T(1e-9) : T(1e-60));  // finite in the precision's range
+            const T iz = Math<T>::rcp(z);
+            T lo = Math<T>::sqrt(T(1.57079632679489661923) * iz) * Math<T>::exp(-z);
+            T hi = lo;  // orders -1/2, 1/2
+            T m = T(0.5);
+#pragma unroll
+            for (int i = 0; i < (D - 1) / 2; ++i) {
+                const T up = Math<T>::fma(T(2) * m * iz, hi, lo);
+                lo = hi;
+                hi = up;
+                m += T(1);
+            }
+            k[0] = lo;
+            k[1] = hi;
+        };
+        half(za, ka);
+        half(zb, kb);
+    } else {
+        const T nu = T(0.5 * D - 1.0);
+        const T tol = sizeof(T) == 4 ? T(1e-8) : T(1e-17);
+        const T cap = T(80);
+        const T z[2] = {oka ? za : T(1), okb ? zb : T(1)};
+        T h[2], s[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            h[i] = Math<T>::min(T(0.25), T(0.5) * Math<T>::rsqrt(z[i]));
+            s[i][0] = s[i][1] = T(0.5) * Math<T>::exp(-z[i]);
+        }
+        bool more = true;
+        for (int j = 1; more && j < 4096; j += 2) {
+            more = false;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                T u[2][2], et[2], iet[2];
+#pragma unroll
+                for (int n = 0; n < 2; ++n) {
+                    const T t = T(j + n) * h[i];
+                    et[n] = Math<T>::exp(t);
+                    iet[n] = Math<T>::rcp(et[n]);
+                    const T a = -z[i] * T(0.5) * (et[n] + iet[n]);
+#pragma unroll
+                    for (int o = 0; o < 2; ++o) {
+                        const T nt = (nu + T(o)) * t;
+                        u[n][o] = T(0.5) * (Math<T>::exp(Math<T>::min(a + nt, cap)) + Math<T>::exp(a - nt));
+                    }
+                }
+                s[i][0] += u[0][0] + u[1][0];
+                s[i][1] += u[0][1] + u[1][1];
+                more = more || !(z[i] * T(0.5) * (et[1] - iet[1]) > nu + T(1) && u[1][1] <= tol * s[i][1]);
+            }
+        }
+        ka[0] = h[0] * s[0][0];
+        ka[1] = h[0] * s[0][1];
+        kb[0] = h[1] * s[1][0];
+        kb[1] = h[1] * s[1][1];
     }
-    const T tol = sizeof(T) == 4 ? T(1e-8) : T(1e-17);
-    const T cap = T(80);
-    const T h = Math<T>::min(T(0.25), T(0.5) * Math<T>::rsqrt(z));
-    const T e0 = Math<T>::exp(-z);
-    T s0 = T(0.5) * e0, s1 = T(0.5) * e0;
-    for (int j = 1; j < 4096; ++j) {
-        const T t = T(j) * h;
-        const T et = Math<T>::exp(t);
-        const T iet = Math<T>::rcp(et);
-        const T a = -z * T(0.5) * (et + iet);
-        const T u0 = T(0.5) * (Math<T>::exp(Math<T>::min(a + nu * t, cap)) + Math<T>::exp(a - nu * t));
-        const T u1 = T(0.5) * (Math<T>::exp(Math<T>::min(a + (nu + T(1)) * t, cap)) + Math<T>::exp(a - (nu + T(1)) * t));
-        s0 += u0;
-        s1 += u1;
-        if (z * T(0.5) * (et - iet) > nu + T(1) && u1 <= tol * s1) break;
-    }
-    k0 = h * s0;
-    k1 = h * s1;
+    if (!oka) ka[0] = ka[1] = Math<T>::inf();
+    if (!okb) kb[0] = kb[1] = Math<T>::inf();
 }
 
 template <typename T>
@@ -1213,14 +1261,14 @@ struct SourceTerm {
 };
 
 template <typename T, int D, bool BWD>
-__device__ __noinline__ SourceTerm<T> ball_green(cenv<T> p, T r, T R)
+__device__ __forceinline__ SourceTerm<T> ball_green(cenv<T> p, T r, T R)
 {
     SourceTerm<T> o;
     if (p->sigma > T(0)) {
         const T nu = p->nu, sq = p->sqrt_sigma;
-        T Kr, K1r, KR, K1R;
-        bessel_k_pair<T>(nu, sq * r, Kr, K1r);
-        bessel_k_pair<T>(nu, sq * R, KR, K1R);
+        T kr[2], kR[2];
+        bessel_k_pairs<T, D>(sq * r, sq * R, kr, kR);
+        const T Kr = kr[0], K1r = kr[1], KR = kR[0], K1R = kR[1];
         const T yr = p->qsigma * r * r, yR = p->qsigma * R * R;
         const T pr = horner<T>(p->cC, p->nt_C, yr), pR = horner<T>(p->cC, p->nt_C, yR);
         const T p1r = horner<T>(p->cC1, p->nt_C1, yr), p1R = horner<T>(p->cC1, p->nt_C1, yR);
@@ -1332,31 +1380,30 @@ __device__ __forceinline__ T start_min(cenv<T> p, const T (&xg)[D], T thr, uint6
     return best;
 }
 
-template <typename T, int D, int DA>
-__device__ __forceinline__ UnitStart<T> unit_start(cenv<T> p, const T (&xq)[DA], WorkCount& wc)
+template <typename T, int D>
+__device__ __forceinline__ UnitStart<T> unit_start(cenv<T> p, const T (&x)[D], int32_t n_walks, WorkCount& wc)
 {
-    T x[D], xg[D];
+    T xg[D];
 #pragma unroll
-    for (int i = 0; i < D; ++i) {
-        x[i] = xq[i];
-        xg[i] = (i < p->geom_d) ? x[i] : T(0);
-    }
+    for (int i = 0; i < D; ++i) xg[i] = (i < p->geom_d) ? x[i] : T(0);
     const T dg = goal_dist<T, D>(p, x);
     const T dout = outer_dist<T, D>(p, xg);
     const T da = p->n_arm ? arm_dist<T, D>(p, x) : Math<T>::inf();
     const T tg = Math<T>::min(dg, Math<T>::min(da, dout));
-    uint64_t es = 0, eb = 0, cbt = 0;
+    uint64_t es = 0, eb = 0, cbt = 0;  // obstacle distances and cluster boxes evaluated
     const T db = start_min<T, D, true>(p, xg, tg, eb, cbt);
     const T ds = start_min<T, D, false>(p, xg, Math<T>::min(tg, db), es, cbt);
-    // counted where the steps' own work is that of the lists (scans of every
-    // obstacle count one evaluation per obstacle and step, the first included)
+    // where the steps read lists this work is counted once; where they scan
+    // every obstacle each walk counts one such scan for its first step
     if (p->box_cells) wc.box += eb;
+    else if (!p->n_cl_box) wc.box += (uint64_t)n_walks * eb;
     if (p->sph_cells) wc.sph += es;
-    if (p->box_cells || p->sph_cells) wc.cbox += cbt;
+    else if (!p->n_cl_sph) wc.sph += (uint64_t)n_walks * es;
+    wc.cbox += cbt;
     UnitStart<T> st;
-    int cls;
-    st.R = uniform_of(nearest_of<T>(dg, ds, db, da, dout, cls));
-    st.cls = __builtin_amdgcn_readfirstlane(cls);
+    const Near<T> near = {dg, ds, db, da, dout};
+    st.R = uniform_of(near.R());
+    st.cls = __builtin_amdgcn_readfirstlane(near.cls());
     st.gfac = uniform_of(T(D) * Math<T>::rcp(st.R * horner<T>(p->cC1, p->nt_C1, p->qsigma * (st.R * st.R))));
     st.g = T(0);
     if (st.R < p->eps) st.g = uniform_of(boundary_value<T, D, false>(p, x, st.cls));
@@ -1364,14 +1411,15 @@ __device__ __forceinline__ UnitStart<T> unit_start(cenv<T> p, const T (&xq)[DA],
 }
 
 // ------------------------------------------------------------------------
-// One walk (Sec. IV-A).  State lives in registers; an iteration makes one
-// distance evaluation and either absorbs (eps-shell, Fig. 2) or applies the
-// step's weight and jumps to a uniform point on the sphere of radius R.
+// One walk (Sec. IV-A).  State lives in registers; an iteration applies the
+// step's weight, jumps to a uniform point on the sphere of radius R and
+// evaluates the distance there, which absorbs the walk in the eps-shell
+// (Fig. 2) or is the next step's R.
 // ------------------------------------------------------------------------
 template <typename T, int D>
 struct Walker {
     T x[D];    // current point x_k
-    T v0[D];   // first direction
+    T R;       // distance at x_k
     T W;       // prod_{i < k} C(R_i): weight of u_hat(x_0)
     T W1;      // prod_{1 <= i < k} C(R_i): weight of u_hat(x_1)
     T S;       // sum_{i < k} d ln C(R_i) / d sigma
@@ -1380,32 +1428,16 @@ struct Walker {
     T srcS;    // sum_i W_i amp (S_i G_B + d G_B / d sigma)
     T gs0;     // c_imp amp |grad G_B(x_0, z)| / |z - x_0| (the first ball holds z)
     uint32_t k;
-    uint32_t w;
+    int32_t w;   // walk, counted from the unit's first
     int32_t ex;  // W, W1, src, src1 and srcS hold their values times 2^-ex (FP32 only)
-    T rb;        // bound on this step's R from the previous one (+inf on a walk's first step)
 };
 
-template <typename T>
-struct WalkEnd {
-    T u;        // u_hat(x_0)
-    T gs;       // gradient = gs * v0 (+ gs0 (z - x_0) with a point source)
-    T S;        // sum of d ln C / d sigma over the weighted steps
-    T goal_w;   // W 1{goal}
-    T gs0;      // point source: coefficient of z - x_0 in the gradient
-    T ubd;      // point source: boundary part of u_hat(x_0), W g
-    T srcS;     // point source: source part of d u_hat / d sigma
-    uint32_t steps;
-    int32_t status, cls;
-    int32_t ex;  // u, gs, goal_w, ubd and srcS hold their values times 2^-ex
-};
-
-template <typename T, int D, int DA>
-__device__ __forceinline__ void walker_start(Walker<T, DA>& s, const T (&xq)[DA], uint32_t w)
+template <typename T, int D>
+__device__ __forceinline__ void walker_start(Walker<T, D>& s, const T (&xq)[D], T R, int32_t w)
 {
 #pragma unroll
     for (int i = 0; i < D; ++i) s.x[i] = xq[i];
-#pragma unroll
-    for (int i = 0; i < DA; ++i) s.v0[i] = T(0);
+    s.R = R;
     s.W = T(1);
     s.W1 = T(1);
     s.S = T(0);
@@ -1416,8 +1448,21 @@ __device__ __forceinline__ void walker_start(Walker<T, DA>& s, const T (&xq)[DA]
     s.k = 0;
     s.w = w;
     s.ex = 0;
-    s.rb = Math<T>::inf();
 }
+
+// What a finished walk adds to its unit's sums, apart from its first
+// direction v_0, which the accumulation draws again.
+template <typename T>
+struct WalkEnd {
+    T u;        // u_hat(x_0)
+    T gs;       // gradient = gs * v0 (+ gs0 (z - x_0) with a point source)
+    T S;        // sum of d ln C / d sigma over the weighted steps
+    T goal_w;   // W 1{goal}
+    T gs0;      // point source: coefficient of z - x_0 in the gradient
+    T ubd;      // point source: boundary part of u_hat(x_0), W g
+    T srcS;     // point source: source part of d u_hat / d sigma
+    int32_t ex; // u, gs, goal_w, ubd and srcS hold their values times 2^-ex
+};
 
 // FP32 walks: the weight product of a long walk at a large screening
 // coefficient leaves the FP32 range (1/I_0(sqrt(sigma) R) per step in d = 2,
@@ -1452,67 +1497,16 @@ __device__ __forceinline__ void renormalize(Walker<float, DA>& s)
 template <bool SRC, bool BWD, int DA>
 __device__ __forceinline__ void renormalize(Walker<double, DA>&) {}
 
-// Returns true when the walk ended (e is then filled in).  (key0, key1) is
-// the Philox key of the launch, q the query's index in its environment, st
-// the unit's start.  LISTS: see distance().  The walker may store DA >= D
-// coordinates; only the first D are used.
-template <typename T, int D, bool BWD, bool LISTS, int DA = D, bool SRC = false>
-__device__ __forceinline__ bool walker_step(cenv<T> p0, Walker<T, DA>& s, uint32_t q, uint32_t key0,
-                                            uint32_t key1, WalkEnd<T>& e, WorkCount& wc, bool live,
-                                            const UnitStart<T>& st)
+// The step from x_k: weight, jump, k + 1.  (key0, key1) is the Philox key of
+// the launch, walk and q the walk's and the query's index words.
+template <typename T, int D, bool BWD, bool SRC>
+__device__ __forceinline__ void walker_move(cenv<T> p0, Walker<T, D>& s, uint32_t walk, uint32_t q, uint32_t key0,
+                                            uint32_t key1)
 {
-    static_assert(DA >= D, "walker storage narrower than the dimension");
-    const T(&x)[D] = reinterpret_cast<const T(&)[D]>(s.x);
-    int cls;
-    // the step-to-step bound, in the dimensions where it culls (kStepBoundMaxDim)
-    constexpr bool kBound = D <= kStepBoundMaxDim;
+    const T(&x)[D] = s.x;
+    const T R = s.R;
     const uint32_t k = s.k;
-    // the step's direction does not depend on its distance
-    T v[D];
-    T R = distance<T, D, LISTS>(fresh(p0), x, cls, wc, live, live && k > 0, kBound ? s.rb : Math<T>::inf(),
-                                [&] { direction<T, D>(k, s.w, q, fresh(p0)->env_id, key0, key1, v); });
-    R = k > 0 ? R : st.R;
-    cls = k > 0 ? cls : st.cls;
     cenv<T> p = fresh(p0);
-    // R(x) is a minimum of distances, each 1-Lipschitz, and the walker moves
-    // R: the next R is at most 2 R, and with the margins (rb_abs covers the
-    // rounding of the positions and of every component's computed distance,
-    // +inf where coordinates are unbounded) at most this computed bound, so
-    // it is a threshold the scans may cull against without changing R or cls
-    if (kBound) s.rb = Math<T>::fma(R, T(2.001953125), p->rb_abs);  // 2 (1 + 2^-10)
-    if (R < p->eps) {
-        const bool first = (k == 0);
-        T g = st.g;
-        if (!first) g = boundary_value<T, D, LISTS>(p, x, cls);
-        e.steps = k + 1;
-        e.cls = cls;
-        e.status = first ? kDegenerate : kAbsorbed;
-        e.ex = s.ex;
-        e.u = s.W * g;
-        e.gs = first ? T(0) : st.gfac * s.W1 * g;
-        e.S = s.S;
-        e.goal_w = (cls == kGoal) ? s.W : T(0);
-        if (SRC) {
-            e.ubd = e.u;
-            e.u += s.src;
-            e.gs = first ? T(0) : st.gfac * (s.W1 * g + s.src1);
-            e.gs0 = s.gs0;
-            e.srcS = s.srcS;
-        }
-        return true;
-    }
-    if (k + 1 >= p->max_steps) {
-        e.steps = k + 1;
-        e.cls = cls;
-        e.status = kTruncated;
-        e.ex = 0;
-        e.u = T(0);
-        e.gs = T(0);
-        e.S = T(0);
-        e.goal_w = T(0);
-        if (SRC) e.gs0 = e.ubd = e.srcS = T(0);
-        return true;
-    }
     if (SRC && p->has_src) {  // the ball around x_k holds the source: volume term
         T dz2 = T(0);
 #pragma unroll
@@ -1543,14 +1537,34 @@ __device__ __forceinline__ bool walker_step(cenv<T> p0, Walker<T, DA>& s, uint32
         const T p1 = horner<T>(p->cC1, p->nt_C1, y);
         s.S = Math<T>::fma(T(-0.5 / D) * R2 * p1, C, s.S);
     }
-    if (k == 0) {
-#pragma unroll
-        for (int i = 0; i < D; ++i) s.v0[i] = v[i];
-    }
+    T v[D];
+    direction<T, D>(k, walk, q, fresh(p0)->env_id, key0, key1, v);
 #pragma unroll
     for (int i = 0; i < D; ++i) s.x[i] = Math<T>::fma(R, v[i], s.x[i]);
     s.k = k + 1;
-    return false;
+}
+
+// The sums' part of a walk absorbed at x with the distances near.
+template <typename T, int D, bool LISTS, bool SRC>
+__device__ __forceinline__ WalkEnd<T> walker_end(cenv<T> p, const Walker<T, D>& s, const Near<T>& near, T gfac)
+{
+    const int cls = near.cls();
+    const T g = boundary_value<T, D, LISTS>(p, s.x, cls);
+    WalkEnd<T> e;
+    e.ex = s.ex;
+    e.u = s.W * g;
+    e.gs = gfac * s.W1 * g;
+    e.S = s.S;
+    e.goal_w = (cls == kGoal) ? s.W : T(0);
+    e.gs0 = e.ubd = e.srcS = T(0);
+    if (SRC) {
+        e.ubd = e.u;
+        e.u += s.src;
+        e.gs = gfac * (s.W1 * g + s.src1);
+        e.gs0 = s.gs0;
+        e.srcS = s.srcS;
+    }
+    return e;
 }
 
 // ------------------------------------------------------------------------

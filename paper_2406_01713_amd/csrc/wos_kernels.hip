@@ -235,9 +235,9 @@ plan_update(const EnvP<float>* penv, float* __restrict__ x, int64_t n, const flo
     float xs[D];
 #pragma unroll
     for (int i = 0; i < D; ++i) xs[i] = (n > 0) ? x[si * D + i] : 0.0f;
-    int cls;
     WorkCount wc(pair_lds[__builtin_amdgcn_readfirstlane(threadIdx.x / kWave)]);
-    const float R = distance<float, D, false>(p, xs, cls, wc, valid, false, Math<float>::inf(), [] {});
+    const Near<float> near = distance<float, D, false>(p, xs, wc, valid, Math<float>::inf());
+    const float R = near.R();
     if (valid) {
         float dz2 = 0.0f;
         if (p->has_src) {
@@ -245,7 +245,7 @@ plan_update(const EnvP<float>* penv, float* __restrict__ x, int64_t n, const flo
             for (int i = 0; i < D; ++i) dz2 = Math<float>::fma(xs[i] - p->src_z[i], xs[i] - p->src_z[i], dz2);
         }
         if (R < p->eps) {
-            status[s] = (cls == kGoal) ? 1 : 2;
+            status[s] = (near.cls() == kGoal) ? 1 : 2;
         } else if (p->has_src && dz2 < s_ub * s_ub) {
             status[s] = 1;  // a point-source goal is reached within one nominal step
         } else {
@@ -358,22 +358,46 @@ hipError_t launch_reduce_pairs(const double* prod, int64_t n, double* out0, doub
     return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_plain(int d, bool bwd, bool src, bool lists, const EnvP<T>* p, const T* queries, int64_t n_q,
+                        int64_t n_walks, int32_t wpu, int64_t w_base, uint32_t q_base, double* partials,
+                        double* records, hipStream_t st)
+{
+#define WOS_PLAIN_CASE(D) \
+    case D: return launch_plain_d<T, D>(bwd, src, lists, p, queries, n_q, n_walks, wpu, w_base, q_base, partials, records, st);
+    switch (d) {
+        WOS_PLAIN_CASE(2)
+        WOS_PLAIN_CASE(3)
+        WOS_PLAIN_CASE(4)
+        WOS_PLAIN_CASE(5)
+        WOS_PLAIN_CASE(6)
+        WOS_PLAIN_CASE(7)
+        WOS_PLAIN_CASE(8)
+    default: return hipErrorInvalidValue;
+    }
+#undef WOS_PLAIN_CASE
+}
+template hipError_t launch_plain<float>(int, bool, bool, bool, const EnvP<float>*, const float*, int64_t, int64_t,
+                                        int32_t, int64_t, uint32_t, double*, double*, hipStream_t);
+template hipError_t launch_plain<double>(int, bool, bool, bool, const EnvP<double>*, const double*, int64_t, int64_t,
+                                         int32_t, int64_t, uint32_t, double*, double*, hipStream_t);
+
 hipError_t launch_persistent(bool bwd, bool src, bool lists, int grid, int block, const EnvP<float>* envs,
-                             const BatchEnv* benv, int n_benv, const float* queries, int64_t total_units,
+                             const BatchEnv* benv, int n_benv, int max_d, const float* queries, int64_t total_units,
                              uint32_t key0, uint32_t key1, const uint64_t* key_add, unsigned* counter,
                              double* partials, hipStream_t st)
 {
     if (total_units == 0) return hipSuccess;
     auto* go = src ? (lists ? launch_persistent_variant<true, true> : launch_persistent_variant<true, false>)
                    : (lists ? launch_persistent_variant<false, true> : launch_persistent_variant<false, false>);
-    return go(bwd, grid, block, envs, benv, n_benv, queries, total_units, key0, key1, key_add, counter, partials, st);
+    return go(bwd, grid, block, envs, benv, n_benv, max_d, queries, total_units, key0, key1, key_add, counter, partials, st);
 }
 
-int persistent_resident_blocks(bool bwd, bool src, bool lists, int block)
+int persistent_resident_blocks(bool bwd, bool src, bool lists, int max_d, int block)
 {
     auto* per = src ? (lists ? persistent_blocks_per_cu<true, true> : persistent_blocks_per_cu<true, false>)
                     : (lists ? persistent_blocks_per_cu<false, true> : persistent_blocks_per_cu<false, false>);
-    const int per_cu = per(bwd, block);
+    const int per_cu = per(bwd, max_d, block);
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess) return per_cu;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 1;

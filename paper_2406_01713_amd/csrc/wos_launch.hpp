@@ -15,15 +15,19 @@ bool lists_ok(const EnvP<T>& p)
     return (p.sph_cells || !p.n_cl_sph) && (p.box_cells || !p.n_cl_box);
 }
 
-// Plain walk kernel: one walk per lane, one wave per (query, 64-walk chunk),
-// no refill.  Writes one partial-sum row per wave.  p is a device pointer;
-// src selects the variant with point-source terms, lists the one whose steps
-// read cell lists or scan every obstacle (EnvP must be fit for it: lists_ok).
+// Plain walk kernel: one wave per (query, range of `wpu` walks), lanes
+// refilled within the range.  Writes one partial-sum row per wave, chunks =
+// ceil(n_walks / wpu) rows per query.  p is a device pointer; src selects the
+// variant with point-source terms, lists the one whose steps read cell lists
+// or scan every obstacle (EnvP must be fit for it: lists_ok).
 template <typename T>
 hipError_t launch_plain(int d, bool bwd, bool src, bool lists, const EnvP<T>* p, const T* queries, int64_t n_q,
-                        int64_t n_walks, int64_t w_base, uint32_t q_base,
-                        const uint64_t* key_add, double* partials, double* records,
-                        hipStream_t st);
+                        int64_t n_walks, int32_t wpu, int64_t w_base, uint32_t q_base, double* partials,
+                        double* records, hipStream_t st);
+template <typename T, int D>
+hipError_t launch_plain_d(bool bwd, bool src, bool lists, const EnvP<T>* p, const T* queries, int64_t n_q,
+                          int64_t n_walks, int32_t wpu, int64_t w_base, uint32_t q_base, double* partials,
+                          double* records, hipStream_t st);
 
 // Per-query means / standard errors (and backward products) from the plain
 // kernel's partials.  prod (Q x 2) receives grad_u[q] * (du/dsigma, du/dg).
@@ -41,7 +45,7 @@ hipError_t launch_reduce_pairs(const double* prod, int64_t n, double* out0, doub
 // units from *counter; refills lanes with the next walk of the unit.  src
 // selects the variant with point-source terms (any env of the batch).
 hipError_t launch_persistent(bool bwd, bool src, bool lists, int grid, int block, const EnvP<float>* envs,
-                             const BatchEnv* benv, int n_benv, const float* queries,
+                             const BatchEnv* benv, int n_benv, int max_d, const float* queries,
                              int64_t total_units, uint32_t key0, uint32_t key1,
                              const uint64_t* key_add, unsigned* counter, double* partials,
                              hipStream_t st);
@@ -49,14 +53,15 @@ hipError_t launch_persistent(bool bwd, bool src, bool lists, int grid, int block
 // The variants of the above.
 template <bool SRC, bool LISTS>
 hipError_t launch_persistent_variant(bool bwd, int grid, int block, const EnvP<float>* envs, const BatchEnv* benv,
-                                     int n_benv, const float* queries, int64_t total_units, uint32_t key0,
+                                     int n_benv, int max_d, const float* queries, int64_t total_units, uint32_t key0,
                                      uint32_t key1, const uint64_t* key_add, unsigned* counter, double* partials,
                                      hipStream_t st);
 template <bool SRC, bool LISTS>
-int persistent_blocks_per_cu(bool bwd, int block);
+int persistent_blocks_per_cu(bool bwd, int max_d, int block);
 
 // Resident waves of the persistent kernel for a block size (occupancy x CUs).
-int persistent_resident_blocks(bool bwd, bool src, bool lists, int block);
+// max_d: the batch's largest dimension.
+int persistent_resident_blocks(bool bwd, bool src, bool lists, int max_d, int block);
 
 // Outputs of a batched launch; one block per env; also resets *counter.
 // out_dir (optional, rows like out_grad) receives grad / |grad| formed from
