@@ -105,6 +105,7 @@ struct wos_domain {
     GridCell* box_cells = nullptr;
     uint32_t* sph_list = nullptr;
     uint32_t* box_list = nullptr;
+    bool goal_in_list = false;  // the spheres' lists hold the goal ball as row n_sph
 };
 
 namespace {
@@ -124,6 +125,18 @@ int series_coeffs(double b, double y_max, double tol, double* c)
         if (y_max == 0.0) return 1;
     }
     return -1;
+}
+
+// Largest y up to which the first n terms of 0F1(; b; y) (and of 0F1(; b + 1; y),
+// whose terms are smaller) give it to tol relatively; all of them when the
+// series holds no more.  The tail is below twice its first term while
+// y <= (b + n) (n + 1) / 2.
+double short_series_range(double b, int n, int terms, double tol)
+{
+    if (terms <= n) return 1e30;
+    double lg = std::log(0.5 * tol);
+    for (int k = 0; k < n; ++k) lg += std::log((b + k) * (k + 1.0));
+    return std::min(std::exp(lg / n), 0.5 * (b + n) * (n + 1.0));
 }
 
 // counted: the caller reports how many obstacle distances the walks evaluate;
@@ -197,11 +210,11 @@ int make_env(const wos_domain* D, double sigma, double eps, uint64_t seed, uint3
         if (!counted || D->n_box >= kClusterMin) p.box_cells = D->box_cells;
         p.sph_list = D->sph_list;
         p.box_list = D->box_list;
+        p.goal_listed = p.sph_cells && D->goal_in_list;
         p.grid_last = D->grid.cells - 1;
         p.grid_inv = (T)(1.0 / (double)D->grid.h);
         for (int i = 0; i < kMaxDim; ++i) {
             p.grid_n[i] = D->grid.n[i];
-            p.grid_off[i] = i < D->geom_d ? (T)(-(double)D->grid.lo[i] / (double)D->grid.h) : T(0);
             p.grid_max[i] = (T)(D->grid.n[i] - 1);
         }
         for (int l = 0; l < 3; ++l) p.grid_lev[l] = (T)D->grid.lev[l];
@@ -220,13 +233,14 @@ int make_env(const wos_domain* D, double sigma, double eps, uint64_t seed, uint3
     p.mode = D->mode;
     p.nt_C = nC;
     p.nt_C1 = nC1;
+    p.y_short = (T)std::ldexp(short_series_range(0.5 * D->d, kShortTerms<T>, std::max(nC, nC1), tol), -m);
     p.key0 = (uint32_t)seed;
     p.key1 = (uint32_t)(seed >> 32);
     p.env_id = env_id;
     p.max_steps = o.max_steps ? o.max_steps : kDefaultMaxSteps;
     for (int i = 0; i < kMaxDim; ++i) {
         p.goal_c[i] = (T)D->goal_c[i];
-        p.lo[i] = (T)D->lo[i];
+        p.lo[i] = (T)(D->outer_kind == WOS_OUTER_BOX ? D->lo[i] : D->oc[i] - D->orad);
         p.hi[i] = (T)D->hi[i];
         p.oc[i] = (T)D->oc[i];
         p.ak[i] = (T)D->ak[i];
@@ -1363,6 +1377,17 @@ int wos_create_domain(int d, const wos_spheres* spheres, const wos_boxes* boxes,
         }
         D->coord_scale = sc;
     }
+    // the goal ball follows the spheres: where obstacles depend on every
+    // coordinate the cell lists hold it as one more sphere
+    D->goal_in_list = D->has_goal && gd == d && ns >= kGridMin;
+    if (D->goal_in_list) {
+        sf.resize((size_t)(ns + 1) * ss, 0.0f);
+        sd.resize((size_t)(ns + 1) * ss, 0.0);
+        for (int i = 0; i <= d; ++i) {
+            sd[ns * ss + i] = i < d ? D->goal_c[i] : D->goal_r;
+            sf[ns * ss + i] = (float)sd[ns * ss + i];
+        }
+    }
     hipError_t e = hipGetDevice(&D->device);
     if (e == hipSuccess) e = hipMalloc(&D->sph_f, sf.size() * sizeof(float));
     if (e == hipSuccess) e = hipMalloc(&D->sph_d, sd.size() * sizeof(double));
@@ -1430,7 +1455,7 @@ int wos_create_domain(int d, const wos_spheres* spheres, const wos_boxes* boxes,
     if (ns >= kGridMin || nb >= kGridMin) plan_grid(D, D->grid);
     if (D->grid.cells) {
         if (e == hipSuccess && ns >= kGridMin)
-            e = build_grid(D->grid, d, false, D->sph_f, ns, &D->sph_cells, &D->sph_list);
+            e = build_grid(D->grid, d, false, D->sph_f, ns + (D->goal_in_list ? 1 : 0), &D->sph_cells, &D->sph_list);
         if (e == hipSuccess && nb >= kGridMin)
             e = build_grid(D->grid, d, true, D->box_f, nb, &D->box_cells, &D->box_list);
     }

@@ -247,6 +247,30 @@ __device__ __forceinline__ T boxes_min(cptr<T> box, int n, const T (&x)[D])
     return best;
 }
 
+// Extruded geometry: obstacles and the outer boundary see the leading geom_d
+// coordinates only (their stored centres are zero beyond them).
+template <typename T, int D>
+__device__ __forceinline__ void leading(cenv<T> p, const T (&x)[D], T (&xg)[D])
+{
+#pragma unroll
+    for (int i = 0; i < D; ++i) xg[i] = (i < p->geom_d) ? x[i] : T(0);
+}
+
+template <typename T, int D>
+__device__ __forceinline__ T ball_dist(cenv<T> p, const T (&x)[D])
+{
+    T xg[D];
+    leading<T, D>(p, x, xg);
+    T t = xg[0] - p->oc[0];
+    T acc = t * t;
+#pragma unroll
+    for (int i = 1; i < D; ++i) {
+        t = xg[i] - p->oc[i];
+        acc = Math<T>::fma(t, t, acc);
+    }
+    return p->orad - Math<T>::sqrt(acc);
+}
+
 template <typename T, int D>
 __device__ __forceinline__ T outer_dist(cenv<T> p, const T (&x)[D])
 {
@@ -256,14 +280,7 @@ __device__ __forceinline__ T outer_dist(cenv<T> p, const T (&x)[D])
         for (int i = 1; i < D; ++i) m = Math<T>::min(m, Math<T>::min(x[i] - p->lo[i], p->hi[i] - x[i]));
         return m;
     }
-    T t = x[0] - p->oc[0];
-    T acc = t * t;
-#pragma unroll
-    for (int i = 1; i < D; ++i) {
-        t = x[i] - p->oc[i];
-        acc = Math<T>::fma(t, t, acc);
-    }
-    return p->orad - Math<T>::sqrt(acc);
+    return ball_dist<T, D>(p, x);
 }
 
 // ------------------------------------------------------------------------
@@ -644,19 +661,17 @@ __device__ __forceinline__ uint32_t wave_incl_max(uint32_t v)
 // ------------------------------------------------------------------------
 // Cell lists (see kGridMin): the cell of x, and the minimum over a list.
 // ------------------------------------------------------------------------
-// Cell index of x.  The coordinate is clamped per axis (NaN gives an end of
-// the range), so the index is always inside the table; the lists allow for
-// the rounding of the coordinate.
+// Cell index of the point at offset a = x - lo.  The coordinate is clamped per
+// axis (NaN gives an end of the range), so the index is always inside the
+// table; the lists allow for the rounding of the coordinate.
 template <typename T, int D>
-__device__ __forceinline__ uint32_t grid_cell(cenv<T> p, const T (&x)[D])
+__device__ __forceinline__ uint32_t grid_cell(cenv<T> p, const T (&a)[D])
 {
     uint32_t idx = 0;
     const T inv = p->grid_inv;
 #pragma unroll
-    for (int i = 0; i < D; ++i) {
-        const T t = Math<T>::clamp0(Math<T>::fma(x[i], inv, p->grid_off[i]), p->grid_max[i]);
-        idx = __umul24(idx, p->grid_n[i]) + (uint32_t)t;
-    }
+    for (int i = 0; i < D; ++i)
+        idx = __umul24(idx, p->grid_n[i]) + (uint32_t)Math<T>::clamp0(a[i] * inv, p->grid_max[i]);
     return idx < p->grid_last ? idx : p->grid_last;
 }
 
@@ -683,9 +698,12 @@ constexpr uint32_t kCellDirect = 2;
 // maximum carries the owner to the following slots, and the position, list
 // offset and minimum are the owner's, by lane shuffles and an LDS atomic min.
 template <typename T, int D, bool BOX>
-__device__ __forceinline__ T cell_min(cptr<uint32_t> list, cptr<T> rows, uint32_t off, uint32_t n, const T (&x)[D],
-                                      uint64_t& evals, uint32_t* lds)
+__device__ __forceinline__ T cell_min(cenv<T> p, uint32_t off, uint32_t n, const T (&x)[D], uint64_t& evals,
+                                      uint32_t* lds)
 {
+    p = fresh(p);
+    cptr<uint32_t> list = to_const(BOX ? p->box_list : p->sph_list);
+    cptr<T> rows = to_const(BOX ? p->box : p->sph);
     constexpr int S = BOX ? box_stride(D) : sph_stride(D);
     T best = Math<T>::inf();
     uint64_t m = __builtin_amdgcn_ballot_w64(n > 0);
@@ -943,46 +961,63 @@ struct Near {
 template <typename T, int D, bool LISTS>
 __device__ __forceinline__ Near<T> distance(cenv<T> p, const T (&x)[D], WorkCount& wc, bool live, T ub)
 {
-    // extruded geometry: obstacles and the outer boundary see the leading
-    // geom_d coordinates only (their stored centres are zero beyond them)
-    T xg[D];
+    // the offsets from the outer box's corner give the cell and half of the box
+    // distance; coordinates past geom_d have unbounded faces and one cell
+    T off[D];
 #pragma unroll
-    for (int i = 0; i < D; ++i) xg[i] = (i < p->geom_d) ? x[i] : T(0);
+    for (int i = 0; i < D; ++i) off[i] = x[i] - p->lo[i];
     GridCell hs = {0, 0}, hb = {0, 0};
     const GridCell* cs = LISTS ? p->sph_cells : nullptr;  // wave-uniform
     const GridCell* cb = LISTS ? p->box_cells : nullptr;
     if (LISTS && (cs || cb)) {
-        const uint32_t cell = grid_cell<T, D>(fresh(p), xg);
+        const uint32_t cell = grid_cell<T, D>(p, off);
         if (cs) hs = cs[cell];
         if (cb) hb = cb[cell];
     }
+    T dout;
+    if (p->outer_kind == 0) {
+        dout = Math<T>::min(off[0], p->hi[0] - x[0]);
+#pragma unroll
+        for (int i = 1; i < D; ++i) dout = Math<T>::min(dout, Math<T>::min(off[i], p->hi[i] - x[i]));
+    } else {
+        dout = ball_dist<T, D>(p, x);
+    }
     p = fresh(p);
-    const T dg = goal_dist<T, D>(p, x);
-    const T dout = outer_dist<T, D>(p, xg);
-    p = fresh(p);
+    // a listed goal ball is found with the spheres
+    const T dg = (LISTS && p->goal_listed) ? Math<T>::inf() : goal_dist<T, D>(p, x);
     // the arm bound (joint coordinates, never extruded) tightens the scans
     const T da = p->n_arm ? arm_dist<T, D>(p, x) : Math<T>::inf();
     const T tg = Math<T>::min(Math<T>::min(dg, Math<T>::min(da, dout)), ub);  // threshold before the box result
     T db = Math<T>::inf(), ds = Math<T>::inf();
     uint32_t nb = 0, ns = 0;  // distances per live lane (wave-uniform scans)
     if (LISTS) {
-        if (cb) {
-            const uint32_t n = live ? grid_count<T>(fresh(p), hb.counts, tg) : 0u;
-            db = cell_min<T, D, true>(to_const(fresh(p)->box_list), to_const(fresh(p)->box), hb.off, n, xg, wc.box,
-                                      wc.pairs);
+        if (cb) {  // boxes are never extruded
+            const uint32_t n = live ? grid_count<T>(p, hb.counts, tg) : 0u;
+            db = cell_min<T, D, true>(p, hb.off, n, x, wc.box, wc.pairs);
         } else if (p->n_box) {
             nb = (uint32_t)p->n_box;
-            db = boxes_min<T, D>(to_const(p->box), (int)nb, xg);
+            db = boxes_min<T, D>(to_const(p->box), (int)nb, x);
         }
         if (cs) {
-            const uint32_t n = live ? grid_count<T>(fresh(p), hs.counts, Math<T>::min(tg, db)) : 0u;
-            ds = cell_min<T, D, false>(to_const(fresh(p)->sph_list), to_const(fresh(p)->sph), hs.off, n, xg, wc.sph,
-                                       wc.pairs);
+            const uint32_t n = live ? grid_count<T>(p, hs.counts, Math<T>::min(tg, db)) : 0u;
+            if (__builtin_amdgcn_ballot_w64(n > 0) != 0) {
+                if (p->geom_d == D) {
+                    ds = cell_min<T, D, false>(p, hs.off, n, x, wc.sph, wc.pairs);
+                } else {
+                    T xg[D];
+                    leading<T, D>(p, x, xg);
+                    ds = cell_min<T, D, false>(p, hs.off, n, xg, wc.sph, wc.pairs);
+                }
+            }
         } else if (p->n_sph) {
+            T xg[D];
+            leading<T, D>(p, x, xg);
             ns = (uint32_t)p->n_sph;
             ds = spheres_min<T, D>(to_const(p->sph), (int)ns, xg);
         }
     } else {
+        T xg[D];
+        leading<T, D>(p, x, xg);
         db = scan_min<T, D, true>(p, xg, tg, live, nb, wc.box, wc.cbox, wc.pairs);
         ds = scan_min<T, D, false>(p, xg, Math<T>::min(tg, db), live, ns, wc.sph, wc.cbox, wc.pairs);
     }
@@ -1008,7 +1043,10 @@ __device__ __forceinline__ int nearest_index(cenv<T> p, const T (&x)[D])
     T best = Math<T>::inf();
     const GridCell* cells = LISTS ? (BOX ? p->box_cells : p->sph_cells) : nullptr;
     if (LISTS && cells) {
-        const GridCell h = cells[grid_cell<T, D>(p, x)];
+        T a[D];
+#pragma unroll
+        for (int i = 0; i < D; ++i) a[i] = x[i] - p->lo[i];
+        const GridCell h = cells[grid_cell<T, D>(p, a)];
         const uint32_t n = grid_decode(h.counts >> 24);
         cptr<uint32_t> list = to_const(BOX ? p->box_list : p->sph_list) + h.off;
         for (uint32_t i = 0; i < n; ++i) {
@@ -1384,8 +1422,7 @@ template <typename T, int D>
 __device__ __forceinline__ UnitStart<T> unit_start(cenv<T> p, const T (&x)[D], int32_t n_walks, WorkCount& wc)
 {
     T xg[D];
-#pragma unroll
-    for (int i = 0; i < D; ++i) xg[i] = (i < p->geom_d) ? x[i] : T(0);
+    leading<T, D>(p, x, xg);
     const T dg = goal_dist<T, D>(p, x);
     const T dout = outer_dist<T, D>(p, xg);
     const T da = p->n_arm ? arm_dist<T, D>(p, x) : Math<T>::inf();
@@ -1500,8 +1537,8 @@ __device__ __forceinline__ void renormalize(Walker<double, DA>&) {}
 // The step from x_k: weight, jump, k + 1.  (key0, key1) is the Philox key of
 // the launch, walk and q the walk's and the query's index words.
 template <typename T, int D, bool BWD, bool SRC>
-__device__ __forceinline__ void walker_move(cenv<T> p0, Walker<T, D>& s, uint32_t walk, uint32_t q, uint32_t key0,
-                                            uint32_t key1)
+__device__ __forceinline__ void walker_move(cenv<T> p0, Walker<T, D>& s, uint32_t walk, uint32_t q, uint32_t env,
+                                            uint32_t key0, uint32_t key1)
 {
     const T(&x)[D] = s.x;
     const T R = s.R;
@@ -1528,17 +1565,29 @@ __device__ __forceinline__ void walker_move(cenv<T> p0, Walker<T, D>& s, uint32_
     }
     const T R2 = R * R;
     const T y = p->qsigma * R2;
-    const T C = Math<T>::rcp(horner<T>(p->cC, p->nt_C, y));
-    p = fresh(p0);
+    T F, F1 = T(1);  // 0F1(; d/2; y), and of d/2 + 1 where the backward sums need it
+    if (__builtin_amdgcn_ballot_w64(y > p->y_short) == 0) {
+        // straight-line short series, both at once: a loop over all terms
+        // waits for its coefficients every four of them
+        constexpr int N = kShortTerms<T>;
+        F = p->cC[N - 1];
+        F1 = BWD ? p->cC1[N - 1] : T(1);
+#pragma unroll
+        for (int i = N - 2; i >= 0; --i) {
+            F = Math<T>::fma(F, y, p->cC[i]);
+            if (BWD) F1 = Math<T>::fma(F1, y, p->cC1[i]);
+        }
+    } else {
+        F = horner<T>(p->cC, p->nt_C, y);
+        if (BWD) F1 = horner<T>(p->cC1, p->nt_C1, y);
+    }
+    const T C = Math<T>::rcp(F);
     s.W *= C;
     s.W1 *= (k > 0) ? C : T(1);
     renormalize<SRC, BWD>(s);
-    if (BWD) {
-        const T p1 = horner<T>(p->cC1, p->nt_C1, y);
-        s.S = Math<T>::fma(T(-0.5 / D) * R2 * p1, C, s.S);
-    }
+    if (BWD) s.S = Math<T>::fma(T(-0.5 / D) * R2 * F1, C, s.S);
     T v[D];
-    direction<T, D>(k, walk, q, fresh(p0)->env_id, key0, key1, v);
+    direction<T, D>(k, walk, q, env, key0, key1, v);
 #pragma unroll
     for (int i = 0; i < D; ++i) s.x[i] = Math<T>::fma(R, v[i], s.x[i]);
     s.k = k + 1;
@@ -1546,9 +1595,13 @@ __device__ __forceinline__ void walker_move(cenv<T> p0, Walker<T, D>& s, uint32_
 
 // The sums' part of a walk absorbed at x with the distances near.
 template <typename T, int D, bool LISTS, bool SRC>
-__device__ __forceinline__ WalkEnd<T> walker_end(cenv<T> p, const Walker<T, D>& s, const Near<T>& near, T gfac)
+__device__ __forceinline__ WalkEnd<T> walker_end(cenv<T> p, const Walker<T, D>& s, const Near<T>& near, T gfac,
+                                                 int& cls)
 {
-    const int cls = near.cls();
+    // a listed goal's distance is in near.ds; it is the nearest if it attains it
+    Near<T> at = near;
+    if (LISTS && p->goal_listed) at.dg = goal_dist<T, D>(p, s.x);
+    cls = at.cls();
     const T g = boundary_value<T, D, LISTS>(p, s.x, cls);
     WalkEnd<T> e;
     e.ex = s.ex;

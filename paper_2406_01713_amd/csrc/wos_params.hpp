@@ -78,6 +78,12 @@ constexpr int kStepBoundMaxDim = 5;
 // (see build_cluster_boxes) and rounded outwards.
 constexpr int kClusterBox = 2 * kMaxDim;
 
+// Weight-series terms of a step whose walkers all have sigma R^2 / 4 at most
+// y_short: the tail is below the series' own tolerance (1e-9 in FP32, 1e-18 in
+// FP64, relative), as the full count's is at the largest possible R.
+template <typename T>
+constexpr int kShortTerms = sizeof(T) == 4 ? 8 : 16;
+
 constexpr int kMfmaTile = 16;
 constexpr int kMfmaFeat = 12;
 
@@ -140,10 +146,14 @@ struct EnvP {
     const GridCell* box_cells;
     const uint32_t* sph_list;
     const uint32_t* box_list;
+    // lo: the outer box's corner, or of the box around the outer ball; the cell
+    // coordinate (x - lo) inv is clamped to [0, max]
+    T lo[kMaxDim], hi[kMaxDim], grid_max[kMaxDim];
     uint32_t grid_n[kMaxDim];   // cells per axis (1 past geom_d)
-    uint32_t grid_last, pad_grid;  // cells - 1
-    T grid_inv, grid_off[kMaxDim], grid_max[kMaxDim];  // cell coordinate x inv + off, clamped to [0, max]
+    T grid_inv;
     T grid_lev[3];              // threshold ranges of the count bytes
+    uint32_t grid_last;         // cells - 1
+    int32_t goal_listed;        // the goal ball is an entry (index n_sph) of the spheres' lists
     int32_t geom_d, pad_g;     // obstacles and the outer boundary depend on x[0..geom_d) only
     const T* arm_pts;          // planar arm: n_arm x 2 task-plane obstacle points
     int32_t n_arm, pad_arm;    // 0: no arm
@@ -151,11 +161,11 @@ struct EnvP {
     T arm_invK;                // 1 / K, K the arm's Lipschitz constant
     int32_t outer_kind, mode;  // outer: 0 box, 1 ball; mode: 0 class, 1 affine, 2 plane
     int32_t nt_C, nt_C1;       // Horner terms of 0F1(;d/2;y) and 0F1(;d/2+1;y)
+    T y_short;                 // both series need only kShortTerms terms up to this y (scaled as qsigma)
     uint32_t key0, key1;       // Philox key (seed)
     uint32_t env_id, max_steps;
     T goal_c[kMaxDim];
     T goal_r;
-    T lo[kMaxDim], hi[kMaxDim];
     T oc[kMaxDim];
     T orad;
     T g_goal, g_obs, g_outer, b;

@@ -174,7 +174,8 @@ __device__ __forceinline__ void run_unit(cenv<T> p, cptr<T> qrow, uint32_t q, ui
     Walker<T, D> s;
     bool active = !first_only && lane < lanes && lane < n;
     walker_start<T, D>(s, xq, st.R, lane);
-    T rb_abs = p->rb_abs;
+    const T rb_abs = p->rb_abs, eps = p->eps;
+    const uint32_t max_steps = p->max_steps, env = p->env_id;
     int32_t base = lanes;
     for (;;) {
         const bool any = __builtin_amdgcn_ballot_w64(active) != 0;  // wave-uniform, as everything about the queue
@@ -182,7 +183,7 @@ __device__ __forceinline__ void run_unit(cenv<T> p, cptr<T> qrow, uint32_t q, ui
         Near<T> near = {};
         uint64_t m = 0;
         if (any) {
-            walker_move<T, D, BWD, SRC>(p, s, id0 + (uint32_t)s.w, q, k0, k1);
+            walker_move<T, D, BWD, SRC>(p, s, id0 + (uint32_t)s.w, q, env, k0, k1);
             // R(x) is a minimum of distances, each 1-Lipschitz, and the walker
             // moved R: the next R is at most 2 R, and with the margins (rb_abs
             // covers the rounding of the positions and of every component's
@@ -196,8 +197,9 @@ __device__ __forceinline__ void run_unit(cenv<T> p, cptr<T> qrow, uint32_t q, ui
             s.R = near.R();
             const uint64_t act = __builtin_amdgcn_ballot_w64(active);
             steps += (uint64_t)__popcll(act);
-            fin = active && (s.R < fresh(p)->eps || s.k + 1 >= p->max_steps);
+            fin = active && (s.R < eps || s.k + 1 >= max_steps);
             m = __builtin_amdgcn_ballot_w64(fin);
+            if (m == 0) continue;
         }
         int left = __popcll(m);
         const int rank =
@@ -222,7 +224,7 @@ __device__ __forceinline__ void run_unit(cenv<T> p, cptr<T> qrow, uint32_t q, ui
                     e.ex = (int32_t)wd[0];
                     const uint32_t w = wd[lds.cap];
                     T v0[D];
-                    direction<T, D>(0u, id0 + w, q, fresh(p)->env_id, k0, k1, v0);
+                    direction<T, D>(0u, id0 + w, q, env, k0, k1, v0);
                     const double sc = walk_scale<T>(e.ex);
                     const double u = (double)e.u * sc;
                     su += u;
@@ -255,8 +257,9 @@ __device__ __forceinline__ void run_unit(cenv<T> p, cptr<T> qrow, uint32_t q, ui
             if (left == 0) break;
             if (fin && rank >= from && rank < from + take) {
                 WalkEnd<T> e = {};
-                const bool cut = !(s.R < fresh(p)->eps);  // truncated: contributes nothing
-                if (!cut) e = walker_end<T, D, LISTS, SRC>(fresh(p), s, near, st.gfac);
+                const bool cut = !(s.R < eps);  // truncated: contributes nothing
+                int cls = near.cls();
+                if (!cut) e = walker_end<T, D, LISTS, SRC>(fresh(p), s, near, st.gfac, cls);
                 const int at = qn + rank - from;
                 T* r = lds.real + at;
                 uint32_t* wd = lds.word + at;
@@ -273,7 +276,7 @@ __device__ __forceinline__ void run_unit(cenv<T> p, cptr<T> qrow, uint32_t q, ui
                 wd[lds.cap] = (uint32_t)s.w;
                 if (REC) {
                     wd[(REC ? 2 : 0) * lds.cap] = s.k + 1;
-                    wd[(REC ? 3 : 0) * lds.cap] = (uint32_t)(cut ? kTruncated : kAbsorbed) | ((uint32_t)near.cls() << 8);
+                    wd[(REC ? 3 : 0) * lds.cap] = (uint32_t)(cut ? kTruncated : kAbsorbed) | ((uint32_t)cls << 8);
                 }
             }
             qn += take;
@@ -282,7 +285,7 @@ __device__ __forceinline__ void run_unit(cenv<T> p, cptr<T> qrow, uint32_t q, ui
         }
         if (!any) break;
         if (m) {
-            trunc += (uint64_t)__popcll(__builtin_amdgcn_ballot_w64(fin && !(s.R < fresh(p)->eps)));
+            trunc += (uint64_t)__popcll(__builtin_amdgcn_ballot_w64(fin && !(s.R < eps)));
             // lane refill: finished lanes take the unit's next walks in lane order
             const int32_t wn = base + rank;
             if (fin) {
