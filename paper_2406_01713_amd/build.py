@@ -23,8 +23,9 @@ ARCH = os.environ.get("WOS_OFFLOAD_ARCH", "gfx950")
 
 # (source, macro definitions): the walk kernels are compiled once per
 # variant, so their long compilations run side by side
-SOURCES = [*(("wos_persistent.hip", [f"-DWOS_PERSISTENT_SRC={s}", f"-DWOS_PERSISTENT_LISTS={l}"])
-             for s in (0, 1) for l in (0, 1)),
+SOURCES = [*(("wos_persistent.hip", [f"-DWOS_PERSISTENT_SRC={s}", f"-DWOS_PERSISTENT_LISTS={l}",
+                                     f"-DWOS_PERSISTENT_MAXD={m}"])
+             for s in (0, 1) for l, m in ((0, 8), (1, 8), (1, 5))),
            *(("wos_plain.hip", [f"-DWOS_PLAIN_T={t}", f"-DWOS_PLAIN_LOW={h}"])
              for t in ("float", "double") for h in (0, 1)),
            ("wos_kernels.hip", []), ("wos_grid.hip", []), ("wos_api.cpp", []), ("wos_microbench.hip", [])]

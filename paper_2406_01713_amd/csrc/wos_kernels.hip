@@ -388,15 +388,15 @@ hipError_t launch_persistent(bool bwd, bool src, bool lists, int grid, int block
                              double* partials, hipStream_t st)
 {
     if (total_units == 0) return hipSuccess;
-    auto* go = src ? (lists ? launch_persistent_variant<true, true> : launch_persistent_variant<true, false>)
-                   : (lists ? launch_persistent_variant<false, true> : launch_persistent_variant<false, false>);
+    auto* go = src ? (!lists ? launch_persistent_variant<true, false, kMaxDim> : max_d > 5 ? launch_persistent_variant<true, true, kMaxDim> : launch_persistent_variant<true, true, 5>)
+                   : (!lists ? launch_persistent_variant<false, false, kMaxDim> : max_d > 5 ? launch_persistent_variant<false, true, kMaxDim> : launch_persistent_variant<false, true, 5>);
     return go(bwd, grid, block, envs, benv, n_benv, max_d, queries, total_units, key0, key1, key_add, counter, partials, st);
 }
 
 int persistent_resident_blocks(bool bwd, bool src, bool lists, int max_d, int block)
 {
-    auto* per = src ? (lists ? persistent_blocks_per_cu<true, true> : persistent_blocks_per_cu<true, false>)
-                    : (lists ? persistent_blocks_per_cu<false, true> : persistent_blocks_per_cu<false, false>);
+    auto* per = src ? (!lists ? persistent_blocks_per_cu<true, false, kMaxDim> : max_d > 5 ? persistent_blocks_per_cu<true, true, kMaxDim> : persistent_blocks_per_cu<true, true, 5>)
+                    : (!lists ? persistent_blocks_per_cu<false, false, kMaxDim> : max_d > 5 ? persistent_blocks_per_cu<false, true, kMaxDim> : persistent_blocks_per_cu<false, true, 5>);
     const int per_cu = per(bwd, max_d, block);
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess) return per_cu;

@@ -51,12 +51,12 @@ hipError_t launch_persistent(bool bwd, bool src, bool lists, int grid, int block
                              hipStream_t st);
 
 // The variants of the above.
-template <bool SRC, bool LISTS>
+template <bool SRC, bool LISTS, int MAXD>
 hipError_t launch_persistent_variant(bool bwd, int grid, int block, const EnvP<float>* envs, const BatchEnv* benv,
                                      int n_benv, int max_d, const float* queries, int64_t total_units, uint32_t key0,
                                      uint32_t key1, const uint64_t* key_add, unsigned* counter, double* partials,
                                      hipStream_t st);
-template <bool SRC, bool LISTS>
+template <bool SRC, bool LISTS, int MAXD>
 int persistent_blocks_per_cu(bool bwd, int max_d, int block);
 
 // Resident waves of the persistent kernel for a block size (occupancy x CUs).

@@ -21,12 +21,14 @@ constexpr int kPlainBlock = kWave;
 // FP32: at least 4 waves per SIMD (at most 128 registers per lane) where that
 // needs no scratch memory (d <= 6, and d = 7 without a point source), else at
 // least 3 (168 registers); left free, the allocator may take a few more and
-// fall a wave lower.
+// fall a wave lower.  (Bounds of 5, 6 or 8 for d <= 5 change nothing: those
+// kernels need few registers as they are.)
 template <typename T, int D, bool SRC>
 constexpr int plain_waves()
 {
     return sizeof(T) != 4 ? 1 : (D < 7 || (D == 7 && !SRC)) ? 4 : 3;
 }
+constexpr int kLdsWaves = 4;  // waves per SIMD the record queue leaves room for
 
 template <typename T, int D, bool BWD, bool SRC, bool LISTS>
 __global__ void __launch_bounds__(kPlainBlock, (plain_waves<T, D, SRC>()))
@@ -36,7 +38,7 @@ plain_kernel(const EnvP<T>* penv, const T* __restrict__ queries, int64_t n_units
 {
     extern __shared__ __align__(16) unsigned char lds_all[];
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const WaveLds<T, SRC, LISTS, true> lds(lds_all + wv * wave_lds<T, SRC, LISTS, true>(D), D);
+    const WaveLds<T, SRC, LISTS, true> lds(lds_all + wv * wave_lds<T, SRC, LISTS, true>(D, kLdsWaves), D, kLdsWaves);
     const int64_t unit = (int64_t)blockIdx.x * (kPlainBlock / kWave) + wv;
     if (unit >= n_units) return;
     const int64_t q = unit / chunks;
@@ -57,7 +59,7 @@ static void plain_go(unsigned grid, const EnvP<T>* p, const T* queries, int64_t 
                      int64_t n_walks, int64_t w_base, uint32_t q_base, double* partials, double* records,
                      hipStream_t st)
 {
-    const size_t lds = (kPlainBlock / kWave) * wave_lds<T, SRC, LISTS, true>(D);
+    const size_t lds = (kPlainBlock / kWave) * wave_lds<T, SRC, LISTS, true>(D, kLdsWaves);
     hipLaunchKernelGGL((plain_kernel<T, D, BWD, SRC, LISTS>), dim3(grid), dim3(kPlainBlock), lds, st, p, queries, units,
                        chunks, wpu, n_walks, w_base, q_base, partials, records);
 }

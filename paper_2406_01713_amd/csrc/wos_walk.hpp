@@ -85,25 +85,22 @@ constexpr int kRecWord = REC ? 4 : 2;
 template <bool LISTS>
 constexpr int kScanLds = LISTS ? 2 * kWave : kPairLds;
 
-// LDS budget of a wave: 16 waves fill a CU's 160 KB.
-constexpr size_t kWaveLdsMax = 10240;
-
 // Queue entries and LDS bytes of a wave in a launch whose largest dimension
-// is d.
+// is d, at `waves` resident waves per SIMD of a CU's 160 KB.
 template <typename T, bool SRC, bool LISTS, bool REC>
-constexpr int rec_cap(int d)
+constexpr int rec_cap(int d, int waves)
 {
     const size_t fixed = (size_t)2 * d * kWave * sizeof(double) + kScanLds<LISTS> * sizeof(uint32_t);
     const size_t rec = kRecReal<SRC> * sizeof(T) + kRecWord<REC> * sizeof(uint32_t);
-    const size_t cap = (kWaveLdsMax - fixed) / rec;
+    const size_t cap = ((size_t)163840 / (4 * waves) / 64 * 64 - fixed) / rec;
     return cap > (size_t)kWave ? kWave : (int)cap;
 }
 template <typename T, bool SRC, bool LISTS, bool REC>
-constexpr size_t wave_lds(int d)
+constexpr size_t wave_lds(int d, int waves)
 {
     return ((size_t)2 * d * kWave * sizeof(double) + kScanLds<LISTS> * sizeof(uint32_t) +
-            rec_cap<T, SRC, LISTS, REC>(d) * (kRecReal<SRC> * sizeof(T) + kRecWord<REC> * sizeof(uint32_t)) + 15) /
-           16 * 16;
+            rec_cap<T, SRC, LISTS, REC>(d, waves) * (kRecReal<SRC> * sizeof(T) + kRecWord<REC> * sizeof(uint32_t)) +
+            15) / 16 * 16;
 }
 
 // The wave's slice, laid out for dimension `dim` (the launch's largest).
@@ -114,7 +111,8 @@ struct WaveLds {
     uint32_t* word;
     uint32_t* scan;
     int cap;
-    __device__ __forceinline__ WaveLds(unsigned char* base, int dim) : cap(rec_cap<T, SRC, LISTS, REC>(dim))
+    __device__ __forceinline__ WaveLds(unsigned char* base, int dim, int waves)
+        : cap(rec_cap<T, SRC, LISTS, REC>(dim, waves))
     {
         g = reinterpret_cast<double*>(base);
         real = reinterpret_cast<T*>(g + 2 * dim * kWave);
