@@ -422,7 +422,9 @@ int wos_autotune_batch(const wos_domain* const* envs, int n_envs, const float* q
  * M sphere obstacles and Q queries (fused forward + backward), recorded in
  * the cache file (JSON, created or updated) under the bucket of (d, M, Q).
  * Batched launches look up their batch mix first, then the bucket of their
- * heaviest environment, else use the built-in shape; the cache is read from
+ * heaviest environment, else use the built-in shape (launches of at most 262144
+ * walks: one walk per lane, and fewer walks per wave the fewer there are); the
+ * cache is read from
  * cache_path (or $WOS_AUTOTUNE_CACHE when wos_set_autotune_cache was not
  * called).  Blocks the calling thread (synchronises the device).
  */

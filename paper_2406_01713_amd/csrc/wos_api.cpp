@@ -776,18 +776,24 @@ void load_tune_locked(const char* path)
     fclose(f);
 }
 
-// The batch mix's entry, else the heaviest env's bucket, else the defaults.
-Tune lookup_tune(const char* mix, int d, int64_t M, int64_t Q)
+// The batch mix's entry, else the heaviest env's bucket; false: neither.
+bool lookup_tune(const char* mix, int d, int64_t M, int64_t Q, Tune& t)
 {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     if (!g_tune_loaded) load_tune_locked(getenv("WOS_AUTOTUNE_CACHE"));
     auto it = g_tune.find(mix);
-    if (it != g_tune.end()) return it->second;
+    if (it != g_tune.end()) {
+        t = it->second;
+        return true;
+    }
     char k[48];
     tune_key(k, d, M, Q);
     it = g_tune.find(k);
-    if (it != g_tune.end()) return it->second;
-    return Tune{};
+    if (it != g_tune.end()) {
+        t = it->second;
+        return true;
+    }
+    return false;
 }
 
 int save_tune_locked(const char* path)
@@ -834,12 +840,31 @@ void mix_key(char (&k)[48], const wos_domain* const* envs, const int64_t* q_off,
     snprintf(k, sizeof(k), "mix_%d_%016llx", n_envs, (unsigned long long)h);
 }
 
+constexpr int kSmallSpread = 8;  // lanes per walk at most (16: the same, 4: up to 4 % slower calls)
+
 struct BatchLayout {
     int64_t total_units = 0;
     int max_d = 2;
     int grid = 0;
     int block = 256;
 };
+
+// Shape of a launch that does not fill the device's walk-carrying lanes (4096
+// waves of 64): every walk then runs at once, the launch takes as long as its
+// longest walk, and what counts is the time of one step.  One walk per lane
+// (six environments of 1-13 queries x 1024 walks 1094 -> 882 us, one planning
+// start with 1e5 walks in 2-D 343 -> 311 us; 2^19 walks, two per lane, 2.03 ms
+// against 2.51 with one, so fuller launches keep two); and, while they still
+// fit five eighths of the lanes, fewer walks per wave, so that fewer
+// steps wait for some walk's end (882 -> 804 us with 16 per wave; 1e5 walks
+// with 32 per wave 1 % slower).
+void small_launch(int64_t walks, Tune& t)
+{
+    const int64_t lanes = 4096 * kWave;
+    if (walks > lanes) return;
+    t.walks_per_lane = 1;
+    while (t.lanes_per_walker < kSmallSpread && walks * t.lanes_per_walker * 2 <= lanes * 5 / 8) t.lanes_per_walker *= 2;
+}
 
 // Work units: each query's walks are split into `splits` ranges so that the
 // launch has about units_per_wave units per resident wave; envs are ordered
@@ -869,12 +894,14 @@ void plan_batch(const wos_domain* const* envs, const int64_t* q_off, int n_envs,
     }
     char mk[48];
     mix_key(mk, envs, q_off, n_envs, n_walks);
-    Tune t = lookup_tune(mk, heavy_d, maxM, heavyQ);
+    Tune t;
+    const bool tuned = lookup_tune(mk, heavy_d, maxM, heavyQ, t) || force;
     if (force && force->units_per_wave > 0) t.units_per_wave = force->units_per_wave;
     if (force && force->grid_mult > 0) t.grid_mult = force->grid_mult;
     if (force && force->walks_per_lane > 0) t.walks_per_lane = force->walks_per_lane;
     if (force && force->waves_per_block > 0) t.waves_per_block = force->waves_per_block;
     if (force && force->lanes_per_walker > 0) t.lanes_per_walker = force->lanes_per_walker;
+    if (!tuned) small_launch(sumQW, t);
     // walks a wave carries at once; the other lanes only share the member
     // scans of those walks (the pair rounds spread over all 64 lanes)
     const int64_t lanes = kWave / t.lanes_per_walker;
@@ -1590,12 +1617,16 @@ int wos_debug_cluster_boxes(int d, const wos_spheres* spheres, const wos_boxes* 
 }
 
 // Walks per wave of the plain kernel.  Up to one walk per lane of the 4096
-// resident waves (4 per SIMD), one per lane: every walk runs at once.  Above,
+// resident waves (4 per SIMD), one per lane (or spread wider: small_launch).  Above,
 // one range per resident wave (lanes refill) until a range holds 256 walks,
 // then ranges of 256 until each wave takes four, then a quarter of a wave's
 // share.
-static int32_t plain_range(int64_t Q, int64_t n_walks)
+static int32_t plain_range(int64_t Q, int64_t n_walks, int& lanes)
 {
+    Tune t;
+    small_launch(std::max<int64_t>(Q, 1) * n_walks, t);
+    lanes = kWave / t.lanes_per_walker;
+    if (lanes < kWave) return lanes;
     const double per = (double)std::max<int64_t>(Q, 1) * (double)n_walks / 4096.0;
     const double want = std::max(0.25 * per, std::min(256.0, per));
     const int64_t r = ((int64_t)std::min(std::ceil(want), 1e9) + kWave - 1) / kWave * kWave;
@@ -1625,7 +1656,8 @@ static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, in
     if (bwd && D->has_src && !(sigma > 0.0))
         return fail(WOS_ENOTSUP, "the sigma derivative of a point source is provided for sigma > 0 only");
     const int d = D->d;
-    const int32_t wpu = plain_range(Q, n_walks);
+    int lanes = kWave;
+    const int32_t wpu = plain_range(Q, n_walks, lanes);
     const int32_t chunks = (int32_t)((n_walks + wpu - 1) / wpu);
     Scratch S(st);
     double* partials = nullptr;
@@ -1650,7 +1682,7 @@ static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, in
         }
         EnvP<double>* pd;
         if ((rc = S.get(&pd, 1)) || (rc = upload(pd, &p, sizeof(p), st))) return rc;
-        WOS_HIP(launch_plain<double>(d, bwd, D->has_src, lists_ok(p), pd, (const double*)queries, Q, n_walks, wpu, 0, 0, partials, nullptr, st),
+        WOS_HIP(launch_plain<double>(d, bwd, D->has_src, lists_ok(p), pd, (const double*)queries, Q, n_walks, wpu, lanes, 0, 0, partials, nullptr, st),
                 "plain walk kernel");
         WOS_HIP(launch_finalize_plain<double>(d, bwd, partials, Q, chunks, n_walks, uo, (double*)out_grad, out_stats,
                                               (const double*)grad_u, (double*)out_dx, out_dq, prod, st),
@@ -1673,7 +1705,7 @@ static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, in
         }
         EnvP<float>* pd;
         if ((rc = S.get(&pd, 1)) || (rc = upload(pd, &p, sizeof(p), st))) return rc;
-        WOS_HIP(launch_plain<float>(d, bwd, D->has_src, lists_ok(p), pd, (const float*)queries, Q, n_walks, wpu, 0, 0, partials, nullptr, st),
+        WOS_HIP(launch_plain<float>(d, bwd, D->has_src, lists_ok(p), pd, (const float*)queries, Q, n_walks, wpu, lanes, 0, 0, partials, nullptr, st),
                 "plain walk kernel");
         if (o.flags & WOS_OUT_FP64)  // forward only: the FP64 sums written without rounding to FP32
             WOS_HIP(launch_finalize_plain<double>(d, false, partials, Q, chunks, n_walks, (double*)out_u,
@@ -1751,7 +1783,7 @@ int wos_debug_walks(const wos_domain* D, const double* query, uint32_t q_index, 
             if (!rc && e == hipSuccess) e = hipMalloc(&pd, sizeof(p));
             if (!rc && e == hipSuccess) e = hipMemcpy(pd, &p, sizeof(p), hipMemcpyHostToDevice);
             if (!rc && e == hipSuccess)
-                e = launch_plain<double>(d, true, D->has_src, lists_ok(p), (const EnvP<double>*)pd, (const double*)dq, 1, n, kWave, w0, q_index, part, rec, nullptr);
+                e = launch_plain<double>(d, true, D->has_src, lists_ok(p), (const EnvP<double>*)pd, (const double*)dq, 1, n, kWave, kWave, w0, q_index, part, rec, nullptr);
             if (e == hipSuccess) e = hipDeviceSynchronize();
             (void)hipFree(pd);
         } else {
@@ -1764,7 +1796,7 @@ int wos_debug_walks(const wos_domain* D, const double* query, uint32_t q_index, 
             if (!rc && e == hipSuccess) e = hipMalloc(&pd, sizeof(p));
             if (!rc && e == hipSuccess) e = hipMemcpy(pd, &p, sizeof(p), hipMemcpyHostToDevice);
             if (!rc && e == hipSuccess)
-                e = launch_plain<float>(d, true, D->has_src, lists_ok(p), (const EnvP<float>*)pd, (const float*)dq, 1, n, kWave, w0, q_index, part, rec, nullptr);
+                e = launch_plain<float>(d, true, D->has_src, lists_ok(p), (const EnvP<float>*)pd, (const float*)dq, 1, n, kWave, kWave, w0, q_index, part, rec, nullptr);
             if (e == hipSuccess) e = hipDeviceSynchronize();
             (void)hipFree(pd);
         }

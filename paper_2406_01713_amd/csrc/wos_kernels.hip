@@ -360,11 +360,11 @@ hipError_t launch_reduce_pairs(const double* prod, int64_t n, double* out0, doub
 
 template <typename T>
 hipError_t launch_plain(int d, bool bwd, bool src, bool lists, const EnvP<T>* p, const T* queries, int64_t n_q,
-                        int64_t n_walks, int32_t wpu, int64_t w_base, uint32_t q_base, double* partials,
+                        int64_t n_walks, int32_t wpu, int lanes, int64_t w_base, uint32_t q_base, double* partials,
                         double* records, hipStream_t st)
 {
 #define WOS_PLAIN_CASE(D) \
-    case D: return launch_plain_d<T, D>(bwd, src, lists, p, queries, n_q, n_walks, wpu, w_base, q_base, partials, records, st);
+    case D: return launch_plain_d<T, D>(bwd, src, lists, p, queries, n_q, n_walks, wpu, lanes, w_base, q_base, partials, records, st);
     switch (d) {
         WOS_PLAIN_CASE(2)
         WOS_PLAIN_CASE(3)
@@ -378,9 +378,9 @@ hipError_t launch_plain(int d, bool bwd, bool src, bool lists, const EnvP<T>* p,
 #undef WOS_PLAIN_CASE
 }
 template hipError_t launch_plain<float>(int, bool, bool, bool, const EnvP<float>*, const float*, int64_t, int64_t,
-                                        int32_t, int64_t, uint32_t, double*, double*, hipStream_t);
+                                        int32_t, int, int64_t, uint32_t, double*, double*, hipStream_t);
 template hipError_t launch_plain<double>(int, bool, bool, bool, const EnvP<double>*, const double*, int64_t, int64_t,
-                                         int32_t, int64_t, uint32_t, double*, double*, hipStream_t);
+                                         int32_t, int, int64_t, uint32_t, double*, double*, hipStream_t);
 
 hipError_t launch_persistent(bool bwd, bool src, bool lists, int grid, int block, const EnvP<float>* envs,
                              const BatchEnv* benv, int n_benv, int max_d, const float* queries, int64_t total_units,

@@ -22,11 +22,11 @@ bool lists_ok(const EnvP<T>& p)
 // or scan every obstacle (EnvP must be fit for it: lists_ok).
 template <typename T>
 hipError_t launch_plain(int d, bool bwd, bool src, bool lists, const EnvP<T>* p, const T* queries, int64_t n_q,
-                        int64_t n_walks, int32_t wpu, int64_t w_base, uint32_t q_base, double* partials,
+                        int64_t n_walks, int32_t wpu, int lanes, int64_t w_base, uint32_t q_base, double* partials,
                         double* records, hipStream_t st);
 template <typename T, int D>
 hipError_t launch_plain_d(bool bwd, bool src, bool lists, const EnvP<T>* p, const T* queries, int64_t n_q,
-                          int64_t n_walks, int32_t wpu, int64_t w_base, uint32_t q_base, double* partials,
+                          int64_t n_walks, int32_t wpu, int lanes, int64_t w_base, uint32_t q_base, double* partials,
                           double* records, hipStream_t st);
 
 // Per-query means / standard errors (and backward products) from the plain

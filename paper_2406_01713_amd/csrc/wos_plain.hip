@@ -32,7 +32,7 @@ constexpr int kLdsWaves = 4;  // waves per SIMD the record queue leaves room for
 
 template <typename T, int D, bool BWD, bool SRC, bool LISTS>
 __global__ void __launch_bounds__(kPlainBlock, (plain_waves<T, D, SRC>()))
-plain_kernel(const EnvP<T>* penv, const T* __restrict__ queries, int64_t n_units, int32_t chunks, int32_t wpu,
+plain_kernel(const EnvP<T>* penv, const T* __restrict__ queries, int64_t n_units, int32_t chunks, int32_t wpu, int lanes,
              int64_t n_walks, int64_t w_base, uint32_t q_base, double* __restrict__ partials,
              double* __restrict__ records)
 {
@@ -46,7 +46,7 @@ plain_kernel(const EnvP<T>* penv, const T* __restrict__ queries, int64_t n_units
     const cenv<T> p = (cenv<T>)penv;
     const int32_t n = (int32_t)(n_walks - w0 < wpu ? n_walks - w0 : wpu);
     run_unit<T, D, D, BWD, SRC, LISTS, true>(p, to_const(queries) + q * D, q_base + (uint32_t)q,
-                                             (uint32_t)(w_base + w0), n, kWave, p->key0, p->key1, lds,
+                                             (uint32_t)(w_base + w0), n, lanes, p->key0, p->key1, lds,
                                              partials + unit * nacc(D), records ? records + w0 * (D + 7) : nullptr);
 }
 
@@ -55,18 +55,18 @@ inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1)
 }  // namespace
 
 template <typename T, int D, bool BWD, bool SRC, bool LISTS>
-static void plain_go(unsigned grid, const EnvP<T>* p, const T* queries, int64_t units, int32_t chunks, int32_t wpu,
+static void plain_go(unsigned grid, const EnvP<T>* p, const T* queries, int64_t units, int32_t chunks, int32_t wpu, int lanes,
                      int64_t n_walks, int64_t w_base, uint32_t q_base, double* partials, double* records,
                      hipStream_t st)
 {
     const size_t lds = (kPlainBlock / kWave) * wave_lds<T, SRC, LISTS, true>(D, kLdsWaves);
     hipLaunchKernelGGL((plain_kernel<T, D, BWD, SRC, LISTS>), dim3(grid), dim3(kPlainBlock), lds, st, p, queries, units,
-                       chunks, wpu, n_walks, w_base, q_base, partials, records);
+                       chunks, wpu, lanes, n_walks, w_base, q_base, partials, records);
 }
 
 template <typename T, int D>
 hipError_t launch_plain_d(bool bwd, bool src, bool lists, const EnvP<T>* p, const T* queries, int64_t n_q,
-                          int64_t n_walks, int32_t wpu, int64_t w_base, uint32_t q_base, double* partials,
+                          int64_t n_walks, int32_t wpu, int lanes, int64_t w_base, uint32_t q_base, double* partials,
                           double* records, hipStream_t st)
 {
     const int32_t chunks = (int32_t)((n_walks + wpu - 1) / wpu);
@@ -76,13 +76,13 @@ hipError_t launch_plain_d(bool bwd, bool src, bool lists, const EnvP<T>* p, cons
                           : (lists ? plain_go<T, D, true, false, true> : plain_go<T, D, true, false, false>))
                    : (src ? (lists ? plain_go<T, D, false, true, true> : plain_go<T, D, false, true, false>)
                           : (lists ? plain_go<T, D, false, false, true> : plain_go<T, D, false, false, false>));
-    go(blocks_for(units, kPlainBlock / kWave), p, queries, units, chunks, wpu, n_walks, w_base, q_base, partials, records, st);
+    go(blocks_for(units, kPlainBlock / kWave), p, queries, units, chunks, wpu, lanes, n_walks, w_base, q_base, partials, records, st);
     return hipGetLastError();
 }
 
 #define WOS_PLAIN_INST(D)                                                                                             \
     template hipError_t launch_plain_d<WOS_PLAIN_T, D>(bool, bool, bool, const EnvP<WOS_PLAIN_T>*, const WOS_PLAIN_T*, \
-                                                       int64_t, int64_t, int32_t, int64_t, uint32_t, double*, double*, \
+                                                       int64_t, int64_t, int32_t, int, int64_t, uint32_t, double*, double*, \
                                                        hipStream_t);
 #if WOS_PLAIN_LOW
 WOS_PLAIN_INST(2)
