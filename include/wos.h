@@ -335,7 +335,7 @@ int wos_estimate_batch_noalloc(const wos_domain* const* envs, int n_envs, const 
 /*
  * wos_plan_create -- gradient-ascent planning loop (Sec. III, screened-harmonic
  * paths; Sec. VII step rule s = min(s_ub, d(x)/2)) captured once as a HIP graph
- * of [fused forward + backward walk kernel, finalize, update] on `stream`.
+ * of [walk kernel, finalize, update] on `stream`.
  *   x      device float, S x d start points, updated in place each step
  *   Step t uses key seed + t (t kept on the device, so replays need no host
  *   work); start s is query s of the walks.  The step direction is the unit

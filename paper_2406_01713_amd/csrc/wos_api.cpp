@@ -1826,11 +1826,7 @@ struct wos_plan {
     float* x = nullptr;
     float* u = nullptr;
     float* grad = nullptr;
-    float* ubar = nullptr;
-    float* dx = nullptr;
     float* dir = nullptr;
-    double* dsig = nullptr;
-    double* dg = nullptr;
     double* partials = nullptr;
     double* path_len = nullptr;
     int32_t* stalls = nullptr;
@@ -1847,7 +1843,7 @@ static void plan_free(wos_plan* P)
     if (!P) return;
     if (P->exec) (void)hipGraphExecDestroy(P->exec);
     if (P->graph) (void)hipGraphDestroy(P->graph);
-    void* bufs[] = {P->u, P->grad, P->ubar, P->dx, P->dir, P->dsig, P->dg, P->partials, P->path_len,
+    void* bufs[] = {P->u, P->grad, P->dir, P->partials, P->path_len,
                     P->stalls, P->status, P->step, P->counter, P->env, P->benv};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
@@ -1901,11 +1897,7 @@ int wos_plan_create(const wos_domain* D, float* x, int64_t n_starts, int64_t n_w
     const int64_t S = n_starts;
     if (e == hipSuccess) e = hipMalloc(&P->u, S * sizeof(float));
     if (e == hipSuccess) e = hipMalloc(&P->grad, S * kBatchStride * sizeof(float));
-    if (e == hipSuccess) e = hipMalloc(&P->ubar, S * sizeof(float));
-    if (e == hipSuccess) e = hipMalloc(&P->dx, S * kBatchStride * sizeof(float));
     if (e == hipSuccess) e = hipMalloc(&P->dir, S * kBatchStride * sizeof(float));
-    if (e == hipSuccess) e = hipMalloc(&P->dsig, sizeof(double));
-    if (e == hipSuccess) e = hipMalloc(&P->dg, sizeof(double));
     if (e == hipSuccess) e = hipMalloc(&P->partials, (size_t)std::max<int64_t>(L.total_units, 1) * nacc(kMaxDim) * sizeof(double));
     if (e == hipSuccess) e = hipMalloc(&P->path_len, S * sizeof(double));
     if (e == hipSuccess) e = hipMalloc(&P->stalls, S * sizeof(int32_t));
@@ -1921,19 +1913,19 @@ int wos_plan_create(const wos_domain* D, float* x, int64_t n_starts, int64_t n_w
     if (e == hipSuccess) e = launch_fill_u32((unsigned*)P->status, S, 0u, st);
     if (e == hipSuccess) e = launch_fill_u32((unsigned*)P->step, 2, 0u, st);
     if (e == hipSuccess) e = launch_fill_u32(P->counter, 1, 0u, st);
-    if (e == hipSuccess) e = launch_fill_u32((unsigned*)P->ubar, S, 0x3f800000u, st);  // upstream weights 1.0f
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
         plan_free(P);
         return hip_fail(e, "plan set-up");
     }
-    // capture [fused forward + backward walks, finalize, update]
+    // capture [walks, finalize, update]; the step needs no backward sums
     e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        hipError_t e1 = launch_persistent(true, D->has_src, lists_ok(P->henv), L.grid, L.block, P->env, P->benv, 1, L.max_d, x, L.total_units,
-                                          P->henv.key0, P->henv.key1, P->step, P->counter, P->partials, st);
-        hipError_t e2 = launch_finalize_batch(true, P->benv, 1, P->partials, P->ubar, P->u, P->grad,
-                                              kBatchStride, nullptr, P->dx, P->dsig, P->dg, P->dir, P->counter, st);
+        hipError_t e1 = launch_persistent(false, D->has_src, lists_ok(P->henv), L.grid, L.block, P->env, P->benv, 1,
+                                          L.max_d, x, L.total_units, P->henv.key0, P->henv.key1, P->step, P->counter,
+                                          P->partials, st);
+        hipError_t e2 = launch_finalize_batch(false, P->benv, 1, P->partials, nullptr, P->u, P->grad, kBatchStride,
+                                              nullptr, nullptr, nullptr, nullptr, P->dir, P->counter, st);
         hipError_t e3 = launch_plan_update(D->d, P->env, x, S, P->dir, kBatchStride, (float)s_ub, P->path_len,
                                            P->stalls, P->status, P->step, st);
         e = hipStreamEndCapture(st, &P->graph);
