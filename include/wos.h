@@ -256,6 +256,19 @@ int wos_backward(const wos_domain* dom, const void* queries, int64_t n_queries, 
                  const wos_options* opt, void* stream);
 
 /*
+ * wos_estimate_jac -- wos_estimate that also writes every query's derivatives,
+ * so that one pass over the walks serves the estimate and any later product
+ * with upstream weights (wos_backward walks again):
+ *   out_jac device double, Q x (d + 2): grad u, du/dsigma, du/dg_goal (the
+ *           means wos_backward weights by grad_u, before rounding)
+ * Other arguments as wos_estimate.  Errors: as wos_estimate and wos_backward;
+ * WOS_EINVAL without out_jac.
+ */
+int wos_estimate_jac(const wos_domain* dom, const void* queries, int64_t n_queries, int64_t n_walks,
+                     double sigma, double eps, uint64_t seed, void* out_u, void* out_grad,
+                     double* out_stats, double* out_jac, const wos_options* opt, void* stream);
+
+/*
  * wos_estimate_batch -- forward (grad_u == NULL) or fused forward + backward
  * over a ragged batch of environments in ONE persistent launch: a wave takes
  * a work unit (env, query, walk range) from a device counter and refills its

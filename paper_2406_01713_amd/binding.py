@@ -34,7 +34,7 @@ BATCH_STRIDE = WOS_BATCH_STRIDE
 MAX_DIM = 8
 
 EXPORTED = ["wos_create_domain", "wos_destroy_domain", "wos_domain_dim", "wos_estimate",
-            "wos_backward", "wos_estimate_batch", "wos_estimate_batch_noalloc", "wos_plan_create", "wos_plan_step",
+            "wos_estimate_jac", "wos_backward", "wos_estimate_batch", "wos_estimate_batch_noalloc", "wos_plan_create", "wos_plan_step",
             "wos_plan_buffers", "wos_plan_read", "wos_plan_destroy", "wos_autotune", "wos_autotune_batch",
             "wos_set_autotune_cache",
             "wos_debug_walks", "wos_debug_clusters", "wos_debug_cluster_boxes", "wos_varadhan", "wos_microbench",
@@ -103,6 +103,8 @@ def _load():
     L.wos_domain_dim.argtypes = [vp]
     L.wos_estimate.argtypes = [vp, vp, i64, i64, C.c_double, C.c_double, u64, vp, vp, vp,
                                C.POINTER(Options), vp]
+    L.wos_estimate_jac.argtypes = [vp, vp, i64, i64, C.c_double, C.c_double, u64, vp, vp, vp, vp,
+                                   C.POINTER(Options), vp]
     L.wos_backward.argtypes = [vp, vp, i64, i64, C.c_double, C.c_double, u64, vp, vp, vp, vp, vp,
                                C.POINTER(Options), vp]
     L.wos_estimate_batch.argtypes = [C.POINTER(vp), C.c_int, vp, C.POINTER(i64), dp, dp, C.POINTER(i64), u64,
@@ -248,6 +250,13 @@ def wos_estimate(dom, queries, n_walks, sigma, eps, seed, out_u, out_grad=None, 
     check(lib.wos_estimate(dom.handle, _ptr(queries), queries.shape[0], int(n_walks), float(sigma),
                            float(eps), int(seed), _ptr(out_u), _ptr(out_grad), _ptr(out_stats),
                            C.byref(opt) if opt is not None else None, _stream(stream)))
+
+
+def wos_estimate_jac(dom, queries, n_walks, sigma, eps, seed, out_u, out_grad, out_stats, out_jac, opt=None,
+                     stream=None):
+    check(lib.wos_estimate_jac(dom.handle, _ptr(queries), queries.shape[0], int(n_walks), float(sigma),
+                               float(eps), int(seed), _ptr(out_u), _ptr(out_grad), _ptr(out_stats), _ptr(out_jac),
+                               C.byref(opt) if opt is not None else None, _stream(stream)))
 
 
 def wos_backward(dom, queries, n_walks, sigma, eps, seed, grad_u, out_dx, out_dsigma, out_dg,

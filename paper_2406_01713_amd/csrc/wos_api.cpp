@@ -1636,7 +1636,7 @@ static int32_t plain_range(int64_t Q, int64_t n_walks, int& lanes)
 static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, int64_t n_walks, double sigma,
                          double eps, uint64_t seed, void* out_u, void* out_grad, double* out_stats,
                          const void* grad_u, void* out_dx, double* out_dsigma, double* out_dg, double* out_dq,
-                         const wos_options* opt, hipStream_t st, bool bwd)
+                         double* out_jac, const wos_options* opt, hipStream_t st, bool bwd)
 {
     if (!D) return fail(WOS_EINVAL, "domain is NULL");
     wos_options o;
@@ -1645,7 +1645,10 @@ static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, in
     if ((rc = check_device(D))) return rc;
     if (Q < 0 || Q > ((int64_t)1 << 32)) return fail(WOS_EINVAL, "n_queries out of range");
     if (n_walks < 1 || n_walks > ((int64_t)1 << 31)) return fail(WOS_EINVAL, "n_walks must be in [1, 2^31]");
-    if (bwd) {
+    // bwd without out_jac: products with grad_u (wos_backward); with it: the
+    // estimate and its unweighted derivatives (wos_estimate_jac)
+    const bool vjp = bwd && !out_jac;
+    if (vjp) {
         if (!out_dx || !out_dsigma || !out_dg) return fail(WOS_EINVAL, "out_dx, out_dsigma and out_dg are required");
         if (Q > 0 && !grad_u) return fail(WOS_EINVAL, "grad_u is required");
     } else if (Q > 0 && !out_u) {
@@ -1663,12 +1666,12 @@ static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, in
     double* partials = nullptr;
     double* prod = nullptr;
     if ((rc = S.get(&partials, (size_t)std::max<int64_t>(Q, 1) * chunks * nacc(d)))) return rc;
-    if (bwd && (rc = S.get(&prod, (size_t)std::max<int64_t>(Q, 1) * 2))) return rc;
+    if (vjp && (rc = S.get(&prod, (size_t)std::max<int64_t>(Q, 1) * 2))) return rc;
     if (o.flags & WOS_FP64) {
         EnvP<double> p;
         if ((rc = make_env<double>(D, sigma, eps, seed, o.env_id, o, p))) return rc;
         if (Q == 0) {
-            if (bwd) {
+            if (vjp) {
                 WOS_HIP(launch_fill_f64(out_dsigma, 1, 0.0, st), "fill");
                 WOS_HIP(launch_fill_f64(out_dg, 1, 0.0, st), "fill");
             }
@@ -1676,7 +1679,7 @@ static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, in
         }
         double* uo = (double*)out_u;
         double* uscratch = nullptr;
-        if (bwd && !uo) {
+        if (vjp && !uo) {
             if ((rc = S.get(&uscratch, (size_t)Q))) return rc;
             uo = uscratch;
         }
@@ -1685,13 +1688,13 @@ static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, in
         WOS_HIP(launch_plain<double>(d, bwd, D->has_src, lists_ok(p), pd, (const double*)queries, Q, n_walks, wpu, lanes, 0, 0, partials, nullptr, st),
                 "plain walk kernel");
         WOS_HIP(launch_finalize_plain<double>(d, bwd, partials, Q, chunks, n_walks, uo, (double*)out_grad, out_stats,
-                                              (const double*)grad_u, (double*)out_dx, out_dq, prod, st),
+                                              (const double*)grad_u, (double*)out_dx, out_dq, out_jac, prod, st),
                 "finalize");
     } else {
         EnvP<float> p;
         if ((rc = make_env<float>(D, sigma, eps, seed, o.env_id, o, p))) return rc;
         if (Q == 0) {
-            if (bwd) {
+            if (vjp) {
                 WOS_HIP(launch_fill_f64(out_dsigma, 1, 0.0, st), "fill");
                 WOS_HIP(launch_fill_f64(out_dg, 1, 0.0, st), "fill");
             }
@@ -1699,7 +1702,7 @@ static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, in
         }
         float* uo = (float*)out_u;
         float* uscratch = nullptr;
-        if (bwd && !uo) {
+        if (vjp && !uo) {
             if ((rc = S.get(&uscratch, (size_t)Q))) return rc;
             uo = uscratch;
         }
@@ -1709,14 +1712,14 @@ static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, in
                 "plain walk kernel");
         if (o.flags & WOS_OUT_FP64)  // forward only: the FP64 sums written without rounding to FP32
             WOS_HIP(launch_finalize_plain<double>(d, false, partials, Q, chunks, n_walks, (double*)out_u,
-                                                  (double*)out_grad, out_stats, nullptr, nullptr, nullptr, nullptr, st),
+                                                  (double*)out_grad, out_stats, nullptr, nullptr, nullptr, nullptr, nullptr, st),
                     "finalize");
         else
             WOS_HIP(launch_finalize_plain<float>(d, bwd, partials, Q, chunks, n_walks, uo, (float*)out_grad, out_stats,
-                                                 (const float*)grad_u, (float*)out_dx, out_dq, prod, st),
+                                                 (const float*)grad_u, (float*)out_dx, out_dq, out_jac, prod, st),
                     "finalize");
     }
-    if (bwd) WOS_HIP(launch_reduce_pairs(prod, Q, out_dsigma, out_dg, st), "reduce");
+    if (vjp) WOS_HIP(launch_reduce_pairs(prod, Q, out_dsigma, out_dg, st), "reduce");
     return WOS_OK;
 }
 
@@ -1725,7 +1728,16 @@ int wos_estimate(const wos_domain* dom, const void* queries, int64_t n_queries, 
                  const wos_options* opt, void* stream)
 {
     return estimate_impl(dom, queries, n_queries, n_walks, sigma, eps, seed, out_u, out_grad, out_stats, nullptr,
-                         nullptr, nullptr, nullptr, nullptr, opt, (hipStream_t)stream, false);
+                         nullptr, nullptr, nullptr, nullptr, nullptr, opt, (hipStream_t)stream, false);
+}
+
+int wos_estimate_jac(const wos_domain* dom, const void* queries, int64_t n_queries, int64_t n_walks, double sigma,
+                     double eps, uint64_t seed, void* out_u, void* out_grad, double* out_stats, double* out_jac,
+                     const wos_options* opt, void* stream)
+{
+    if (!out_jac) return fail(WOS_EINVAL, "out_jac is required");
+    return estimate_impl(dom, queries, n_queries, n_walks, sigma, eps, seed, out_u, out_grad, out_stats, nullptr,
+                         nullptr, nullptr, nullptr, nullptr, out_jac, opt, (hipStream_t)stream, true);
 }
 
 int wos_backward(const wos_domain* dom, const void* queries, int64_t n_queries, int64_t n_walks, double sigma,
@@ -1733,7 +1745,7 @@ int wos_backward(const wos_domain* dom, const void* queries, int64_t n_queries, 
                  double* out_dg_goal, double* out_dq, const wos_options* opt, void* stream)
 {
     return estimate_impl(dom, queries, n_queries, n_walks, sigma, eps, seed, nullptr, nullptr, nullptr, grad_u,
-                         out_dx, out_dsigma, out_dg_goal, out_dq, opt, (hipStream_t)stream, true);
+                         out_dx, out_dsigma, out_dg_goal, out_dq, nullptr, opt, (hipStream_t)stream, true);
 }
 
 int wos_estimate_batch(const wos_domain* const* envs, int n_envs, const float* queries, const int64_t* q_offsets,

@@ -32,7 +32,7 @@ __global__ void __launch_bounds__(kBlock)
 finalize_plain(const double* __restrict__ partials, int64_t n_q, int32_t chunks, int64_t n_walks,
                T* __restrict__ out_u, T* __restrict__ out_grad, double* __restrict__ out_stats,
                const T* __restrict__ ubar, T* __restrict__ out_dx, double* __restrict__ out_dq,
-               double* __restrict__ prod)
+               double* __restrict__ out_jac, double* __restrict__ prod)
 {
     // one block per query: thread t sums chunks t, t + kBlock, ... in order,
     // then a butterfly over each wave and the waves in index order, so the
@@ -79,7 +79,14 @@ finalize_plain(const double* __restrict__ partials, int64_t n_q, int32_t chunks,
         st[D + 2] = a[3 + 2 * D];
         st[D + 3] = a[4 + 2 * D];
     }
-    if (BWD) {
+    if (BWD && out_jac) {
+        double* j = out_jac + q * (D + 2);
+#pragma unroll
+        for (int i = 0; i < D; ++i) j[i] = a[2 + i] / n;
+        j[D] = a[5 + 2 * D] / n;
+        j[D + 1] = a[6 + 2 * D] / n;
+    }
+    if (BWD && ubar) {
         const double ub = (double)ubar[q];
         const double dqs = a[5 + 2 * D] / n, dqg = a[6 + 2 * D] / n;
         if (out_dq) {
@@ -314,43 +321,43 @@ inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1)
 template <typename T, int D>
 static hipError_t fin_d(bool bwd, const double* partials, int64_t n_q, int32_t chunks, int64_t n_walks,
                         T* out_u, T* out_grad, double* out_stats, const T* ubar, T* out_dx,
-                        double* out_dq, double* prod, hipStream_t st)
+                        double* out_dq, double* out_jac, double* prod, hipStream_t st)
 {
     if (n_q == 0) return hipSuccess;
     const unsigned grid = (unsigned)n_q;  // one block per query
     if (bwd)
         hipLaunchKernelGGL((finalize_plain<T, D, true>), dim3(grid), dim3(kBlock), 0, st, partials, n_q,
-                           chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, prod);
+                           chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, out_jac, prod);
     else
         hipLaunchKernelGGL((finalize_plain<T, D, false>), dim3(grid), dim3(kBlock), 0, st, partials, n_q,
-                           chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, prod);
+                           chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, out_jac, prod);
     return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_finalize_plain(int d, bool bwd, const double* partials, int64_t n_q, int32_t chunks,
                                  int64_t n_walks, T* out_u, T* out_grad, double* out_stats,
-                                 const T* ubar, T* out_dx, double* out_dq, double* prod,
-                                 hipStream_t st)
+                                 const T* ubar, T* out_dx, double* out_dq, double* out_jac,
+                                 double* prod, hipStream_t st)
 {
     switch (d) {
-    case 2: return fin_d<T, 2>(bwd, partials, n_q, chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, prod, st);
-    case 3: return fin_d<T, 3>(bwd, partials, n_q, chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, prod, st);
-    case 4: return fin_d<T, 4>(bwd, partials, n_q, chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, prod, st);
-    case 5: return fin_d<T, 5>(bwd, partials, n_q, chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, prod, st);
-    case 6: return fin_d<T, 6>(bwd, partials, n_q, chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, prod, st);
-    case 7: return fin_d<T, 7>(bwd, partials, n_q, chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, prod, st);
-    case 8: return fin_d<T, 8>(bwd, partials, n_q, chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, prod, st);
+    case 2: return fin_d<T, 2>(bwd, partials, n_q, chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, out_jac, prod, st);
+    case 3: return fin_d<T, 3>(bwd, partials, n_q, chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, out_jac, prod, st);
+    case 4: return fin_d<T, 4>(bwd, partials, n_q, chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, out_jac, prod, st);
+    case 5: return fin_d<T, 5>(bwd, partials, n_q, chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, out_jac, prod, st);
+    case 6: return fin_d<T, 6>(bwd, partials, n_q, chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, out_jac, prod, st);
+    case 7: return fin_d<T, 7>(bwd, partials, n_q, chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, out_jac, prod, st);
+    case 8: return fin_d<T, 8>(bwd, partials, n_q, chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, out_jac, prod, st);
     default: return hipErrorInvalidValue;
     }
 }
 
 template hipError_t launch_finalize_plain<float>(int, bool, const double*, int64_t, int32_t, int64_t, float*,
-                                                 float*, double*, const float*, float*, double*, double*,
+                                                 float*, double*, const float*, float*, double*, double*, double*,
                                                  hipStream_t);
 template hipError_t launch_finalize_plain<double>(int, bool, const double*, int64_t, int32_t, int64_t,
                                                   double*, double*, double*, const double*, double*,
-                                                  double*, double*, hipStream_t);
+                                                  double*, double*, double*, hipStream_t);
 
 hipError_t launch_reduce_pairs(const double* prod, int64_t n, double* out0, double* out1, hipStream_t st)
 {

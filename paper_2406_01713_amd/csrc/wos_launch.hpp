@@ -30,12 +30,14 @@ hipError_t launch_plain_d(bool bwd, bool src, bool lists, const EnvP<T>* p, cons
                           double* records, hipStream_t st);
 
 // Per-query means / standard errors (and backward products) from the plain
-// kernel's partials.  prod (Q x 2) receives grad_u[q] * (du/dsigma, du/dg).
+// kernel's partials.  With bwd: prod (Q x 2) receives grad_u[q] * (du/dsigma,
+// du/dg) where ubar is given, out_jac (Q x (d + 2), optional) the unweighted
+// FP64 means (grad u, du/dsigma, du/dg).
 template <typename T>
 hipError_t launch_finalize_plain(int d, bool bwd, const double* partials, int64_t n_q,
                                  int32_t chunks, int64_t n_walks, T* out_u, T* out_grad,
                                  double* out_stats, const T* ubar, T* out_dx, double* out_dq,
-                                 double* prod, hipStream_t st);
+                                 double* out_jac, double* prod, hipStream_t st);
 
 // Deterministic sum of the Q x 2 products into two scalars.
 hipError_t launch_reduce_pairs(const double* prod, int64_t n, double* out0, double* out1,
