@@ -27,43 +27,14 @@ __device__ __forceinline__ double se_of(double s, double s2, double n)
     return var > 0.0 ? ::sqrt(var / n) : 0.0;
 }
 
+// A query's outputs from its sums a (nacc(D) layout) over n_walks walks.
 template <typename T, int D, bool BWD>
-__global__ void __launch_bounds__(kBlock)
-finalize_plain(const double* __restrict__ partials, int64_t n_q, int32_t chunks, int64_t n_walks,
-               T* __restrict__ out_u, T* __restrict__ out_grad, double* __restrict__ out_stats,
-               const T* __restrict__ ubar, T* __restrict__ out_dx, double* __restrict__ out_dq,
-               double* __restrict__ out_jac, double* __restrict__ prod)
+__device__ __forceinline__ void write_query(const double (&a)[nacc(D)], int64_t q, int64_t n_walks,
+                                            T* __restrict__ out_u, T* __restrict__ out_grad,
+                                            double* __restrict__ out_stats, const T* __restrict__ ubar,
+                                            T* __restrict__ out_dx, double* __restrict__ out_dq,
+                                            double* __restrict__ out_jac, double* __restrict__ prod)
 {
-    // one block per query: thread t sums chunks t, t + kBlock, ... in order,
-    // then a butterfly over each wave and the waves in index order, so the
-    // result does not depend on timing
-    const int64_t q = blockIdx.x;
-    if (q >= n_q) return;
-    constexpr int NA = nacc(D);
-    constexpr int NW = kBlock / kWave;
-    __shared__ double wsum[NW][NA];
-    double a[NA];
-#pragma unroll
-    for (int i = 0; i < NA; ++i) a[i] = 0.0;
-    const double* row = partials + q * chunks * NA;
-    for (int c = threadIdx.x; c < chunks; c += kBlock) {
-#pragma unroll
-        for (int i = 0; i < NA; ++i) a[i] += row[(int64_t)c * NA + i];
-    }
-#pragma unroll
-    for (int i = 0; i < NA; ++i) a[i] = wave_sum(a[i]);
-    const int wv = threadIdx.x / kWave;
-    if ((threadIdx.x & (kWave - 1)) == 0) {
-#pragma unroll
-        for (int i = 0; i < NA; ++i) wsum[wv][i] = a[i];
-    }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
-        a[i] = wsum[0][i];
-        for (int w = 1; w < NW; ++w) a[i] += wsum[w][i];
-    }
     const double n = (double)n_walks;
     out_u[q] = (T)(a[0] / n);
     if (out_grad) {
@@ -98,6 +69,71 @@ finalize_plain(const double* __restrict__ partials, int64_t n_q, int32_t chunks,
 #pragma unroll
         for (int i = 0; i < D; ++i) out_dx[q * D + i] = (T)(ub * (a[2 + i] / n));
     }
+}
+
+// One block per query: thread t sums chunks t, t + kBlock, ... in order, then a
+// butterfly over each wave and the waves in index order, so the result does
+// not depend on timing.
+template <typename T, int D, bool BWD>
+__global__ void __launch_bounds__(kBlock)
+finalize_plain(const double* __restrict__ partials, int64_t n_q, int32_t chunks, int64_t n_walks,
+               T* __restrict__ out_u, T* __restrict__ out_grad, double* __restrict__ out_stats,
+               const T* __restrict__ ubar, T* __restrict__ out_dx, double* __restrict__ out_dq,
+               double* __restrict__ out_jac, double* __restrict__ prod)
+{
+    const int64_t q = blockIdx.x;
+    if (q >= n_q) return;
+    constexpr int NA = nacc(D);
+    constexpr int NW = kBlock / kWave;
+    __shared__ double wsum[NW][NA];
+    double a[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) a[i] = 0.0;
+    const double* row = partials + q * chunks * NA;
+    for (int c = threadIdx.x; c < chunks; c += kBlock) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) a[i] += row[(int64_t)c * NA + i];
+    }
+#pragma unroll
+    for (int i = 0; i < NA; ++i) a[i] = wave_sum(a[i]);
+    const int wv = threadIdx.x / kWave;
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) wsum[wv][i] = a[i];
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        a[i] = wsum[0][i];
+        for (int w = 1; w < NW; ++w) a[i] += wsum[w][i];
+    }
+    write_query<T, D, BWD>(a, q, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, out_jac, prod);
+}
+
+// Few chunks per query: one thread sums them in order.  (A block per query
+// whose sums are one row each spends 256 threads and their wave sums on it:
+// 16384 queries of one chunk in 2-D 124 us, a seventh of the whole call.)
+constexpr int kFewChunks = 8;
+template <typename T, int D, bool BWD>
+__global__ void __launch_bounds__(kWave)
+finalize_few(const double* __restrict__ partials, int64_t n_q, int32_t chunks, int64_t n_walks,
+             T* __restrict__ out_u, T* __restrict__ out_grad, double* __restrict__ out_stats,
+             const T* __restrict__ ubar, T* __restrict__ out_dx, double* __restrict__ out_dq,
+             double* __restrict__ out_jac, double* __restrict__ prod)
+{
+    const int64_t q = (int64_t)blockIdx.x * kWave + threadIdx.x;
+    if (q >= n_q) return;
+    constexpr int NA = nacc(D);
+    double a[NA];
+    const double* row = partials + q * chunks * NA;
+#pragma unroll
+    for (int i = 0; i < NA; ++i) a[i] = row[i];
+    for (int c = 1; c < chunks; ++c) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) a[i] += row[(int64_t)c * NA + i];
+    }
+    write_query<T, D, BWD>(a, q, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, out_jac, prod);
 }
 
 // Fixed-order block reduction (deterministic run to run).
@@ -324,13 +360,11 @@ static hipError_t fin_d(bool bwd, const double* partials, int64_t n_q, int32_t c
                         double* out_dq, double* out_jac, double* prod, hipStream_t st)
 {
     if (n_q == 0) return hipSuccess;
-    const unsigned grid = (unsigned)n_q;  // one block per query
-    if (bwd)
-        hipLaunchKernelGGL((finalize_plain<T, D, true>), dim3(grid), dim3(kBlock), 0, st, partials, n_q,
-                           chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, out_jac, prod);
-    else
-        hipLaunchKernelGGL((finalize_plain<T, D, false>), dim3(grid), dim3(kBlock), 0, st, partials, n_q,
-                           chunks, n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, out_jac, prod);
+    auto* go = chunks <= kFewChunks ? (bwd ? finalize_few<T, D, true> : finalize_few<T, D, false>)
+                                    : (bwd ? finalize_plain<T, D, true> : finalize_plain<T, D, false>);
+    const unsigned grid = chunks <= kFewChunks ? blocks_for(n_q, kWave) : (unsigned)n_q;
+    hipLaunchKernelGGL(go, dim3(grid), dim3(chunks <= kFewChunks ? kWave : kBlock), 0, st, partials, n_q, chunks,
+                       n_walks, out_u, out_grad, out_stats, ubar, out_dx, out_dq, out_jac, prod);
     return hipGetLastError();
 }
 
