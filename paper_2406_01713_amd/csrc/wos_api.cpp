@@ -1617,14 +1617,16 @@ int wos_debug_cluster_boxes(int d, const wos_spheres* spheres, const wos_boxes* 
 }
 
 // Walks per wave of the plain kernel.  Up to one walk per lane of the 4096
-// resident waves (4 per SIMD), one per lane (or spread wider: small_launch).  Above,
+// resident waves (4 per SIMD), one per lane, or in FP32 spread wider (small_launch;
+// FP64 steps are bound by issue even alone: 51200 5-D walks forward + backward
+// 2.36 ms spread over twice the waves, 2.19 not).  Above,
 // one range per resident wave (lanes refill) until a range holds 256 walks,
 // then ranges of 256 until each wave takes four, then a quarter of a wave's
 // share.
-static int32_t plain_range(int64_t Q, int64_t n_walks, int& lanes)
+static int32_t plain_range(int64_t Q, int64_t n_walks, bool fp64, int& lanes)
 {
     Tune t;
-    small_launch(std::max<int64_t>(Q, 1) * n_walks, t);
+    if (!fp64) small_launch(std::max<int64_t>(Q, 1) * n_walks, t);
     lanes = kWave / t.lanes_per_walker;
     if (lanes < kWave) return lanes;
     const double per = (double)std::max<int64_t>(Q, 1) * (double)n_walks / 4096.0;
@@ -1660,7 +1662,7 @@ static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, in
         return fail(WOS_ENOTSUP, "the sigma derivative of a point source is provided for sigma > 0 only");
     const int d = D->d;
     int lanes = kWave;
-    const int32_t wpu = plain_range(Q, n_walks, lanes);
+    const int32_t wpu = plain_range(Q, n_walks, (o.flags & WOS_FP64) != 0, lanes);
     const int32_t chunks = (int32_t)((n_walks + wpu - 1) / wpu);
     Scratch S(st);
     double* partials = nullptr;
