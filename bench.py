@@ -36,7 +36,6 @@ if ROOT not in sys.path:
 
 METRIC = "WoS walk-steps/s + ∇u queries/s at fixed std error (d=7), batched vs plain"
 PEAK_FP32_TFLOPS = 157.3   # MI355X FP32 vector peak (datasheet)
-PEAK_FP32_MFMA_TFLOPS = 157.3  # MI355X dense FP32 matrix-core peak (datasheet)
 JOB_CPU_SHARE = 16
 # one FP32 FMA per lane per cycle: 256 CUs x 4 SIMDs x 16 lanes x 2 FLOP x
 # 2.4 GHz; the datasheet figure counts packed FP32, which these kernels do
@@ -68,35 +67,21 @@ def distance_flops_per_step(s):
     return ms * (3 * d + 2) + mb * (5 * d + 1) + 4 * d
 
 
-def n_clusters(m):
-    """Clusters of 8 that a domain with m obstacles of one kind keeps (none
-    below 64 obstacles)."""
-    return -(-m // 8) if m >= 64 else 0
-
-
-MFMA_FLOP_PER_PAIR = 24  # 12 features x (multiply + add) per (walker, cluster) pair
-
-
 def executed_flops(s, st):
-    """Distance arithmetic that one env's walks actually executed, from the
-    work columns of the batched stats (per-walk means of sphere and box
-    member distances), split by the unit that runs it:
-      valu  member spheres 3d + 2, member boxes 5d + 1, cluster bounding
-            boxes 6d + 2 (per axis two differences, a three-way max, a
-            multiply-add; a square root and the margin), the goal 3d + 2 and
-            the outer box 4d per walk-step: the vector ALUs;
-      mfma  the cluster test, 16 clusters per matrix-core tile, 12-term dot
-            product per (walker, cluster) pair, for every cluster tile at
-            every walk-step: v_mfma_f32_16x16x4f32 (FP32 matrix cores).
-    Returns (valu, mfma, walk_steps)."""
+    """Distance arithmetic that one env's walks actually executed on the
+    vector ALUs, from the work columns of the batched stats (per-walk means):
+    sphere distances 3d + 2 (a listed goal ball among them), box distances
+    5d + 1, cluster bounding boxes 6d + 2 (per axis two differences, a
+    three-way max, a multiply-add; a square root and the margin), the outer
+    box 4d per walk-step and, where the obstacles are all scanned instead of
+    looked up in cell lists (column 14 is 0), the goal 3d + 2.  Returns
+    (valu, walk_steps)."""
     d, n = s["d"], s["n_walks"]
     steps = st[:, 9]
-    goal = 1.0 if s.get("goal_r") is not None else 0.0
+    goal = (st[:, 14] == 0) * (1.0 if s.get("goal_r") is not None else 0.0)
     valu = (st[:, 12] * (3 * d + 2) + st[:, 13] * (5 * d + 1) + st[:, 15] * (6 * d + 2)
             + steps * (goal * (3 * d + 2) + 4 * d)) * n
-    tiles = -(-n_clusters(len(s["sph_r"])) // 16) + -(-n_clusters(len(s["box_h"])) // 16)
-    mfma = steps * n * tiles * 16 * MFMA_FLOP_PER_PAIR
-    return float(valu.sum()), float(mfma.sum()), float((steps * n).sum())
+    return float(valu.sum()), float((steps * n).sum())
 
 
 def timed(fn, reps, torch, st):
@@ -284,14 +269,13 @@ def max_rel_diff(outs, ub, off):
 
 
 def launch_work(envs, off, stats):
-    """(walk-steps, VALU FLOP, MFMA FLOP) of a batched launch's stats."""
-    ws = valu = mfma = 0.0
+    """(walk-steps, VALU FLOP) of a batched launch's stats."""
+    ws = valu = 0.0
     for e, s in enumerate(envs):
-        v, m, w = executed_flops(s, stats[off[e]:off[e + 1]])
+        v, w = executed_flops(s, stats[off[e]:off[e + 1]])
         ws += w
         valu += v
-        mfma += m
-    return ws, valu, mfma
+    return ws, valu
 
 
 def ragged_c4(B, torch, st, reps=3, plain_reps=2, tune_cache=None):
@@ -309,15 +293,15 @@ def ragged_c4(B, torch, st, reps=3, plain_reps=2, tune_cache=None):
                                 cache_path=tune_cache)
     tune["search_s"] = time.perf_counter() - t
     fwd_ms, fwd_min = timed(lambda: bat.run(bwd=False), reps, torch, st)
-    ws_f, valu_f, mfma_f = launch_work(envs, bat.off, bat.st.cpu().numpy())
+    ws_f, valu_f = launch_work(envs, bat.off, bat.st.cpu().numpy())
     fused_ms, fused_min = timed(lambda: bat.run(), reps, torch, st)
     stats = bat.st.cpu().numpy()
-    ws, valu, mfma = launch_work(envs, bat.off, stats)
+    ws, valu = launch_work(envs, bat.off, stats)
     by_d = {}
     for d in range(2, 8):
         es = [e for e, s in enumerate(envs) if s["d"] == d]
         by_d[str(d)] = {"envs": len(es), "queries": int(sum(len(envs[e]["queries"]) for e in es)),
-                        "walk_steps": float(sum(executed_flops(envs[e], stats[bat.off[e]:bat.off[e + 1]])[2]
+                        "walk_steps": float(sum(executed_flops(envs[e], stats[bat.off[e]:bat.off[e + 1]])[1]
                                                 for e in es))}
     pl = Plain(B, envs, bat.doms, torch, bat.seed)
     pf_ms, _ = timed(lambda: pl.run(bwd=False), plain_reps, torch, st)
@@ -329,10 +313,9 @@ def ragged_c4(B, torch, st, reps=3, plain_reps=2, tune_cache=None):
            "envs": len(envs), "queries": int(bat.off[-1]), "walks": int(bat.off[-1]) * 2048,
            "walk_steps_per_step": ws, "by_d": by_d, "draw_s": draw_s, "repeats": reps,
            "forward": {"ms": fwd_ms, "ms_min": fwd_min, "walk_steps_per_s": ws_f / (fwd_ms / 1e3),
-                       "valu_tflops": valu_f / (fwd_ms / 1e3) / 1e12, "mfma_tflops": mfma_f / (fwd_ms / 1e3) / 1e12},
+                       "valu_tflops": valu_f / (fwd_ms / 1e3) / 1e12},
            "fused_fwd_bwd": {"ms": fused_ms, "ms_min": fused_min, "walk_steps_per_s": ws / (fused_ms / 1e3),
-                             "valu_tflops": valu / (fused_ms / 1e3) / 1e12,
-                             "mfma_tflops": mfma / (fused_ms / 1e3) / 1e12},
+                             "valu_tflops": valu / (fused_ms / 1e3) / 1e12},
            "plain": {"forward_ms": pf_ms, "backward_ms": pb_ms, "launches_per_pass": len(envs),
                      "forward_walk_steps_per_s": ws_f / (pf_ms / 1e3),
                      "fwd_plus_bwd_walk_steps_per_s": ws / ((pf_ms + pb_ms) / 1e3),
@@ -365,13 +348,13 @@ def c2_forward(B, torch, st, reps=3):
     ws_plain = float((sto.cpu().numpy()[:, d + 1] * s["n_walks"]).sum())
     bat = Batch(B, [s], torch)
     b_ms, b_min = timed(lambda: bat.run(bwd=False), reps, torch, st)
-    ws, valu, mfma = launch_work([s], bat.off, bat.st.cpu().numpy())
+    ws, valu = launch_work([s], bat.off, bat.st.cpu().numpy())
     assert abs(ws - ws_plain) <= 1e-9 * ws, (ws, ws_plain)  # the same walks
     res = {"workload": "d6: 4096 uniform free queries x 4096 walks, 256 spheres r U[0.1, 0.4], sigma 4, eps 1e-4, "
                        "FP32 forward u and grad u", "walk_steps_per_step": ws, "repeats": reps,
            "plain": {"ms": p_ms, "ms_min": p_min, "walk_steps_per_s": ws / (p_ms / 1e3)},
            "batched": {"ms": b_ms, "ms_min": b_min, "walk_steps_per_s": ws / (b_ms / 1e3),
-                       "valu_tflops": valu / (b_ms / 1e3) / 1e12, "mfma_tflops": mfma / (b_ms / 1e3) / 1e12},
+                       "valu_tflops": valu / (b_ms / 1e3) / 1e12},
            "grad_queries_per_s": Q / (b_ms / 1e3),
            "max_rel_diff_u_vs_batched": max_rel_diff([u], bat.u.cpu().numpy(), bat.off)}
     del bat
@@ -687,12 +670,11 @@ def main():
     log(f"batched fused fwd+bwd: {ms_step:.1f} ms/step")
 
     stats = bat.st.cpu().numpy()
-    walk_steps, valu, mfma = launch_work(envs, bat.off, stats)
+    walk_steps, valu = launch_work(envs, bat.off, stats)
     flops_full = sum(float((stats[bat.off[e]:bat.off[e + 1], 9] * s["n_walks"]).sum()) * distance_flops_per_step(s)
                      for e, s in enumerate(envs))
     value = walk_steps / (ms_step / 1e3)
     valu_rate = valu / (launch_ms / 1e3) / 1e12
-    mfma_rate = mfma / (launch_ms / 1e3) / 1e12
     khash = kernel_hash()
     counters = counter_entry(khash)
     ceilings = {}
@@ -717,20 +699,16 @@ def main():
                       "walks": int(sum(len(e["queries"]) * e["n_walks"] for e in envs)),
                       "walk_steps_per_step": walk_steps, "eps": 1e-4, "seed": int(bat.seed),
                       "obstacle_scan": "every obstacle" if args.full_scan else
-                                       "cluster-culled (exact: same walks as a full scan)"},
+                                       "cell lists (exact: same walks as a full scan)"},
            "roofline": {"bound": "alu", "achieved": valu_rate, "peak": PEAK_FP32_TFLOPS,
                         "unit": "TFLOP/s", "frac": valu_rate / PEAK_FP32_TFLOPS,
                         "traffic": counters.get("bytes_per_launch"),
-                        "basis": "distance arithmetic executed on the vector ALUs: member sphere (3d + 2) and "
-                                 "box (5d + 1) distances, cluster bounding-box tests (6d + 2) of the pairs the "
-                                 "matrix-core test keeps, the goal (3d + 2) and the outer box (4d) per "
-                                 "walk-step, counted by the kernel's work tallies; the cluster test runs on the "
-                                 "matrix cores and is reported under 'mfma'",
-                        "mfma": {"achieved": mfma_rate, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
-                                 "frac": mfma_rate / PEAK_FP32_MFMA_TFLOPS, "flops_per_launch": mfma,
-                                 "basis": "cluster tests (12-term dot product, 24 FLOP per walker and cluster) "
-                                          "for every 16-cluster tile at every walk-step, "
-                                          "v_mfma_f32_16x16x4f32; peak = MI355X dense FP32 matrix peak"},
+                        "basis": "distance arithmetic executed on the vector ALUs: sphere (3d + 2) and box "
+                                 "(5d + 1) distances of the cell lists (goal balls among them) or of full scans "
+                                 "below 64 obstacles (then plus the goal, 3d + 2), cluster bounding-box tests "
+                                 "(6d + 2) at the query points and the outer box (4d) per walk-step, counted by "
+                                 "the kernel's work tallies; random numbers, cell lookup, weights and sums are "
+                                 "not counted",
                         "valu_busy": counters.get("valu_busy"),
                         "valu_busy_basis": "share of cycles the vector ALUs issue (SQ_ACTIVE_INST_VALU, "
                                            "rocprofv3 on these kernel sources)",
