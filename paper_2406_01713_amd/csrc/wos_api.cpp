@@ -871,10 +871,11 @@ void small_launch(int64_t walks, Tune& t)
 // by decreasing unit cost (longest-processing-time first, ties in caller
 // order).  order (n_envs ints) is working storage; benv receives the
 // n_envs rows of the unit table.  force: launch-shape fields > 0 override
-// the tuned ones.
+// the tuned ones.  wave_cap: count at most that many resident waves (times
+// grid_mult) for the length of a unit; fewer waves, longer and fewer units.
 void plan_batch(const wos_domain* const* envs, const int64_t* q_off, int n_envs, const int64_t* n_walks,
                 int q_stride, const Tune* force, bool full_scan, bool src, bool lists, int* order, BatchEnv* benv,
-                BatchLayout& L)
+                BatchLayout& L, int64_t wave_cap = (int64_t)1 << 40)
 {
     int64_t sumQW = 0, maxM = 0, heavyQ = 0, maxW = 1;
     int heavy_d = 2;
@@ -910,7 +911,7 @@ void plan_batch(const wos_domain* const* envs, const int64_t* q_off, int n_envs,
     L.block = block;
     L.grid = std::max(1, resident_blocks * t.grid_mult);
     const int64_t waves = (int64_t)L.grid * (block / kWave);
-    const int64_t target = waves * t.units_per_wave;
+    const int64_t target = std::min(waves, wave_cap * t.grid_mult) * t.units_per_wave;
     // one walk-range length for the launch: total walks / target units, a
     // multiple of the walk-carrying lanes, at least walks_per_lane walks per
     // such lane
@@ -1082,6 +1083,14 @@ int run_batch(const wos_domain* const* envs, int n_envs, const float* queries, c
     BatchLayout L;
     plan_batch(envs, q_offsets, n_envs, n_walks, kBatchStride, force, (o.flags & WOS_FULL_SCAN) != 0, src, lists, order, hb,
                L);
+    const size_t off_tab = 256, off_part = align256(off_tab + tab_bytes);
+    // five resident waves per SIMD (d <= 5) ask for a quarter more units than
+    // four; a batch whose rows outgrow the fixed array by that is split as for
+    // four, so the array's limit does not depend on the kernel's occupancy
+    const int64_t rows = ((int64_t)WOS_NOALLOC_SCRATCH_BYTES - (int64_t)off_part) / (int64_t)(nacc(kMaxDim) * sizeof(double));
+    if (fixed && L.total_units > rows)
+        plan_batch(envs, q_offsets, n_envs, n_walks, kBatchStride, force, (o.flags & WOS_FULL_SCAN) != 0, src, lists, order,
+                   hb, L, 4096);
     // the kernel hands out units with a 32-bit device counter
     if (L.total_units >= ((int64_t)1 << 32) - 1)
         return fail(WOS_EINVAL, "the batch splits into %lld work units; at most 2^32 - 2", (long long)L.total_units);
@@ -1092,7 +1101,6 @@ int run_batch(const wos_domain* const* envs, int n_envs, const float* queries, c
     double* partials;
     unsigned* counter;
     if (fixed) {
-        const size_t off_tab = 256, off_part = align256(off_tab + tab_bytes);
         const size_t need = off_part + part_bytes;
         if (need > (size_t)WOS_NOALLOC_SCRATCH_BYTES)
             return fail(WOS_EINVAL,
