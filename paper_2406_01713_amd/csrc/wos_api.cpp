@@ -813,15 +813,17 @@ int save_tune_locked(const char* path)
     return WOS_OK;
 }
 
+// Typical walk length by dimension.
+constexpr double kWalkSteps[kMaxDim + 1] = {0, 0, 12, 25, 40, 55, 71, 85, 95};
+
 // Relative cost of one work unit of an env: obstacle work per walk step
 // times a typical walk length times the walks of the unit.
 double unit_cost(const wos_domain* D, int64_t wps)
 {
-    static const double steps[9] = {0, 0, 12, 25, 40, 55, 71, 85, 95};
     const int d = D->d;
     const double per_step = (double)D->n_sph * (2 * d + 3) + (double)D->n_box * (5 * d + 4) +
                             (double)D->n_arm * d * 12 + 150.0 * ((d + 3) / 4);
-    return per_step * steps[d] * (double)wps;
+    return per_step * kWalkSteps[d] * (double)wps;
 }
 
 // Key of a batch mix: the sum over envs of a hash of (d, log2 buckets of
@@ -871,18 +873,20 @@ void small_launch(int64_t walks, Tune& t)
 // by decreasing unit cost (longest-processing-time first, ties in caller
 // order).  order (n_envs ints) is working storage; benv receives the
 // n_envs rows of the unit table.  force: launch-shape fields > 0 override
-// the tuned ones.  wave_cap: count at most that many resident waves (times
-// grid_mult) for the length of a unit; fewer waves, longer and fewer units.
+// the tuned ones.  fewest: ranges of equal walks for four waves per SIMD at
+// most, so that the number of units depends on the sizes alone.
 void plan_batch(const wos_domain* const* envs, const int64_t* q_off, int n_envs, const int64_t* n_walks,
                 int q_stride, const Tune* force, bool full_scan, bool src, bool lists, int* order, BatchEnv* benv,
-                BatchLayout& L, int64_t wave_cap = (int64_t)1 << 40)
+                BatchLayout& L, bool fewest = false)
 {
     int64_t sumQW = 0, maxM = 0, heavyQ = 0, maxW = 1;
+    double sum_steps = 0;
     int heavy_d = 2;
     double heavy = -1;
     for (int e = 0; e < n_envs; ++e) {
         const int64_t q = q_off[e + 1] - q_off[e];
         sumQW += q * n_walks[e];
+        sum_steps += (double)q * (double)n_walks[e] * kWalkSteps[envs[e]->d];
         maxW = std::max(maxW, n_walks[e]);
         L.max_d = std::max(L.max_d, envs[e]->d);
         const double c = unit_cost(envs[e], n_walks[e]) * (double)q;
@@ -911,20 +915,26 @@ void plan_batch(const wos_domain* const* envs, const int64_t* q_off, int n_envs,
     L.block = block;
     L.grid = std::max(1, resident_blocks * t.grid_mult);
     const int64_t waves = (int64_t)L.grid * (block / kWave);
-    const int64_t target = std::min(waves, wave_cap * t.grid_mult) * t.units_per_wave;
-    // one walk-range length for the launch: total walks / target units, a
-    // multiple of the walk-carrying lanes, at least walks_per_lane walks per
-    // such lane
-    // (default 2, so lanes refill).  Measured: on the 7-D planning step
+    const int64_t target = (fewest ? std::min<int64_t>(waves, 4096 * t.grid_mult) : waves) * t.units_per_wave;
+    // walk ranges of about equal steps: the launch's steps / target units,
+    // over the typical walk length of the env's dimension; a multiple of the
+    // walk-carrying lanes, at least walks_per_lane walks per such lane
+    // (default 2, so lanes refill).  With ranges of equal walks the 7-D units
+    // of a batch of 40 envs, d = 2..7, took several times the others' time and
+    // the launch waited for the last of them (five such batches 13.6 to 21.3
+    // ms; equal steps 13.7 to 15.2).  Batches of one dimension are cut alike
+    // either way.  Measured for walks_per_lane: on the 7-D planning step
     // (524288 walks, 4096 resident waves) 2 per lane beat 4 by 25 % (half the
     // waves had been idle) and 1 by 7 %; on one-start planning with 1e5 walks
     // 2 beat 1 by 5-20 % (a wave with one walk per lane waits for its longest
     // of 64 walks).
-    int64_t wps = std::max<int64_t>((int64_t)t.walks_per_lane * lanes, sumQW / std::max<int64_t>(target, 1));
-    wps = std::min(wps, maxW);
-    wps = ((wps + lanes - 1) / lanes) * lanes;
-
-    auto env_wps = [&](int e) { return std::min<int64_t>(wps, ((n_walks[e] + lanes - 1) / lanes) * lanes); };
+    auto env_wps = [&](int e) {
+        const double share = fewest ? (double)sumQW : sum_steps / kWalkSteps[envs[e]->d];
+        int64_t w = std::max<int64_t>((int64_t)t.walks_per_lane * lanes, (int64_t)(share / (double)std::max<int64_t>(target, 1)));
+        w = std::min(w, maxW);
+        w = ((w + lanes - 1) / lanes) * lanes;
+        return std::min<int64_t>(w, ((n_walks[e] + lanes - 1) / lanes) * lanes);
+    };
     auto cost = [&](int e) {
         return q_off[e + 1] > q_off[e] ? unit_cost(envs[e], env_wps(e)) : -1.0;
     };
@@ -1085,12 +1095,13 @@ int run_batch(const wos_domain* const* envs, int n_envs, const float* queries, c
                L);
     const size_t off_tab = 256, off_part = align256(off_tab + tab_bytes);
     // five resident waves per SIMD (d <= 5) ask for a quarter more units than
-    // four; a batch whose rows outgrow the fixed array by that is split as for
-    // four, so the array's limit does not depend on the kernel's occupancy
+    // four, ranges of equal steps for more where the long queries have the
+    // longer walks; a batch whose rows outgrow the fixed array by that is cut
+    // into fewer, so the array's limit depends on the sizes alone
     const int64_t rows = ((int64_t)WOS_NOALLOC_SCRATCH_BYTES - (int64_t)off_part) / (int64_t)(nacc(kMaxDim) * sizeof(double));
     if (fixed && L.total_units > rows)
         plan_batch(envs, q_offsets, n_envs, n_walks, kBatchStride, force, (o.flags & WOS_FULL_SCAN) != 0, src, lists, order,
-                   hb, L, 4096);
+                   hb, L, true);
     // the kernel hands out units with a 32-bit device counter
     if (L.total_units >= ((int64_t)1 << 32) - 1)
         return fail(WOS_EINVAL, "the batch splits into %lld work units; at most 2^32 - 2", (long long)L.total_units);
