@@ -1598,10 +1598,12 @@ template <bool SRC, bool BWD, int DA>
 __device__ __forceinline__ void renormalize(Walker<double, DA>&) {}
 
 // The step from x_k: weight, jump, k + 1.  (key0, key1) is the Philox key of
-// the launch, walk and q the walk's and the query's index words.
+// the launch, walk and q the walk's and the query's index words.  Lanes with
+// live false run along; their R depends on what the scan skipped for them, so
+// nothing here may turn on it for the others.
 template <typename T, int D, bool BWD, bool SRC>
-__device__ __forceinline__ void walker_move(cenv<T> p0, Walker<T, D>& s, uint32_t walk, uint32_t q, uint32_t env,
-                                            uint32_t key0, uint32_t key1)
+__device__ __forceinline__ void walker_move(cenv<T> p0, Walker<T, D>& s, bool live, uint32_t walk, uint32_t q,
+                                            uint32_t env, uint32_t key0, uint32_t key1)
 {
     const T(&x)[D] = s.x;
     const T R = s.R;
@@ -1614,7 +1616,7 @@ __device__ __forceinline__ void walker_move(cenv<T> p0, Walker<T, D>& s, uint32_
             const T t = p->src_z[i] - x[i];
             dz2 = Math<T>::fma(t, t, dz2);
         }
-        if (dz2 < R * R) {
+        if (live && dz2 < R * R) {
             const T r = Math<T>::sqrt(dz2);
             const SourceTerm<T> sg = ball_green<T, D, BWD>(p, r, R);
             p = fresh(p0);
@@ -1628,21 +1630,26 @@ __device__ __forceinline__ void walker_move(cenv<T> p0, Walker<T, D>& s, uint32_
     }
     const T R2 = R * R;
     const T y = p->qsigma * R2;
-    T F, F1 = T(1);  // 0F1(; d/2; y), and of d/2 + 1 where the backward sums need it
-    if (__builtin_amdgcn_ballot_w64(y > p->y_short) == 0) {
-        // straight-line short series, both at once: a loop over all terms
-        // waits for its coefficients every four of them
-        constexpr int N = kShortTerms<T>;
-        F = p->cC[N - 1];
-        F1 = BWD ? p->cC1[N - 1] : T(1);
+    // 0F1(; d/2; y), and of d/2 + 1 where the backward sums need it: the short
+    // series, straight-line and both at once (a loop over all terms waits for
+    // its coefficients every four of them).  A walk past its range takes the
+    // full one; the two differ in the last bit, so the choice is the walk's own,
+    // whichever walks share its wave.
+    constexpr int N = kShortTerms<T>;
+    T F = p->cC[N - 1], F1 = BWD ? p->cC1[N - 1] : T(1);
 #pragma unroll
-        for (int i = N - 2; i >= 0; --i) {
-            F = Math<T>::fma(F, y, p->cC[i]);
-            if (BWD) F1 = Math<T>::fma(F1, y, p->cC1[i]);
+    for (int i = N - 2; i >= 0; --i) {
+        F = Math<T>::fma(F, y, p->cC[i]);
+        if (BWD) F1 = Math<T>::fma(F1, y, p->cC1[i]);
+    }
+    const bool full = live && y > p->y_short;
+    if (__builtin_amdgcn_ballot_w64(full) != 0) {  // wave-uniform
+        const T G = horner<T>(p->cC, p->nt_C, y);
+        F = full ? G : F;
+        if (BWD) {
+            const T G1 = horner<T>(p->cC1, p->nt_C1, y);
+            F1 = full ? G1 : F1;
         }
-    } else {
-        F = horner<T>(p->cC, p->nt_C, y);
-        if (BWD) F1 = horner<T>(p->cC1, p->nt_C1, y);
     }
     const T C = Math<T>::rcp(F);
     s.W *= C;

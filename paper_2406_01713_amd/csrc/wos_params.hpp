@@ -78,8 +78,8 @@ constexpr int kStepBoundMaxDim = 5;
 // (see build_cluster_boxes) and rounded outwards.
 constexpr int kClusterBox = 2 * kMaxDim;
 
-// Weight-series terms of a step whose walkers all have sigma R^2 / 4 at most
-// y_short: the tail is below the series' own tolerance (1e-9 in FP32, 1e-18 in
+// Weight-series terms of a step from a point with sigma R^2 / 4 at most
+// y_short (the walk's own; the wave's other lanes do not matter): the tail is below the series' own tolerance (1e-9 in FP32, 1e-18 in
 // FP64, relative), as the full count's is at the largest possible R.
 template <typename T>
 constexpr int kShortTerms = sizeof(T) == 4 ? 8 : 16;

@@ -181,7 +181,7 @@ __device__ __forceinline__ void run_unit(cenv<T> p, cptr<T> qrow, uint32_t q, ui
         Near<T> near = {};
         uint64_t m = 0;
         if (any) {
-            walker_move<T, D, BWD, SRC>(p, s, id0 + (uint32_t)s.w, q, env, k0, k1);
+            walker_move<T, D, BWD, SRC>(p, s, active, id0 + (uint32_t)s.w, q, env, k0, k1);
             // R(x) is a minimum of distances, each 1-Lipschitz, and the walker
             // moved R: the next R is at most 2 R, and with the margins (rb_abs
             // covers the rounding of the positions and of every component's
