@@ -262,7 +262,8 @@ int wos_backward(const wos_domain* dom, const void* queries, int64_t n_queries, 
  *   out_jac device double, Q x (d + 2): grad u, du/dsigma, du/dg_goal (the
  *           means wos_backward weights by grad_u, before rounding)
  * Other arguments as wos_estimate.  Errors: as wos_estimate and wos_backward;
- * WOS_EINVAL without out_jac.
+ * WOS_EINVAL without out_jac (which may be NULL, as the other outputs, for no
+ * queries).
  */
 int wos_estimate_jac(const wos_domain* dom, const void* queries, int64_t n_queries, int64_t n_walks,
                      double sigma, double eps, uint64_t seed, void* out_u, void* out_grad,

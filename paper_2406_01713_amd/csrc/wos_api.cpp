@@ -1657,7 +1657,7 @@ static int32_t plain_range(int64_t Q, int64_t n_walks, bool fp64, int& lanes)
 static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, int64_t n_walks, double sigma,
                          double eps, uint64_t seed, void* out_u, void* out_grad, double* out_stats,
                          const void* grad_u, void* out_dx, double* out_dsigma, double* out_dg, double* out_dq,
-                         double* out_jac, const wos_options* opt, hipStream_t st, bool bwd)
+                         double* out_jac, const wos_options* opt, hipStream_t st, bool bwd, bool jac = false)
 {
     if (!D) return fail(WOS_EINVAL, "domain is NULL");
     wos_options o;
@@ -1666,15 +1666,16 @@ static int estimate_impl(const wos_domain* D, const void* queries, int64_t Q, in
     if ((rc = check_device(D))) return rc;
     if (Q < 0 || Q > ((int64_t)1 << 32)) return fail(WOS_EINVAL, "n_queries out of range");
     if (n_walks < 1 || n_walks > ((int64_t)1 << 31)) return fail(WOS_EINVAL, "n_walks must be in [1, 2^31]");
-    // bwd without out_jac: products with grad_u (wos_backward); with it: the
-    // estimate and its unweighted derivatives (wos_estimate_jac)
-    const bool vjp = bwd && !out_jac;
+    // bwd: products with grad_u (wos_backward), or with jac the estimate and its
+    // unweighted derivatives (wos_estimate_jac)
+    const bool vjp = bwd && !jac;
     if (vjp) {
         if (!out_dx || !out_dsigma || !out_dg) return fail(WOS_EINVAL, "out_dx, out_dsigma and out_dg are required");
         if (Q > 0 && !grad_u) return fail(WOS_EINVAL, "grad_u is required");
     } else if (Q > 0 && !out_u) {
         return fail(WOS_EINVAL, "out_u is required");
     }
+    if (jac && Q > 0 && !out_jac) return fail(WOS_EINVAL, "out_jac is required");
     if (Q > 0 && !queries) return fail(WOS_EINVAL, "queries is NULL");
     if (bwd && (o.flags & WOS_OUT_FP64)) return fail(WOS_ENOTSUP, "WOS_OUT_FP64 applies to wos_estimate only");
     if (bwd && D->has_src && !(sigma > 0.0))
@@ -1756,9 +1757,8 @@ int wos_estimate_jac(const wos_domain* dom, const void* queries, int64_t n_queri
                      double eps, uint64_t seed, void* out_u, void* out_grad, double* out_stats, double* out_jac,
                      const wos_options* opt, void* stream)
 {
-    if (!out_jac) return fail(WOS_EINVAL, "out_jac is required");
     return estimate_impl(dom, queries, n_queries, n_walks, sigma, eps, seed, out_u, out_grad, out_stats, nullptr,
-                         nullptr, nullptr, nullptr, nullptr, out_jac, opt, (hipStream_t)stream, true);
+                         nullptr, nullptr, nullptr, nullptr, out_jac, opt, (hipStream_t)stream, true, true);
 }
 
 int wos_backward(const wos_domain* dom, const void* queries, int64_t n_queries, int64_t n_walks, double sigma,

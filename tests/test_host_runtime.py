@@ -1,0 +1,69 @@
+"""Host-side behaviour of the library around its GPU calls, on a stand-in for
+the HIP runtime (fake_hip.c: device memory is host memory, kernels do not run,
+every launch takes the same time).  Each check runs in a process of its own,
+which loads the stand-in before the library."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+HEAD = """
+import ctypes as C, sys
+F = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+F.fake_hip_log.restype = C.c_char_p
+F.fake_hip_fail_above.argtypes = [C.c_size_t]
+import numpy as np
+from paper_2406_01713_amd import binding as B, scenes as S
+
+def launches(name):
+    return [tuple(map(int, l.split()[1:])) + (l.split()[0],) for l in F.fake_hip_log().decode().splitlines() if name in l]
+
+def batch(dom, d, Q, n_walks, call="estimate"):
+    off, one = np.array([0, Q], dtype=np.int64), np.ones(1)
+    q, u = np.zeros((Q, 8), np.float32), np.zeros(Q, np.float32)
+    nw = np.array([n_walks], dtype=np.int64)
+    i64p, p = C.POINTER(C.c_int64), lambda a: a.ctypes.data_as(C.c_void_p)
+    hs = (C.c_void_p * 1)(dom.handle.value)
+    if call == "estimate":
+        return B.check(B.lib.wos_estimate_batch(hs, 1, p(q), off.ctypes.data_as(i64p), B._dp(one), B._dp(0.01 * one),
+                                                nw.ctypes.data_as(i64p), 1, p(u), None, None, None, None, None, None,
+                                                None, None))
+    r = B.TuneResult()
+    B.check(B.lib.wos_autotune_batch(hs, 1, p(q), off.ctypes.data_as(i64p), B._dp(one), B._dp(0.01 * one),
+                                     nw.ctypes.data_as(i64p), 1, 0, None, C.byref(r)))
+    return r
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("hip") / "fake_hip.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(ROOT, "tests", "fake_hip.c")], check=True)
+
+    def go(code):
+        r = subprocess.run([sys.executable, "-c", HEAD + code, so], cwd=ROOT, capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, r.stdout + r.stderr
+        return r.stdout
+    return go
+
+
+def test_jac_takes_no_queries(run):
+    """No query rows: there is nothing to write, so the (empty) outputs may be
+    NULL, as in wos_estimate; with rows the derivatives' array is required."""
+    run("""
+dom = B.Domain(S.scene_spheres(3, m_sph=8, n_queries=1))
+for fp64 in (False, True):
+    opt = C.byref(B.options(fp64))
+    assert B.lib.wos_estimate(dom.handle, None, 0, 8, 1.0, 1e-3, 1, None, None, None, opt, None) == 0
+    assert B.lib.wos_estimate_jac(dom.handle, None, 0, 8, 1.0, 1e-3, 1, None, None, None, None, opt, None) == 0
+assert not launches("kernel")
+q = np.zeros((1, 3))
+p = q.ctypes.data_as(C.c_void_p)
+assert B.lib.wos_estimate_jac(dom.handle, p, 1, 8, 1.0, 1e-3, 1, p, None, None, None, None, None) == B.WOS_EINVAL
+assert b"out_jac" in B.lib.wos_last_error()
+assert B.lib.wos_estimate_jac(dom.handle, p, 1, 8, 1.0, 1e-3, 1, None, None, None, p, None, None) == B.WOS_EINVAL
+assert b"out_u" in B.lib.wos_last_error()
+""")
