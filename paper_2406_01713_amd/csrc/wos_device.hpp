@@ -1663,15 +1663,20 @@ __device__ __forceinline__ void walker_move(cenv<T> p0, Walker<T, D>& s, bool li
     s.k = k + 1;
 }
 
-// The sums' part of a walk absorbed at x with the distances near.
-template <typename T, int D, bool LISTS, bool SRC>
-__device__ __forceinline__ WalkEnd<T> walker_end(cenv<T> p, const Walker<T, D>& s, const Near<T>& near, T gfac,
-                                                 int& cls)
+// Component of the boundary nearest to the point x of a walk that ends there.
+template <typename T, int D, bool LISTS>
+__device__ __forceinline__ int end_cls(cenv<T> p, const T (&x)[D], const Near<T>& near)
 {
     // a listed goal's distance is in near.ds; it is the nearest if it attains it
     Near<T> at = near;
-    if (LISTS && p->goal_listed) at.dg = goal_dist<T, D>(p, s.x);
-    cls = at.cls();
+    if (LISTS && p->goal_listed) at.dg = goal_dist<T, D>(p, x);
+    return at.cls();
+}
+
+// The sums' part of a walk absorbed at x by component cls.
+template <typename T, int D, bool LISTS, bool SRC>
+__device__ __forceinline__ WalkEnd<T> walker_end(cenv<T> p, const Walker<T, D>& s, int cls, T gfac)
+{
     const T g = boundary_value<T, D, LISTS>(p, s.x, cls);
     WalkEnd<T> e;
     e.ex = s.ex;

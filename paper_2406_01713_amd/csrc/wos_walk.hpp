@@ -256,8 +256,8 @@ __device__ __forceinline__ void run_unit(cenv<T> p, cptr<T> qrow, uint32_t q, ui
             if (fin && rank >= from && rank < from + take) {
                 WalkEnd<T> e = {};
                 const bool cut = !(s.R < eps);  // truncated: contributes nothing
-                int cls = near.cls();
-                if (!cut) e = walker_end<T, D, LISTS, SRC>(fresh(p), s, near, st.gfac, cls);
+                const int cls = end_cls<T, D, LISTS>(fresh(p), s.x, near);
+                if (!cut) e = walker_end<T, D, LISTS, SRC>(fresh(p), s, cls, st.gfac);
                 const int at = qn + rank - from;
                 T* r = lds.real + at;
                 uint32_t* wd = lds.word + at;
