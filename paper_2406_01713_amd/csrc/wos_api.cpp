@@ -1497,13 +1497,19 @@ int wos_create_domain(int d, const wos_spheres* spheres, const wos_boxes* boxes,
         if (e == hipSuccess) e = hipMemcpy(D->cl_f, cf.data(), cf_elems * sizeof(float), hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(D->cl_d, cd.data(), cl_elems * sizeof(double), hipMemcpyHostToDevice);
     }
-    // cell lists
+    // cell lists; they only save work, so where there is no room for them the
+    // domain does without (its steps scan clusters)
     if (ns >= kGridMin || nb >= kGridMin) plan_grid(D, D->grid);
+    auto build_lists = [&](bool box, const float* rows, int64_t m, GridCell** cells, uint32_t** list) {
+        const hipError_t g = build_grid(D->grid, d, box, rows, m, cells, list);
+        if (g != hipErrorOutOfMemory) return g;
+        (void)hipGetLastError();
+        return hipSuccess;
+    };
     if (D->grid.cells) {
         if (e == hipSuccess && ns >= kGridMin)
-            e = build_grid(D->grid, d, false, D->sph_f, ns + (D->goal_in_list ? 1 : 0), &D->sph_cells, &D->sph_list);
-        if (e == hipSuccess && nb >= kGridMin)
-            e = build_grid(D->grid, d, true, D->box_f, nb, &D->box_cells, &D->box_list);
+            e = build_lists(false, D->sph_f, ns + (D->goal_in_list ? 1 : 0), &D->sph_cells, &D->sph_list);
+        if (e == hipSuccess && nb >= kGridMin) e = build_lists(true, D->box_f, nb, &D->box_cells, &D->box_list);
     }
     if (e != hipSuccess) {
         wos_destroy_domain(D);

@@ -67,3 +67,33 @@ assert b"out_jac" in B.lib.wos_last_error()
 assert B.lib.wos_estimate_jac(dom.handle, p, 1, 8, 1.0, 1e-3, 1, None, None, None, p, None, None) == B.WOS_EINVAL
 assert b"out_u" in B.lib.wos_last_error()
 """)
+
+
+@pytest.mark.parametrize("boxes", [False, True])
+def test_domain_without_room_for_its_lists(run, boxes):
+    """The cell lists only save work: a domain whose lists cannot be allocated
+    is made without them (its steps scan clusters); one whose obstacles cannot
+    is refused."""
+    run(f"""
+s = S.scene_spheres(2, m_sph=200, n_queries=1)
+if {boxes}:
+    s.update(box_c=s["sph_c"], box_h=np.repeat(s["sph_r"][:, None], 2, 1), sph_c=np.zeros((0, 2)), sph_r=np.zeros(0))
+dom = B.Domain(s)
+batch(dom, 2, 3, 100)
+(l,) = launches("persistent_kernel")
+assert "persistent_kernelILb0ELb0ELb1E" in l[3], l  # <forward, no source, lists, ...>
+F.fake_hip_fail_above(1 << 20)  # 204800 cells take 1.6 MB and more, every other table below 0.1
+dom2 = B.Domain(s)
+assert F.hipGetLastError() == 0
+F.fake_hip_clear()
+F.fake_hip_fail_above(0)
+batch(dom2, 2, 3, 100)
+(l,) = launches("persistent_kernel")
+assert "persistent_kernelILb0ELb0ELb0E" in l[3], l  # <forward, no source, no lists, ...>
+F.fake_hip_fail_above(256)
+try:
+    B.Domain(s)
+    raise SystemExit("made without its obstacles")
+except B.WosError as e:
+    assert e.code == -3, e
+""")
