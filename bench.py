@@ -731,7 +731,7 @@ def main():
         out["autotune"] = dict(tune, basis="wos_autotune_batch on this batch before timing: coordinate descent "
                                             "over waves per block, units per wave, grid multiple, walks per lane, then lanes "
                                             "per walker G doubled (then halved) while faster; ms_default = one "
-                                            "launch with the built-in shape (4, 4, 1, 2, G = 1)",
+                                            "launch with the untuned call's shape, where the search starts",
                                gain_vs_default=tune["ms_default"] / ms_step)
 
     if not args.no_plain:

@@ -407,7 +407,7 @@ typedef struct {
     int walks_per_lane;   /* least walks each walk-carrying lane takes from a work unit */
     int lanes_per_walker; /* G = 1, 2, 4, ..., 64: a wave carries 64 / G walks at once;
                              all 64 lanes share those walks' member scans */
-    double ms_default;    /* launch time with the built-in shape (4, 4, 1, 2, 1) */
+    double ms_default;    /* launch time of an untuned call (the search starts there) */
     double ms_best;       /* launch time with the chosen shape */
     int tried;            /* shapes timed */
 } wos_tune_result;
@@ -416,7 +416,7 @@ typedef struct {
  * wos_autotune_batch -- time the persistent launch of the caller's own batch
  * (arguments as wos_estimate_batch; fused != 0: forward + backward with
  * u-bar = 1, else forward only) for launch shapes reached by coordinate
- * descent from the built-in one: waves per block {1, 2, 4}, units per wave
+ * descent from the untuned call's: waves per block {1, 2, 4}, units per wave
  * {1, 2, 4, 8, 16}, grid multiple {1, 2}, walks per lane {1, 2, 4}, one
  * parameter at a time with the others held, then lanes per walker G (fewer
  * walks per wave, more waves, when the batch has too few walks to fill the
@@ -440,10 +440,10 @@ int wos_autotune_batch(const wos_domain* const* envs, int n_envs, const float* q
  * M sphere obstacles and Q queries (fused forward + backward), recorded in
  * the cache file (JSON, created or updated) under the bucket of (d, M, Q).
  * Batched launches look up their batch mix first, then the bucket of their
- * heaviest environment, else use the built-in shape (launches of at most 262144
- * walks: one walk per lane, and fewer walks per wave the fewer there are); the
- * cache is read from
- * cache_path (or $WOS_AUTOTUNE_CACHE when wos_set_autotune_cache was not
+ * heaviest environment, else use the built-in shape: (4, 4, 1, 2, 1) in the
+ * order of wos_tune_result, and in launches of at most 262144 walks one walk per
+ * lane and fewer walks per wave (G up to 8) the fewer there are.  The cache is
+ * read from cache_path (or $WOS_AUTOTUNE_CACHE when wos_set_autotune_cache was not
  * called).  Blocks the calling thread (synchronises the device).
  */
 int wos_autotune(int d, int64_t n_obstacles, int64_t n_queries, int64_t n_walks,

@@ -1145,7 +1145,7 @@ int run_batch(const wos_domain* const* envs, int n_envs, const float* queries, c
 
 // Launch-shape search on a batch: the persistent launch (forward + backward
 // with u-bar = 1 when fused) timed with HIP events for shapes reached by
-// coordinate descent from the built-in shape.  Each of waves per block,
+// coordinate descent from the shape an untuned call of the batch takes.  Each of waves per block,
 // units per wave, grid multiple and walks per lane in turn runs over its
 // candidate values with the others held; a shape replaces the best only when
 // it is faster by more than 0.5 % (launch times repeat to about 0.1 %), and a
@@ -1191,6 +1191,9 @@ int tune_batch(const wos_domain* const* envs, int n_envs, const float* queries, 
         ms = f;
     };
     Tune cur;
+    int64_t walks = 0;
+    for (int i = 0; i < n_envs; ++i) walks += (q_off[i + 1] - q_off[i]) * n_walks[i];
+    small_launch(walks, cur);
     double best_ms = 0.0, ms = 0.0;
     time_one(cur, ms);  // untimed: first launch of the shape
     time_one(cur, best_ms);

@@ -97,3 +97,26 @@ try:
 except B.WosError as e:
     assert e.code == -3, e
 """)
+
+
+@pytest.mark.parametrize("q,n", [(1, 100), (3, 1000), (1, 100000), (7, 30000), (200, 4096)])
+def test_tuner_starts_from_the_untuned_shape(run, q, n):
+    """Where every shape takes the same time the tuner keeps the one it started
+    from, which is what an untuned call of the batch launches, so ms_default is
+    that call's time."""
+    run(f"""
+dom = B.Domain(S.scene_spheres(3, m_sph=40, n_queries=1))
+batch(dom, 3, {q}, {n})
+(plain,) = launches("persistent_kernel")
+F.fake_hip_clear()
+r = batch(dom, 3, {q}, {n}, "tune")
+assert launches("persistent_kernel")[0][:3] == plain[:3], (launches("persistent_kernel")[0], plain)
+assert r.ms_best == r.ms_default == 1.0
+F.fake_hip_clear()
+batch(dom, 3, {q}, {n})  # the kept shape
+assert launches("persistent_kernel")[0][:3] == plain[:3]
+walks = {q} * {n}
+want = 8 if walks * 8 <= 163840 else 4 if walks * 4 <= 163840 else 2 if walks * 2 <= 163840 else 1
+assert r.lanes_per_walker == want and r.walks_per_lane == (1 if walks <= 262144 else 2), (r.lanes_per_walker, r.walks_per_lane)
+assert (r.waves_per_block, r.units_per_wave, r.grid_mult) == (4, 4, 1)
+""")
