@@ -66,22 +66,29 @@ extern "C" {
 /* flags */
 #define WOS_FP32 0u
 #define WOS_FP64 1u
-#define WOS_FULL_SCAN 2u /* scan every obstacle each step (no cluster culling);
-                            same walks and results, more work: for testing */
-#define WOS_SCALAR_CULL 4u /* FP32: cluster tests on the vector ALUs instead of the
-                              matrix cores; same walks and results */
-#define WOS_WAVE_SCAN 8u   /* FP32: every lane scans the members of every cluster
+#define WOS_FULL_SCAN 2u /* scan every obstacle each step (no cell lists, no
+                            cluster culling): same walks, more work, for testing
+                            (kernels that differ in their scan may add a query's
+                            walks up in another order, in FP64) */
+#define WOS_SCALAR_CULL 4u /* steps scan clusters instead of reading cell lists,
+                              in FP32 with the cluster tests on the vector ALUs
+                              instead of the matrix cores; same walks */
+#define WOS_WAVE_SCAN 8u   /* steps scan clusters instead of reading cell lists; in
+                              FP32 every lane scans the members of every cluster
                               some lane of its wave needs, instead of queuing the
                               needed (walker, cluster) pairs; same walks */
 #define WOS_OUT_FP64 16u   /* wos_estimate with FP32 walks: out_u and out_grad are
                               double, the FP64 walk sums without rounding to FP32
                               (means below FP32's range stay); other calls reject it */
-#define WOS_NO_BOX_TEST 32u /* FP32 pair scan: every (walker, cluster) pair the
-                               cluster bound keeps has its members scanned, without
-                               the bounding-box test; same walks.  By default the
-                               box test runs where the obstacles depend on 6 or
-                               more coordinates (it culls little below that) */
-#define WOS_BOX_TEST 64u    /* FP32 pair scan: the bounding-box test in every
+#define WOS_NO_BOX_TEST 32u /* FP32 cluster scans by pairs: every (walker, cluster)
+                               pair the cluster bound keeps has its members
+                               scanned, without the bounding-box test; same walks.
+                               By default the box test runs where the obstacles
+                               depend on 6 or more coordinates (it culls little
+                               below that).  Cell lists stay in use: where the
+                               steps read them this flag and the next act on the
+                               scan at the query points only */
+#define WOS_BOX_TEST 64u    /* the same scans: the bounding-box test in every
                                dimension; same walks (not with WOS_NO_BOX_TEST) */
 
 /* boundary-data modes */
