@@ -30,6 +30,14 @@ class WoSFunction(torch.autograd.Function):
 
     _cache = {}
 
+    @classmethod
+    def apply(cls, *args, **kwargs):
+        # needs_input_grad tells of the inputs alone: without grad mode nothing
+        # can ask for a gradient, and the estimate needs no derivatives' sums
+        if not torch.is_grad_enabled():
+            args = [a.detach() if isinstance(a, torch.Tensor) else a for a in args]
+        return super().apply(*args, **kwargs)
+
     @staticmethod
     def _digest(obj, h):
         """Feed the scene's contents (arrays by value, nested dicts in key
