@@ -195,7 +195,7 @@ typedef struct {
  * obstacles of a kind on, a table of cells over the outer boundary's box lists
  * the obstacles that can be nearest in each cell (built on the device during
  * this call); walk steps read their cell's list.  The table takes 0.2 MB for
- * 16 obstacles, 5 for 256, 5 to 20 for 2048 (2- to 8-D, uniform) and at most
+ * 16 obstacles, 4 to 7 for 256, 4 to 30 for 2048 (2- to 8-D, uniform) and at most
  * 150 MB a kind.  Where a cell would list more obstacles than its header can
  * count, or there is no memory for the table, the domain has none and its steps
  * scan clusters (as do those of every environment of a batch with it).

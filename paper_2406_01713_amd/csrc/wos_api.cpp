@@ -73,6 +73,7 @@ struct wos_domain {
     double* arm_d = nullptr;
     int device = 0;
     int64_t n_sph = 0, n_box = 0;
+    unsigned char* tables = nullptr;  // the four tables that follow
     float* sph_f = nullptr;
     double* sph_d = nullptr;
     float* box_f = nullptr;
@@ -101,7 +102,7 @@ struct wos_domain {
     size_t off_sph_cb = 0, off_box_cb = 0;  // cluster bounding boxes (FP32 buffer only)
     // cell lists (see kGridMin), shared by both precisions; null: none
     GridBuild grid;
-    GridCell* sph_cells = nullptr;
+    GridCell* sph_cells = nullptr;  // each kind's table, its lists behind the headers
     GridCell* box_cells = nullptr;
     uint32_t* sph_list = nullptr;
     uint32_t* box_list = nullptr;
@@ -1438,14 +1439,36 @@ int wos_create_domain(int d, const wos_spheres* spheres, const wos_boxes* boxes,
         }
     }
     hipError_t e = hipGetDevice(&D->device);
-    if (e == hipSuccess) e = hipMalloc(&D->sph_f, sf.size() * sizeof(float));
-    if (e == hipSuccess) e = hipMalloc(&D->sph_d, sd.size() * sizeof(double));
-    if (e == hipSuccess) e = hipMalloc(&D->box_f, bf.size() * sizeof(float));
-    if (e == hipSuccess) e = hipMalloc(&D->box_d, bd.size() * sizeof(double));
-    if (e == hipSuccess) e = hipMemcpy(D->sph_f, sf.data(), sf.size() * sizeof(float), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(D->sph_d, sd.data(), sd.size() * sizeof(double), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(D->box_f, bf.data(), bf.size() * sizeof(float), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(D->box_d, bd.data(), bd.size() * sizeof(double), hipMemcpyHostToDevice);
+    // both kinds' tables in both precisions, in one allocation and one copy
+    {
+        const size_t nsd = sd.size() * sizeof(double), nbd = bd.size() * sizeof(double);
+        const size_t nsf = sf.size() * sizeof(float), nbf = bf.size() * sizeof(float);
+        const size_t o1 = align256(nsd), o2 = o1 + align256(nbd), o3 = o2 + align256(nsf);
+        std::vector<unsigned char> tab(o3 + nbf, 0);
+        std::memcpy(tab.data(), sd.data(), nsd);
+        std::memcpy(tab.data() + o1, bd.data(), nbd);
+        std::memcpy(tab.data() + o2, sf.data(), nsf);
+        std::memcpy(tab.data() + o3, bf.data(), nbf);
+        if (e == hipSuccess) e = hipMalloc(&D->tables, tab.size());
+        if (e == hipSuccess) e = hipMemcpy(D->tables, tab.data(), tab.size(), hipMemcpyHostToDevice);
+        D->sph_d = (double*)D->tables;
+        D->box_d = (double*)(D->tables + o1);
+        D->sph_f = (float*)(D->tables + o2);
+        D->box_f = (float*)(D->tables + o3);
+    }
+    // cell lists, built on the device while the host makes the clusters.  They
+    // only save work: where there is no room for them the domain does without
+    // (its steps scan clusters).
+    const int64_t n_listed[2] = {ns >= kGridMin ? ns + (D->goal_in_list ? 1 : 0) : 0, nb >= kGridMin ? nb : 0};
+    GridJob jobs[2];
+    auto unless_full = [](hipError_t g) {
+        if (g != hipErrorOutOfMemory) return g;
+        (void)hipGetLastError();
+        return hipSuccess;
+    };
+    if (n_listed[0] || n_listed[1]) plan_grid(D, D->grid);
+    for (int k = 0; k < 2 && e == hipSuccess && D->grid.cells; ++k)
+        e = unless_full(grid_start(D->grid, d, k == 1, k ? D->box_f : D->sph_f, n_listed[k], jobs[k]));
     if (e == hipSuccess && D->n_arm > 0) {
         const size_t na = 2 * (size_t)D->n_arm;
         std::vector<float> af(arm->points, arm->points + na);
@@ -1500,19 +1523,11 @@ int wos_create_domain(int d, const wos_spheres* spheres, const wos_boxes* boxes,
         if (e == hipSuccess) e = hipMemcpy(D->cl_f, cf.data(), cf_elems * sizeof(float), hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(D->cl_d, cd.data(), cl_elems * sizeof(double), hipMemcpyHostToDevice);
     }
-    // cell lists; they only save work, so where there is no room for them the
-    // domain does without (its steps scan clusters)
-    if (ns >= kGridMin || nb >= kGridMin) plan_grid(D, D->grid);
-    auto build_lists = [&](bool box, const float* rows, int64_t m, GridCell** cells, uint32_t** list) {
-        const hipError_t g = build_grid(D->grid, d, box, rows, m, cells, list);
-        if (g != hipErrorOutOfMemory) return g;
-        (void)hipGetLastError();
-        return hipSuccess;
-    };
-    if (D->grid.cells) {
-        if (e == hipSuccess && ns >= kGridMin)
-            e = build_lists(false, D->sph_f, ns + (D->goal_in_list ? 1 : 0), &D->sph_cells, &D->sph_list);
-        if (e == hipSuccess && nb >= kGridMin) e = build_lists(true, D->box_f, nb, &D->box_cells, &D->box_list);
+    for (int k = 0; k < 2; ++k) {
+        if (e == hipSuccess)
+            e = unless_full(grid_finish(D->grid, d, k == 1, k ? D->box_f : D->sph_f, n_listed[k], jobs[k],
+                                        k ? &D->box_cells : &D->sph_cells, k ? &D->box_list : &D->sph_list));
+        (void)hipFree(jobs[k].hd);
     }
     if (e != hipSuccess) {
         wos_destroy_domain(D);
@@ -1525,18 +1540,13 @@ int wos_create_domain(int d, const wos_spheres* spheres, const wos_boxes* boxes,
 void wos_destroy_domain(wos_domain* D)
 {
     if (!D) return;
-    (void)hipFree(D->sph_f);
-    (void)hipFree(D->sph_d);
-    (void)hipFree(D->box_f);
-    (void)hipFree(D->box_d);
+    (void)hipFree(D->tables);
     (void)hipFree(D->cl_f);
     (void)hipFree(D->cl_d);
     (void)hipFree(D->arm_f);
     (void)hipFree(D->arm_d);
     (void)hipFree(D->sph_cells);
     (void)hipFree(D->box_cells);
-    (void)hipFree(D->sph_list);
-    (void)hipFree(D->box_list);
     delete D;
 }
 

@@ -99,13 +99,21 @@ struct GridBuild {
     float olo[kMaxDim], ohi[kMaxDim], oc[kMaxDim], orad = 0;
 };
 
-// Builds the lists of m obstacles (device FP32 rows of dimension d) into
-// arrays it allocates; *cells stays null, with hipSuccess, where the lists
-// would take more than kGridEntriesMax entries or one of them more than a
-// count byte says.  Synchronises the device.
+// The lists of m obstacles (device FP32 rows of dimension d): grid_start
+// enqueues their build on the default stream, grid_finish waits for it and hands
+// over one allocation, whose start *cells receives (*list points into it).
+// *cells stays null, with hipSuccess, where the lists would take more than
+// kGridEntriesMax entries or one of them more than a count byte says.  A job
+// started but not finished is given up by freeing its hd.
 constexpr uint32_t kGridEntriesMax = 1u << 25;
-hipError_t build_grid(const GridBuild& g, int d, bool box, const float* rows, int64_t m, GridCell** cells,
-                      uint32_t** list);
+struct GridJob {
+    GridCell* hd = nullptr;
+    unsigned parts = 0;  // of the list, `cap` entries each
+    uint32_t cap = 0;
+};
+hipError_t grid_start(const GridBuild& g, int d, bool box, const float* rows, int64_t m, GridJob& job);
+hipError_t grid_finish(const GridBuild& g, int d, bool box, const float* rows, int64_t m, GridJob& job,
+                       GridCell** cells, uint32_t** list);
 
 // Fill kernels (used instead of hipMemsetAsync so the calls are capturable).
 hipError_t launch_fill_u32(unsigned* p, int64_t n, unsigned v, hipStream_t st);
