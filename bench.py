@@ -42,7 +42,8 @@ JOB_CPU_SHARE = 16
 # not use
 PEAK_FP32_UNPACKED_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
 KERNEL_SOURCES = ["paper_2406_01713_amd/csrc/" + f for f in
-                  ("wos_device.hpp", "wos_walk.hpp", "wos_persistent.hip", "wos_kernels.hip", "wos_params.hpp")]
+                  ("wos_device.hpp", "wos_walk.hpp", "wos_persistent.hip", "wos_kernels.hip", "wos_params.hpp",
+                   "wos_launch.hpp", "wos_grid.hip", "wos_api.cpp")]  # the last three: what lists and launches hold
 
 
 def log(*a):
@@ -74,8 +75,9 @@ def executed_flops(s, st):
     5d + 1, cluster bounding boxes 6d + 2 (per axis two differences, a
     three-way max, a multiply-add; a square root and the margin), the outer
     box 4d per walk-step and, where the obstacles are all scanned instead of
-    looked up in cell lists (column 14 is 0), the goal 3d + 2.  Returns
-    (valu, walk_steps)."""
+    looked up in cell lists (column 14 is 0), the goal 3d + 2.  Every environment
+    timed here has cell lists; steps that scanned clusters instead would
+    evaluate the goal too.  Returns (valu, walk_steps)."""
     d, n = s["d"], s["n_walks"]
     steps = st[:, 9]
     goal = (st[:, 14] == 0) * (1.0 if s.get("goal_r") is not None else 0.0)

@@ -852,18 +852,28 @@ struct BatchLayout {
     int block = 256;
 };
 
-// Shape of a launch that does not fill the device's walk-carrying lanes (4096
-// waves of 64): every walk then runs at once, the launch takes as long as its
-// longest walk, and what counts is the time of one step.  One walk per lane
-// (six environments of 1-13 queries x 1024 walks 1094 -> 882 us, one planning
-// start with 1e5 walks in 2-D 343 -> 311 us; 2^19 walks, two per lane, 2.03 ms
-// against 2.51 with one, so fuller launches keep two); and, while they still
-// fit five eighths of the lanes, fewer walks per wave, so that fewer
-// steps wait for some walk's end (882 -> 804 us with 16 per wave; 1e5 walks
-// with 32 per wave 1 % slower).
+// Waves of a full MI355X at four per SIMD (256 CUs x 4 SIMDs), as the walk kernels
+// of most shapes run.  A constant: the rules below, and with `fewest` what the
+// no-allocation call accepts, depend on a batch's sizes alone.
+constexpr int64_t kFullWaves = 4096;
+
+// Shape of a launch that does not fill the device's walk-carrying lanes: every
+// walk then runs at once, the launch takes as long as its longest walk, and what
+// counts is the time of one step.  One walk per lane (six environments of 1-13
+// queries x 1024 walks 1094 -> 882 us, one planning start with 1e5 walks in 2-D 343
+// -> 311 us; 2^19 walks, two per lane, 2.03 ms against 2.51 with one, so fuller
+// launches keep two); and, while they still fit five eighths of the lanes, fewer
+// walks per wave, so that fewer steps wait for some walk's end (882 -> 804 us with
+// 16 per wave).  The line, eight queries of 2-, 3-, 4- and 7-D, us with the shape
+// it gives | with one lane per walk | with twice as many lanes per walk: 10000
+// walks (8 lanes) 229, 368, 397, 537 | 240, 378, 430, 585 | 235, 373, 403, 542;
+// 20000 (8) 233, 382, 408, 681 | 250, 389, 437, 665 | 265, 400, 425, 768; 40000 (4)
+// 239, 385, 428, 696 | 243, 383, 441, 666 | 264, 408, 452, 799; 80000 (2) 244, 394,
+// 536, 725 | 242, 393, 539, 728 | 266, 424, 534, 837.  At the line few dimensions
+// still gain and 7-D loses 2 to 4 %; past it every one loses.
 void small_launch(int64_t walks, Tune& t)
 {
-    const int64_t lanes = 4096 * kWave;
+    const int64_t lanes = kFullWaves * kWave;
     if (walks > lanes) return;
     t.walks_per_lane = 1;
     while (t.lanes_per_walker < kSmallSpread && walks * t.lanes_per_walker * 2 <= lanes * 5 / 8) t.lanes_per_walker *= 2;
@@ -916,7 +926,7 @@ void plan_batch(const wos_domain* const* envs, const int64_t* q_off, int n_envs,
     L.block = block;
     L.grid = std::max(1, resident_blocks * t.grid_mult);
     const int64_t waves = (int64_t)L.grid * (block / kWave);
-    const int64_t target = (fewest ? std::min<int64_t>(waves, 4096 * t.grid_mult) : waves) * t.units_per_wave;
+    const int64_t target = (fewest ? std::min<int64_t>(waves, kFullWaves * t.grid_mult) : waves) * t.units_per_wave;
     // walk ranges of about equal steps: the launch's steps / target units,
     // over the typical walk length of the env's dimension; a multiple of the
     // walk-carrying lanes, at least walks_per_lane walks per such lane
@@ -1654,7 +1664,7 @@ int wos_debug_cluster_boxes(int d, const wos_spheres* spheres, const wos_boxes* 
     return WOS_OK;
 }
 
-// Walks per wave of the plain kernel.  Up to one walk per lane of the 4096
+// Walks per wave of the plain kernel.  Up to one walk per lane of the full
 // resident waves (4 per SIMD), one per lane, or in FP32 spread wider (small_launch;
 // FP64 steps are bound by issue even alone: 51200 5-D walks forward + backward
 // 2.36 ms spread over twice the waves, 2.19 not).  Above,
@@ -1667,7 +1677,7 @@ static int32_t plain_range(int64_t Q, int64_t n_walks, bool fp64, int& lanes)
     if (!fp64) small_launch(std::max<int64_t>(Q, 1) * n_walks, t);
     lanes = kWave / t.lanes_per_walker;
     if (lanes < kWave) return lanes;
-    const double per = (double)std::max<int64_t>(Q, 1) * (double)n_walks / 4096.0;
+    const double per = (double)std::max<int64_t>(Q, 1) * (double)n_walks / (double)kFullWaves;
     const double want = std::max(0.25 * per, std::min(256.0, per));
     const int64_t r = ((int64_t)std::min(std::ceil(want), 1e9) + kWave - 1) / kWave * kWave;
     return (int32_t)std::max<int64_t>(kWave, std::min<int64_t>(r, (n_walks + kWave - 1) / kWave * kWave));

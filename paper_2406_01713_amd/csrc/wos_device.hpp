@@ -1217,7 +1217,7 @@ __device__ __forceinline__ T horner(const C& c, int nt, T y)
 //   K_1 = ln(z/2) I_1 + 1/z - (z/4) sum (H_k + H_{k+1} - 2 g) t^k / (k! (k+1)!),
 // six terms (3e-9 relative).  Above, sqrt(z) e^z K_n(z) as a polynomial of
 // degree 11 in 1/z, fitted to its values on (0, 1] in FP64 (relative error
-// below 3e-9 before FP32 rounding, 1e-7 with it).
+// below 3e-9; evaluated in FP32 at most 3e-7, 0.7e-7 rms).
 __device__ __forceinline__ void bessel_k01(float z, float& k0, float& k1)
 {
     constexpr float a0[12] = {

@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "wos_launch.hpp"
 #include "wos_walk.hpp"
@@ -423,22 +424,39 @@ template hipError_t launch_plain<float>(int, bool, bool, bool, const EnvP<float>
 template hipError_t launch_plain<double>(int, bool, bool, bool, const EnvP<double>*, const double*, int64_t, int64_t,
                                          int32_t, int, int64_t, uint32_t, double*, double*, hipStream_t);
 
+// f(SRC, LISTS, MAXD) as constants: the variant for a batch's features (the
+// kernel for at most 5 dimensions reads lists only).
+template <typename F>
+static auto persistent_variant(bool src, bool lists, int max_d, F f)
+{
+    using std::integral_constant;
+    using Y = std::true_type;
+    using N = std::false_type;
+    using Any = integral_constant<int, kMaxDim>;
+    using Low = integral_constant<int, 5>;
+    if (!lists) return src ? f(Y{}, N{}, Any{}) : f(N{}, N{}, Any{});
+    if (max_d > Low::value) return src ? f(Y{}, Y{}, Any{}) : f(N{}, Y{}, Any{});
+    return src ? f(Y{}, Y{}, Low{}) : f(N{}, Y{}, Low{});
+}
+
 hipError_t launch_persistent(bool bwd, bool src, bool lists, int grid, int block, const EnvP<float>* envs,
                              const BatchEnv* benv, int n_benv, int max_d, const float* queries, int64_t total_units,
                              uint32_t key0, uint32_t key1, const uint64_t* key_add, unsigned* counter,
                              double* partials, hipStream_t st)
 {
     if (total_units == 0) return hipSuccess;
-    auto* go = src ? (!lists ? launch_persistent_variant<true, false, kMaxDim> : max_d > 5 ? launch_persistent_variant<true, true, kMaxDim> : launch_persistent_variant<true, true, 5>)
-                   : (!lists ? launch_persistent_variant<false, false, kMaxDim> : max_d > 5 ? launch_persistent_variant<false, true, kMaxDim> : launch_persistent_variant<false, true, 5>);
-    return go(bwd, grid, block, envs, benv, n_benv, max_d, queries, total_units, key0, key1, key_add, counter, partials, st);
+    return persistent_variant(src, lists, max_d, [&](auto s, auto l, auto m) {
+        return launch_persistent_variant<s.value, l.value, m.value>(bwd, grid, block, envs, benv, n_benv, max_d,
+                                                                    queries, total_units, key0, key1, key_add, counter,
+                                                                    partials, st);
+    });
 }
 
 int persistent_resident_blocks(bool bwd, bool src, bool lists, int max_d, int block)
 {
-    auto* per = src ? (!lists ? persistent_blocks_per_cu<true, false, kMaxDim> : max_d > 5 ? persistent_blocks_per_cu<true, true, kMaxDim> : persistent_blocks_per_cu<true, true, 5>)
-                    : (!lists ? persistent_blocks_per_cu<false, false, kMaxDim> : max_d > 5 ? persistent_blocks_per_cu<false, true, kMaxDim> : persistent_blocks_per_cu<false, true, 5>);
-    const int per_cu = per(bwd, max_d, block);
+    const int per_cu = persistent_variant(src, lists, max_d, [&](auto s, auto l, auto m) {
+        return persistent_blocks_per_cu<s.value, l.value, m.value>(bwd, max_d, block);
+    });
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess) return per_cu;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 1;
