@@ -1674,10 +1674,11 @@ int wos_debug_cluster_boxes(int d, const wos_spheres* spheres, const wos_boxes* 
 static int32_t plain_range(int64_t Q, int64_t n_walks, bool fp64, int& lanes)
 {
     Tune t;
-    if (!fp64) small_launch(std::max<int64_t>(Q, 1) * n_walks, t);
+    const double walks = (double)std::max<int64_t>(Q, 1) * (double)n_walks;  // up to 2^63
+    if (!fp64 && walks <= (double)(kFullWaves * kWave)) small_launch((int64_t)walks, t);
     lanes = kWave / t.lanes_per_walker;
     if (lanes < kWave) return lanes;
-    const double per = (double)std::max<int64_t>(Q, 1) * (double)n_walks / (double)kFullWaves;
+    const double per = walks / (double)kFullWaves;
     const double want = std::max(0.25 * per, std::min(256.0, per));
     const int64_t r = ((int64_t)std::min(std::ceil(want), 1e9) + kWave - 1) / kWave * kWave;
     return (int32_t)std::max<int64_t>(kWave, std::min<int64_t>(r, (n_walks + kWave - 1) / kWave * kWave));

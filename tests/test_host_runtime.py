@@ -99,6 +99,21 @@ except B.WosError as e:
 """)
 
 
+def test_largest_single_environment_call_is_refused(run):
+    """2^32 queries of 2^31 walks, the largest counts the call takes, are 2^63
+    walks: more partial sums than there is memory for, refused before any
+    launch."""
+    run("""
+dom = B.Domain(S.scene_spheres(3, m_sph=8, n_queries=1))
+F.fake_hip_clear()
+F.fake_hip_fail_above(1 << 40)
+p = C.c_void_p(8)
+for q, n in ((1 << 32, 1 << 31), (1 << 32, 1 << 30), (1 << 31, 1 << 31)):
+    assert B.lib.wos_estimate(dom.handle, p, q, n, 1.0, 1e-3, 1, p, None, None, None, None) == -3, (q, n)
+assert not launches("plain_kernel"), launches("")
+""")
+
+
 @pytest.mark.parametrize("q,n", [(1, 100), (3, 1000), (1, 100000), (7, 30000), (200, 4096)])
 def test_tuner_starts_from_the_untuned_shape(run, q, n):
     """Where every shape takes the same time the tuner keeps the one it started
