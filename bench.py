@@ -325,7 +325,7 @@ def ragged_c4(B, torch, st, reps=3, plain_reps=2, tune_cache=None):
            "batched_vs_plain_forward": pf_ms / fwd_ms,
            "batched_vs_plain_fwd_plus_bwd": (pf_ms + pb_ms) / fused_ms,
            "batched_vs_plain_like_for_like": pb_ms / fused_ms,
-           "autotune": dict(tune, gain_vs_default=tune["ms_default"] / fused_ms)}
+           "autotune": dict(tune, gain_vs_default=tune["ms_default"] / tune["ms_best"])}
     del pl, bat
     return res
 
@@ -733,8 +733,9 @@ def main():
         out["autotune"] = dict(tune, basis="wos_autotune_batch on this batch before timing: coordinate descent "
                                             "over waves per block, units per wave, grid multiple, walks per lane, then lanes "
                                             "per walker G doubled (then halved) while faster; ms_default = one "
-                                            "launch with the untuned call's shape, where the search starts",
-                               gain_vs_default=tune["ms_default"] / ms_step)
+                                            "launch with the untuned call's shape, where the search starts, "
+                                            "ms_best = one with the chosen shape, both without work statistics",
+                               gain_vs_default=tune["ms_default"] / tune["ms_best"])
 
     if not args.no_plain:
         t = time.perf_counter()
