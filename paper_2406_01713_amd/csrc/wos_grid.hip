@@ -451,7 +451,10 @@ hipError_t grid_finish(const GridBuild& g, int d, bool box, const float* rows, i
             total += told[i * kToldStride];
         }
         const bool overfull = e == hipSuccess && told[kToldWords - 1] != 0;
-        if (e == hipSuccess && !overfull && most <= job.cap) {
+        // obstacles in a corner of the box need far less room than was guessed: from
+        // 16 MB on that is worth a second build
+        const bool loose = most < job.cap / 2 && (uint64_t)job.parts * (job.cap - most) > (4u << 20);
+        if (e == hipSuccess && !overfull && most <= job.cap && !loose) {
             *cells = job.hd;
             *list = d_told + kToldWords;
             job.hd = nullptr;
@@ -460,12 +463,12 @@ hipError_t grid_finish(const GridBuild& g, int d, bool box, const float* rows, i
         (void)hipFree(job.hd);
         job.hd = nullptr;
         if (e != hipSuccess || overfull || total > kGridEntriesMax) return e;
-        // a second time, with room for all
+        // a second time, with room for what there is
         if ((uint64_t)job.parts * most > kGridEntriesMax) {
             job.parts = 1;
             most = (uint32_t)total;
         }
-        job.cap = most;
+        job.cap = std::max(most, 1u);
         const hipError_t again = grid_start(g, d, box, rows, m, job);
         if (again != hipSuccess) {
             (void)hipFree(job.hd);

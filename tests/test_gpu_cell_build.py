@@ -83,3 +83,20 @@ def test_crowded_tiles(B, d, boxes):
     s["queries"][:3] = -0.05 + rng.uniform(-0.02, 0.02, size=(3, d))
     s["eps"] = 1e-4
     _check(B, s)
+
+
+def test_less_entries_than_room(B):
+    """12000 spheres in a slab along one face of a 6-D box: far fewer entries than
+    in a uniform scene, so the table is built again to their size."""
+    import torch
+    d, m = 6, 12000
+    rng = np.random.default_rng(11)
+    c = rng.uniform(-1.9, 1.9, size=(m, d))
+    c[:, 0] = rng.uniform(1.85, 1.95, size=m)
+    s = _scene(d, c, rng.uniform(0.01, 0.03, size=m), np.full(d, 2.0))
+    _check(B, s)
+    torch.zeros(1, device="cuda")
+    free = torch.cuda.mem_get_info()[0]
+    doms = [B.Domain(s) for _ in range(4)]
+    # uniform: 1.8e7 entries guessed, 73 MB; the clusters' tables take 4 MB
+    assert (free - torch.cuda.mem_get_info()[0]) / len(doms) < 50e6
